@@ -22,10 +22,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libstacklstm.so")
 BUILD = os.path.join(HERE, "_build")
-SOURCES = ["api.hip", "scan.hip", "gemm.hip", "recurrent_fwd.hip", "recurrent_fwd_pipe.hip", "recurrent_bwd.hip",
-           "recurrent_fwd_wide.hip"]
-# per-file flags: the wide forward keeps its U slice in AGPRs and its accumulators in VGPRs
-EXTRA = {"recurrent_fwd_wide.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
+SOURCES = ["api.hip", "scan.hip", "plan.hip", "prep.hip", "contract.hip", "level_fwd.hip", "level_bwd.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
          # packed fp32 instructions stay off: only scalar fp32 ALU code is generated
@@ -64,7 +61,7 @@ def resource_report(text: str) -> dict:
 
 
 # wait states between an MFMA and a read of its result that hipcc inserts in straight-line code
-MFMA_WAITS = {"v_mfma_f32_16x16x4_f32": 10, "v_mfma_f32_16x16x32_bf16": 8}
+MFMA_WAITS = {"v_mfma_f32_16x16x4_f32": 10, "v_mfma_f32_16x16x32_bf16": 8, "v_mfma_f32_16x16x32_f16": 8}
 
 
 def _regs(tok: str) -> set:
@@ -131,7 +128,7 @@ def mfma_branch_hazards(asm: str) -> list:
 
 def _compile(src: str):
     obj = os.path.join(BUILD, src.replace(".hip", ".o"))
-    cmd = [HIPCC, *FLAGS, *EXTRA.get(src, []), "-save-temps", "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [HIPCC, *FLAGS, "-save-temps", "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True, cwd=BUILD)
     if r.returncode != 0:
         sys.stderr.write(r.stdout + r.stderr)

@@ -8,43 +8,32 @@
 
 #include "../../include/stacklstm.h"
 #include "common.h"
-#include "gemm.h"
-#include "rec_config.h"
-#include "recurrent.h"
+#include "contract.h"
+#include "levels.h"
+#include "prep.h"
 
 __global__ void k_init_ctl(uint32_t* ctl, int keep_errors);
-template <bool LDS>
-__global__ void k_scan(const int8_t* ops, int T, int B, int cap, int32_t* ptr, int32_t* top, int32_t* depth_end,
-                       int32_t* gstack, uint32_t* ctl);
+template <bool LDS> __global__ void k_plan(PlanArgs a);
+template <int S>
+__global__ void k_split_x(const float* x, const int32_t* order, int lo, int hi, int I, int Ip, int vec, bf16_t* out,
+                          size_t plane);
+template <int S> __global__ void k_prep_fwd(PrepFwdArgs a);
+template <int S> __global__ void k_prep_bwd(PrepBwdArgs a);
+template <int V>
+__global__ void k_gsum(const float* d, const int32_t* gslot, int T, int B, int H, int G, float* out);
 __global__ void k_gather_top(const int32_t* top, const float* cellv, const float* init, float* out, int T, int B,
-                             int H, int skip_push, uint32_t* ctl);
+                             int H, uint32_t* ctl);
 __global__ void k_gather_top4(const int32_t* top, const float* hcell, const float* h0, float* htop, const float* ccell,
-                              const float* c0, float* ctop, int T, int B, int H, int skip_h, uint32_t* ctl);
-__global__ void k_permute_w(const float* W, float* Wp32, bf16_t* Wp16, bf16_t* WpT16, int I, int H);
+                              const float* c0, float* ctop, int T, int B, int H, uint32_t* ctl);
 __global__ void k_fill_f32(float* p, size_t n, float v);
-__global__ void k_zero_u32(uint32_t* p, int n);
 __global__ void k_zero_ctl_bwd(uint32_t* ctl, int keep_errors);
-__global__ void k_fill_pattern(unsigned char* p, size_t bytes, uint32_t v);
-__global__ void k_h0_bf16(const float* h0, bf16_t* hx, size_t n);
-__global__ void k_to_bf16x8(const float* in, bf16_t* out, size_t n8);
-__global__ void k_push_rows(const int8_t* ops, int n, int32_t* rows, uint32_t* count);
 __global__ void k_zero_nonpush_rows(const int8_t* ops, float* out, size_t n, int cols);
-__global__ void k_gather_hprev(const int32_t* top, const float* hcell, const float* h0, const int32_t* prow,
-                               const uint32_t* count, float* out, int T, int B, int H, uint32_t* ctl);
-__global__ void k_transpose_bf16(const void* src, int src_f32, int ld, int cols, const int32_t* prow,
-                                 const uint32_t* count, int ldo, const int32_t* gtop, int B, bf16_t* out, uint32_t* ctl);
-template <int PREC, int AL, int BL> __global__ void k_gemm(GemmArgs g);
-__global__ void k_gemm_wide(GemmArgs g);
-__global__ void k_gemm_ring(GemmArgs g);
-__global__ void k_reduce_splits(const float* P, int splits, size_t split_stride, int M, int N, int unperm_H,
-                                float* out);
-__global__ void k_scatter_splits(const float* P, const int32_t* rows, const uint32_t* count, size_t max_rows, int N,
-                                 int grid_blocks, int n_tiles, float* dst);
+__global__ void k_reduce_grads(const float* part, int splits, size_t stride, const float* db_part, int groups, int I,
+                               int H, float* dW, float* dU, float* db);
 
 namespace {
 
 constexpr int kDefaultSpin = 1 << 22;
-constexpr int kGemmBM = 128, kGemmBN = 128, kGemmBK = 64;
 
 struct DevInfo { int cus; bool ok; };
 
@@ -66,27 +55,8 @@ int device_cus() {
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 bool al16(const void* q) { return ((uintptr_t)q & 15u) == 0; }
 
-// Rows per group are chosen per kernel (forward and backward differ in register use and so
-// in how many workgroups share a CU): NT/G/per_xcc for the forward, NTb/Gb/per_xcc_b for
-// the backward.
-struct Plan {
-  int prec, KS, ks_eff, NW;
-  int NT, G, per_xcc, pipe;   // pipe: the forward runs the pipelined kernel
-  int fuse, kx;               // fuse: the plain bf16 forward contracts x_t W itself (kx chunks of 32)
-  int wide, NWw;              // wide: the forward runs the 32-unit kernel (NWw workgroups per group)
-  int NTb, Gb, per_xcc_b, NWb; // NWb: backward workgroups per group (32 units each in the lean variant)
-  int gs;                     // the backward runs the gate-split contraction
-  int splits_w, splits_u;
-};
-
-struct Layout {
-  size_t ctl, stack, dep, wp, r1, stash, hx, fwd_end, xbt, hp, dat, dh, dc, dbp, part, prow, total;
-};
-
-Layout layout(const slstm_dims* d);
-
-// Push-row count padded to the K tile: leading dimension of the transposed bf16 operands
-size_t padded_rows(const slstm_dims* d) { return ((size_t)d->T * d->B + 63) / 64 * 64; }
+int planes_of(const slstm_dims* d) { return d->precision == SLSTM_BF16_GEMM ? 1 : 3; }
+int rec_planes_of(const slstm_dims* d) { return d->precision == SLSTM_BF16_GEMM ? 1 : 2; }
 
 bool dims_ok(const slstm_dims* d) {
   if (!d) return false;
@@ -94,158 +64,129 @@ bool dims_ok(const slstm_dims* d) {
   if (d->precision != SLSTM_FP32 && d->precision != SLSTM_BF16_GEMM) return false;
   if (d->H > (d->precision == SLSTM_FP32 ? 512 : 1024)) return false;
   if ((int64_t)d->T * d->B > ((int64_t)1 << 28)) return false;
-  // the persistent kernels address T*B*4H fp32 (fp32 mode) or bf16 values with 32-bit byte offsets
+  // sizes the kernels address with 32-bit byte offsets
   const int64_t esz = d->precision == SLSTM_FP32 ? 4 : 2;
   if ((int64_t)d->T * d->B * 4 * d->H * esz >= ((int64_t)1 << 32)) return false;
   if ((int64_t)d->T * d->B * d->H * 4 >= ((int64_t)1 << 32)) return false;
   return true;
 }
 
-int ks_bucket(int prec, int ks_eff) {
-  const int lo = prec ? 2 : 4;
-  int ks = lo;
-  while (ks < ks_eff) ks *= 2;
-  return ks <= 32 ? ks : -1;
-}
+// Workgroups per group, K chunks of 32 compiled into the recurrent kernels, and groups.
+int groups_nw(int H) { return (H + kLevUnits - 1) / kLevUnits; }
+// Largest number of groups on an XCD of `cus` CUs (one 512-thread workgroup per CU), times 8
+int groups_max(int H, int cus) { return std::min(kLevMaxGroups, 8 * (cus / groups_nw(H))); }
+// As many groups as there are elements and room for: a level's rows of a group are padded to 16
+// and every row costs its group's workgroups a copy, so more groups mean shorter levels.
+int groups_for(int B, int H, int cus) { return std::min(B, groups_max(H, cus)); }
+// Largest batch: 128 elements for each set of ceil(H / 16) workgroup slots of an XCD's 32, at most 64 sets
+int batch_max(int H) { return H > 512 ? 1024 : 128 * std::min(64, 8 * (32 / ((H + 15) / 16))); }
 
-// Split-K slices of dW / dU: about 512 blocks, one round of the GEMM's two workgroups per CU
-// on 256 CUs (measured at large: 1024 blocks 0.26 / 0.37 ms fp32 dW + db / dU, 512 blocks
-// 0.24 / 0.36 ms, 384 or 256 blocks slower; bf16 0.13 / 0.09 -> 0.12 / 0.07 ms)
-int splits_for(int M, int N, int K) {
-  int tiles = ((M + kGemmBM - 1) / kGemmBM) * ((N + kGemmBN - 1) / kGemmBN);
-  int s = std::max(1, 512 / std::max(1, tiles));
-  int max_s = std::max(1, (K + kGemmBK - 1) / kGemmBK);
-  return std::min(std::min(s, 64), max_s);
-}
+struct Plan {
+  int prec, S, NP, KS, NW, G, xcc_cus;   // S: bf16 planes of an operand, NP: planes of the recurrent products
+};
 
-// Chooses rows per group (16*NT) so that every group's workgroups fit on one XCC.
 int make_plan(const slstm_dims* d, Plan* p) {
   if (!dims_ok(d)) return SLSTM_EINVAL;
-  const int prec = d->precision;
-  const int KC = rec_kc(prec);
-  p->prec = prec;
-  p->ks_eff = (d->H + KC - 1) / KC;
-  p->KS = ks_bucket(prec, p->ks_eff);
-  if (p->KS < 0) return SLSTM_EINVAL;
-  p->NW = (d->H + 15) / 16;
-  // the backward compiled for K = 32 bf16 chunks (lean variant) runs 512-thread workgroups
-  // of 32 units, one per CU; the others 256-thread workgroups of 16 units
-  p->NWb = rec_occ(prec, p->KS) == 2 ? (d->H + 31) / 32 : p->NW;
+  p->prec = d->precision;
+  p->S = planes_of(d);
+  p->NW = groups_nw(d->H);
+  p->NP = rec_planes_of(d);
+  p->KS = lev_ks(p->NP, p->NW);
   const int cus = device_cus();
-  const int cu_per_xcc = cus > 0 ? cus / 8 : 32;
-  // smallest row tile count per group whose workgroups (NW per group, groups dealt to the 8
-  // XCCs round-robin) are co-resident on one XCC at the kernel's occupancy
-  // the pipelined forward needs whole 1 KB row segments (vector rows, every K chunk in use)
-  const bool pipe_ok = d->H % (prec ? 8 : 4) == 0 && p->ks_eff == p->KS && p->KS >= 16;
-  p->kx = (d->I + 31) / 32;
-  p->fuse = 0;
-  p->gs = 0;
-  // the backward's gate-split contraction covers exactly H units with whole M tiles; its
-  // partial sums (two step buffers of G x 16*NT rows x NW x H fp32) use the post-loop GEMMs'
-  // partials area
-  const Layout Lp = layout(d);
-  const bool gs_ok = p->ks_eff == p->KS && p->KS * KC == d->H;
-  auto pick = [&](bool bwd, int* NT_out, int* G_out, int* per_out, int* pipe_out) -> int {
-    for (int NT = 1; NT <= 8; NT *= 2) {
-      int G = (d->B + 16 * NT - 1) / (16 * NT);
-      if (G > MAX_GROUPS) continue;
-      int per_xcc = (bwd ? p->NWb : p->NW) * ((G + 7) / 8);
-      int occ = 0;
-      const bool pipe = !bwd && pipe_ok && NT >= 2 && rec_pipe_built(prec, NT, p->KS);
-      // the plain bf16 forward fuses the input projection when one pass covers the group
-      // (x rows copied whole: I % 4 == 0, byte offsets within 32 bits)
-      const bool fuse = !bwd && !pipe && rec_fx_built(prec, p->KS) && rec_ntb(prec, NT, p->KS) == NT &&
-                        rec_fx_fits(16 * NT, p->kx) && d->I % 4 == 0 &&
-                        (int64_t)d->T * d->B * d->I * 4 < ((int64_t)1 << 32) &&
-                        rec_lds_bytes(prec, NT, p->KS) + rec_fx_lds_bytes(16 * NT) <= (size_t)160 * 1024;
-      RecArgs dummy;
-      memset(&dummy, 0, sizeof(dummy));
-      FxArgs fdummy;
-      memset(&fdummy, 0, sizeof(fdummy));
-      fdummy.fuse_x = fuse ? 1 : 0;
-      fdummy.kx = p->kx;
-      const bool gs = bwd && gs_ok && rec_bwd_gs_built(prec, NT, p->KS) &&
-                      (size_t)2 * G * 16 * NT * p->NW * d->H * 4 <= Lp.prow - Lp.part;
-      dummy.bwd_gs = gs ? 1 : 0;
-      hipError_t e = bwd    ? launch_bwd(dummy, prec, NT, p->KS, dim3(0), nullptr, &occ)
-                     : pipe ? launch_fwd_pipe(dummy, prec, NT, p->KS, dim3(0), nullptr, &occ)
-                            : launch_fwd(dummy, fdummy, prec, NT, p->KS, dim3(0), nullptr, &occ);
-      if (e != hipSuccess) {
-        (void)hipGetLastError();                  // a failed query leaves no error for later calls
-        return SLSTM_EDEVICE;
-      }
-      if (per_xcc <= cu_per_xcc * occ) {
-        *NT_out = NT;
-        *G_out = G;
-        *per_out = per_xcc;
-        if (pipe_out) *pipe_out = pipe ? 1 : 0;
-        if (!bwd) p->fuse = fuse ? 1 : 0;
-        if (bwd) p->gs = gs ? 1 : 0;
-        return SLSTM_OK;
-      }
-    }
-    return SLSTM_ENORESIDENT;
-  };
-  // bf16 with H > 512: 16-unit workgroups would need two per CU and spill their U slice;
-  // the wide forward gives each CU one workgroup of 32 units (groups of 128 rows, one per XCC)
-  p->wide = 0;
-  p->NWw = (d->H + 31) / 32;
-  if (prec == SLSTM_BF16_GEMM && d->H > 512 && d->H % 8 == 0 && p->KS == 32 && p->NWw <= cu_per_xcc &&
-      (d->B + 127) / 128 <= 8) {
-    int occ = 0;
-    RecArgs dummy;
-    memset(&dummy, 0, sizeof(dummy));
-    if (launch_fwd_wide(dummy, 8, 32, dim3(0), nullptr, &occ) != hipSuccess) return SLSTM_EDEVICE;
-    if (occ >= 1) {
-      p->wide = 1;
-      p->NT = 8;
-      p->G = (d->B + 127) / 128;
-      p->per_xcc = p->NWw;
-      p->pipe = 0;
-    }
-  }
-  int rc = p->wide ? SLSTM_OK : pick(false, &p->NT, &p->G, &p->per_xcc, &p->pipe);
-  if (rc) return rc;
-  if ((rc = pick(true, &p->NTb, &p->Gb, &p->per_xcc_b, nullptr))) return rc;
-  int64_t K = (int64_t)d->T * d->B;
-  p->splits_w = splits_for(d->I, 4 * d->H, (int)std::min<int64_t>(K, 1 << 30));
-  p->splits_u = splits_for(d->H, 4 * d->H, (int)std::min<int64_t>(K, 1 << 30));
+  if (cus <= 0) return SLSTM_EDEVICE;
+  p->xcc_cus = std::min(32, cus / 8);
+  if (p->xcc_cus < p->NW || d->B > batch_max(d->H)) return SLSTM_ENORESIDENT;
+  p->G = groups_for(d->B, d->H, p->xcc_cus);
   return SLSTM_OK;
 }
 
-// Work-space layout; splits are bounded by 64 so the layout does not depend on the device.
-Layout layout(const slstm_dims* d) {
-  const size_t T = d->T, B = d->B, I = d->I, H = d->H;
-  const bool bf = d->precision == SLSTM_BF16_GEMM;
-  const size_t KP = padded_rows(d);
+// Split K of dW | dU: one workgroup per CU, K slices of at least one 64-row step.
+int tn_tiles(const slstm_dims* d) {
+  const int S = planes_of(d), bm = nt_bm(S), bn = nt_bn(S);
+  return ((4 * d->H + bn - 1) / bn) * ((d->I + bm - 1) / bm + (d->H + bm - 1) / bm);
+}
+int tn_splits(const slstm_dims* d) {
+  const int64_t steps = ((int64_t)d->T * d->B + 63) / 64;
+  return (int)std::max<int64_t>(1, std::min<int64_t>({256 / std::max(1, tn_tiles(d)), 64, steps}));
+}
+
+// Work-space layout. It does not depend on the device (group counts as for 32 CUs per XCD).
+struct Layout {
+  size_t ctl, order, opar, cs, loff, gmax, irow, ics, ioff, cidx, kin, gslot, cnt, elem, walk;
+  size_t wt, wp, uf, ufi, rin, hu, stash, cpn, hq, h3, cn, xs, fwd_end;
+  size_t gf, gc, eg, dcs, dap, sxs, ub, ubi, part, dbp, total;
+  int Ip, Hs, H4s, cap, G;
+  int x_rows;                        // rows of x whose planes fit (all, except in the static work space)
+  size_t walk_lds;                   // bytes of a wave's walk arrays when they live in LDS, else 0
+};
+
+// keep: with the parts that only a backward needs; x_budget: bytes for the planes of x (0 = all rows)
+Layout layout(const slstm_dims* d, bool keep, size_t x_budget) {
+  const size_t T = d->T, B = d->B, I = d->I, H = d->H, S = planes_of(d), N0 = T * B, NN = N0 + B, NP = rec_planes_of(d);
   Layout L;
+  L.Ip = (int)((I + 7) / 8 * 8);
+  L.Hs = (int)((H + 7) / 8 * 8);
+  L.H4s = (int)((4 * H + 7) / 8 * 8);
+  L.cap = (int)T + 2;
+  const int NW = groups_nw(d->H), KS = lev_ks((int)NP, NW);
+  L.G = groups_for(d->B, d->H, 32);
+  const size_t wave_walk = (size_t)2 * L.cap * 4;
+  L.walk_lds = wave_walk <= 147456 ? wave_walk : 0;
   size_t o = 0;
-  L.ctl = o; o += align256(CTL_WORDS * 4);
-  L.stack = o; o += align256(B * (T + 1) * 4);                        // op scan: stacks that do not fit in LDS
-  L.dep = o; o += align256(B * 4);                                     // pointer after the last step
-  L.wp = o; o += align256(I * 4 * H * 4);                             // Wp fp32, or Wp and Wp^T in bf16
-  L.r1 = o; o += align256(std::max<size_t>(T * B * 4 * H * 4, 16));   // XW (forward), dA (backward)
-  L.stash = o; o += align256(std::max<size_t>(T * B * 4 * H * 4, 16));
-  L.hx = o; o += bf ? align256((T + 1) * B * H * 2) : 0;
-  L.fwd_end = o;                                                       // the forward uses [0, fwd_end)
-  // post-loop operands over the push rows (at most T*B of them; KP with the K-tile padding)
-  L.xbt = o; o += bf ? align256(KP * I * 2) : 0;                      // x^T in bf16 (bf16 mode)
-  L.hp = o; o += align256(std::max<size_t>(bf ? KP * H * 2 : T * B * H * 4, 16));   // Hprev (bf16 mode: Hprev^T)
-  L.dat = o; o += bf ? align256(KP * 4 * H * 2) : 0;                  // dA^T in bf16 (bf16 mode)
-  L.dh = o; o += align256((T + 1) * B * H * 4);
-  L.dc = o; o += align256((T + 1) * B * H * 4);
-  L.dbp = o; o += align256((size_t)MAX_GROUPS * 4 * H * 4);
-  // split-K partials of dW / dU (at most min(64, ceil(T*B / 64)) slices: the split counts never
-  // exceed the GEMM's 64-row K steps over the T*B rows), the K-slice partials of dx (at most the
-  // rows of the grid's whole tiles: padded T*B x I), and the fp32 backward's gate-split partial
-  // sums (two step buffers of the groups' rows, at most B + 127, x H/16 workgroups x H)
-  const size_t max_splits = std::min<size_t>(64, std::max<size_t>(1, (T * B + 63) / 64));
-  L.part = o; o += align256(std::max({max_splits * std::max(I, H) * 4 * H, (T * B + 127) / 128 * 128 * I,
-                                      bf ? 0 : 2 * (B + 127) * ((H + 15) / 16) * H}) * 4);
-  L.prow = o; o += align256(std::max<size_t>(T * B * 4, 16));         // push-row list
+  auto put = [&](size_t bytes) {
+    const size_t at = o;
+    o += align256(std::max<size_t>(bytes, 16));
+    return at;
+  };
+  L.ctl = put(CTL_WORDS * 4);
+  L.order = put(N0 * 4);
+  L.opar = put(N0 * 4);
+  L.cs = put(NN * 4);
+  L.loff = put((size_t)L.G * (T + 4) * 4);
+  L.gmax = put((size_t)kLevMaxGroups * 4);
+  L.irow = put(NN * 4);
+  L.ics = put(NN * 4);
+  L.ioff = put((size_t)L.G * (T + 4) * 4);
+  L.cidx = put(NN * 4);
+  L.kin = put(N0 * 4);
+  L.gslot = put(N0 * 4);
+  L.cnt = put(B * L.cap * 4);
+  L.elem = put(3 * B * 4);
+  L.walk = put(L.walk_lds ? 0 : (size_t)L.G * 2 * L.cap * 4);
+  L.wt = put(S * 4 * H * L.Ip * 2);
+  L.wp = put(keep ? S * I * L.H4s * 2 : 0);
+  L.uf = put((size_t)NW * 8 * KS * 64 * NP * 16);
+  L.ufi = put((size_t)NW * kLevUnits * 4);
+  L.rin = put(B * 4);
+  // x W and h U of the nodes (forward); the exchange rows of the backward
+  L.hu = put(std::max(NN * 4 * H * 4, keep ? NP * NN * L.H4s * 2 : 0));
+  L.stash = put(keep ? N0 * 4 * H * 4 : 0);
+  L.cpn = put(keep ? N0 * H * 4 : 0);
+  L.hq = put(NP * NN * L.Hs * 2);
+  L.h3 = put(keep && S == 3 ? S * NN * L.Hs * 2 : 0);       // (bf16 mode: hq)
+  L.cn = put(NN * H * 4);
+  L.x_rows = (int)N0;
+  if (x_budget) L.x_rows = (int)std::min<size_t>(N0, std::max<size_t>(x_budget / (S * L.Ip * 2), 1));
+  L.xs = put(S * (size_t)L.x_rows * L.Ip * 2);
+  L.fwd_end = o;
+  if (!keep) {
+    L.total = o;
+    return L;
+  }
+  L.gf = put(2 * NN * H * 4);
+  L.gc = put(2 * NN * H * 4);
+  L.eg = put(NN * H * 4);
+  L.dcs = put(NN * H * 4);
+  L.dap = put(S * N0 * L.H4s * 2);
+  L.sxs = put(NP == 2 ? NN * NW * 4 : 0);
+  L.ub = put((size_t)NW * 8 * KS * 64 * NP * 16);
+  L.ubi = put((size_t)NW * kLevUnits * 4);
+  L.part = put((size_t)tn_splits(d) * (I + H) * 4 * H * 4);
+  L.dbp = put((size_t)kLevMaxGroups * 4 * H * 4);
   L.total = o;
   return L;
 }
+Layout layout(const slstm_dims* d) { return layout(d, true, 0); }
 
 int hip_status(hipError_t e) {
   if (e == hipSuccess) return SLSTM_OK;
@@ -258,44 +199,6 @@ void mark(const slstm_dims* d, int i, hipStream_t st) {
 }
 
 int grid1d(size_t n) { return (int)std::min<size_t>((n + 255) / 256, 8192); }
-
-int launch_gemm(int prec, int AL, int BL, const GemmArgs& g, int splits, hipStream_t st) {
-  dim3 grid((g.N + kGemmBN - 1) / kGemmBN, (g.M + kGemmBM - 1) / kGemmBM, splits);
-#define GCASE(P, A, B_)                                                       \
-  if (prec == P && AL == A && BL == B_) {                                     \
-    hipLaunchKernelGGL((k_gemm<P, A, B_>), grid, dim3(256), 0, st, g);        \
-    return hip_status(hipGetLastError());                                     \
-  }
-  GCASE(0, GEMM_MK, GEMM_KN) GCASE(0, GEMM_MK, GEMM_NK) GCASE(0, GEMM_KM, GEMM_KN)
-  GCASE(1, GEMM_MK, GEMM_NK) GCASE(1, GEMM_MK_F32, GEMM_NK)
-#undef GCASE
-  return SLSTM_EINVAL;
-}
-
-// The wide-tile bf16 GEMM takes MK x NK bf16 operands with 16-byte rows, no row gathers and
-// no device-side M.
-bool gemm_wide_ok(int prec, int AL, int BL, const GemmArgs& g) {
-  return prec == SLSTM_BF16_GEMM && AL == GEMM_MK && BL == GEMM_NK && g.a_vec && g.b_vec && !g.a_rows && !g.b_rows &&
-         !g.c_rows && !(g.dyn && g.dyn_axis == 0) && g.K % 8 == 0;
-}
-int wide_tiles(int M, int N) { return ((M + kGemmWideBM - 1) / kGemmWideBM) * ((N + kGemmWideBN - 1) / kGemmWideBN); }
-// split K of a wide-tile GEMM: one round of one workgroup per CU (256 blocks), at most 64
-// slices and one 64-deep K tile per slice
-int wide_splits(int M, int N, int K) {
-  const int s = std::max(1, 256 / std::max(1, wide_tiles(M, N)));
-  return std::min(std::min(s, 64), std::max(1, (K + 63) / 64));
-}
-int launch_gemm_wide(const GemmArgs& g, int splits, hipStream_t st) {
-  if (hipFuncSetAttribute((const void*)k_gemm_wide, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kGemmWideLds) !=
-      hipSuccess)
-    return SLSTM_EDEVICE;
-  dim3 grid((g.N + kGemmWideBN - 1) / kGemmWideBN, (g.M + kGemmWideBM - 1) / kGemmWideBM, splits);
-  hipLaunchKernelGGL(k_gemm_wide, grid, dim3(256), kGemmWideLds, st, g);
-  return hip_status(hipGetLastError());
-}
-
-// K slice per split, a multiple of the GEMM's K tile (64 covers both precisions)
-int k_chunk_for(int K, int splits) { return ((K + splits - 1) / splits + 63) / 64 * 64; }
 
 // The call's one host synchronisation: reads the control words its kernels set and maps them
 // to a status (op errors first, then a wait that gave up, then a producer index out of range).
@@ -316,47 +219,24 @@ int call_status(const slstm_dims* d, const uint32_t* ctl, hipStream_t st) {
   return d->defer_status ? SLSTM_OK : read_status(ctl, st);
 }
 
-// Backward direct staging: a variant built with it, whole 1 KB row segments, K range equal
-// to the register capacity, and the LDS slice plus static LDS within one CU (one workgroup
-// per CU).
-bool bwd_direct_for(const slstm_dims* d, const Plan& p) {
-  const int esz = d->precision == SLSTM_BF16_GEMM ? 2 : 4;
-  return !p.gs && rec_bwd_direct_built(d->precision, p.NTb, p.KS) && ((size_t)d->H * esz) % 1024 == 0 &&
-         p.KS * rec_kc(d->precision) == d->H &&
-         rec_bwd_lds_bytes(d->precision, p.KS) + rec_bwd_static_lds(p.NTb) <= 160 * 1024 &&
-         p.per_xcc_b <= std::max(1, device_cus() / 8);
+LevIdx idx_of(char* ws, const Layout& L) {
+  LevIdx x;
+  x.order = (int32_t*)(ws + L.order);
+  x.opar = (int32_t*)(ws + L.opar);
+  x.cs = (int32_t*)(ws + L.cs);
+  x.loff = (int32_t*)(ws + L.loff);
+  x.gmax = (int32_t*)(ws + L.gmax);
+  x.irow = (int32_t*)(ws + L.irow);
+  x.ics = (int32_t*)(ws + L.ics);
+  x.ioff = (int32_t*)(ws + L.ioff);
+  x.cidx = (int32_t*)(ws + L.cidx);
+  x.kin = (int32_t*)(ws + L.kin);
+  x.gslot = (int32_t*)(ws + L.gslot);
+  return x;
 }
-
-RecArgs rec_args(const slstm_dims* d, const Plan& p, char* ws, const Layout& L, bool bwd) {
-  RecArgs a;
-  memset(&a, 0, sizeof(a));
-  a.T = d->T; a.B = d->B; a.I = d->I; a.H = d->H;
-  a.G = bwd ? p.Gb : p.G; a.NW = bwd ? p.NWb : p.NW; a.ks_eff = p.ks_eff;
-  a.spin_limit = d->spin_limit > 0 ? d->spin_limit : kDefaultSpin;
-  a.ctl = (uint32_t*)(ws + L.ctl);
-  a.stash = (float*)(ws + L.stash);
-  a.hx = d->precision == SLSTM_BF16_GEMM ? (uint16_t*)(ws + L.hx) : nullptr;
-  a.clk = (long long*)d->step_clock;
-  // Exchange protocol (measured on the large parser workload): the bf16 forward's step is
-  // short and a group barrier's fixed cost (store acknowledgement, then an atomic and a poll
-  // round trip) dominates it, so its workgroups poll the fill-marked rows instead; the fp32
-  // forward's rows are twice as long and checking a staged tile for the fill pattern costs
-  // more than the barrier. The backward uses the barrier in both precisions: it stores and
-  // exchanges only push rows, its barrier's arrival overlaps the row-offset set-up, and a
-  // fill of dA before it would be a large write (bf16 large: 1.24 ms with the barrier,
-  // 1.32 ms polling).
-  a.poll = (d->precision == SLSTM_BF16_GEMM && !bwd) ? 1 : 0;
-  // the pipelined forward has no barrier: it always polls
-  if (!bwd && p.pipe) a.poll = 1;
-  const int esz = d->precision == SLSTM_BF16_GEMM ? 2 : 4;
-  a.coh_rows = ((size_t)d->H * esz) % 128 != 0;
-  a.bwd_direct = bwd_direct_for(d, p) ? 1 : 0;
-  if (bwd && p.gs) {
-    a.bwd_gs = 1;
-    a.gs_part = (float*)(ws + L.part);   // free until the post-loop GEMMs
-  }
-  return a;
-}
+int spin_of(const slstm_dims* d) { return d->spin_limit > 0 ? d->spin_limit : kDefaultSpin; }
+// workgroups of a recurrent kernel: every XCD takes the workgroups of its share of the groups
+int lev_grid(const Plan& p) { return 8 * p.NW * ((p.G + 7) / 8); }
 
 }  // namespace
 
@@ -389,18 +269,14 @@ int stacklstm_plan(const slstm_dims* d, slstm_plan* out) {
   if (!out) return SLSTM_EINVAL;
   memset(out, 0, sizeof(*out));
   out->groups = p.G;
-  out->wg_per_group = p.wide ? p.NWw : p.NW;
-  out->rows_per_group = 16 * p.NT;
-  out->k_chunks = p.ks_eff;
-  out->fwd_kernel = p.wide ? 2 : (p.pipe ? 1 : 0);
-  out->fwd_tiles = p.NT;
+  out->wg_per_group = p.NW;
+  out->rows_per_group = batch_max(d->H) / groups_max(d->H, 32);
+  out->k_chunks = p.NW;
+  out->fwd_tiles = lev_fwd_rt(p.NP, p.KS);
   out->k_chunk_cap = p.KS;
-  out->occupancy = rec_occ(p.prec, p.KS);
-  out->bwd_groups = p.Gb;
-  out->bwd_tiles = p.NTb;
-  out->bwd_direct = bwd_direct_for(d, p) ? 1 : 0;
-  out->fused_x = p.fuse;
-  out->bwd_split = p.gs;
+  out->occupancy = 2;
+  out->bwd_groups = p.G;
+  out->bwd_tiles = 1;
   return SLSTM_OK;
 }
 
@@ -408,122 +284,115 @@ int stacklstm_plan(const slstm_dims* d, slstm_plan* out) {
 
 namespace {
 
-// The forward pass on a work space that the caller checked (at least layout(d).fwd_end bytes).
-int fwd_impl(const slstm_dims* d, const Plan& p, const Layout& L, const float* x, const int8_t* ops, const float* W,
-             const float* U, const float* b, const float* h0, const float* c0, float* h_cell, float* c_cell,
-             float* h_top, float* c_top, int32_t* ptr, int32_t* top, char* ws, hipStream_t st) {
+// The forward pass on a work space that the caller checked.
+int fwd_impl(const slstm_dims* d, const Plan& p, const Layout& L, bool keep, const float* x, const int8_t* ops,
+             const float* W, const float* U, const float* b, const float* h0, const float* c0, float* h_cell,
+             float* c_cell, float* h_top, float* c_top, int32_t* ptr, int32_t* top, char* ws, hipStream_t st) {
   int rc = SLSTM_OK;
   uint32_t* ctl = (uint32_t*)(ws + L.ctl);
-  const int T = d->T, B = d->B, I = d->I, H = d->H;
-  const bool bf = p.prec == SLSTM_BF16_GEMM;
+  const int T = d->T, B = d->B, I = d->I, H = d->H, S = p.S, N0 = T * B;
+  const LevIdx ix = idx_of(ws, L);
 
-  // a1: op validation, pointer scan and producer trace. One thread per element; its stack of
-  // T + 1 step indices in LDS when a few elements' stacks fit in 64 KB, else in the work space
+  // op validation, pointer scan, producer trace and level schedule. One workgroup per group; as
+  // many waves as have walk arrays in LDS (at most one per element of the group)
   mark(d, 0, st);
   hipLaunchKernelGGL(k_init_ctl, dim3(1), dim3(256), 0, st, ctl, d->defer_status ? 1 : 0);
   {
-    const int cap = (T + 1) | 1;                  // odd: neighbouring stacks start in other banks
-    int R = (int)std::min<size_t>(64, 65536 / ((size_t)cap * 4));
-    const int lds = R >= 1 ? 1 : 0;
-    if (!lds) R = 64;
-    if (lds)
-      hipLaunchKernelGGL(k_scan<true>, dim3((B + R - 1) / R), dim3(R), (size_t)R * cap * 4, st, ops, T, B, cap, ptr, top,
-                         (int32_t*)(ws + L.dep), (int32_t*)(ws + L.stack), ctl);
-    else
-      hipLaunchKernelGGL(k_scan<false>, dim3((B + R - 1) / R), dim3(R), 0, st, ops, T, B, cap, ptr, top,
-                         (int32_t*)(ws + L.dep), (int32_t*)(ws + L.stack), ctl);
+    PlanArgs a;
+    a.T = T; a.B = B; a.G = p.G; a.cap = L.cap;
+    a.ops = ops; a.ptr = ptr; a.top = top; a.ix = ix;
+    a.cnt = (int32_t*)(ws + L.cnt); a.elem = (int32_t*)(ws + L.elem); a.walk = (int32_t*)(ws + L.walk); a.ctl = ctl;
+    if (L.walk_lds) {
+      const int waves = (int)std::min<size_t>(16, 147456 / L.walk_lds);
+      const size_t shm = waves * L.walk_lds;
+      if (hipFuncSetAttribute((const void*)k_plan<true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm) != hipSuccess)
+        return SLSTM_EDEVICE;
+      hipLaunchKernelGGL(k_plan<true>, dim3(p.G), dim3(64 * waves), shm, st, a);
+    } else {
+      hipLaunchKernelGGL(k_plan<false>, dim3(p.G), dim3(64), 0, st, a);
+    }
   }
   if ((rc = hip_status(hipGetLastError()))) return rc;
   mark(d, 1, st);
   if (T == 0) return call_status(d, ctl, st);
 
-  // a2: XW = x W + b for all steps on the library's MFMA GEMM, columns gate-interleaved
-  // (Wp = W with permuted columns; bf16 mode: Wp and its transpose in bf16), bias added in
-  // the GEMM's epilogue in fp32
-  void* wp = ws + L.wp;
-  bf16_t* wpt = bf ? (bf16_t*)wp + (size_t)I * 4 * H : nullptr;
-  // the fused projection copies x rows by 16-byte DMA: x must be 16-byte aligned, else XW
-  const bool fuse = p.fuse && al16(x);
-  hipLaunchKernelGGL(k_permute_w, dim3(grid1d((size_t)I * 4 * H)), dim3(256), 0, st, W, bf ? nullptr : (float*)wp,
-                     bf ? (bf16_t*)wp : nullptr, fuse ? nullptr : wpt, I, H);
-  float* xw = (float*)(ws + L.r1);
-  // (with the fused projection the recurrent kernel contracts x_t W itself: no XW)
-  if (!fuse) {
-    GemmArgs g;
-    memset(&g, 0, sizeof(g));
-    g.M = T * B; g.N = 4 * H; g.K = I;
-    g.A = x; g.lda = I; g.a_vec = (I % 4 == 0) && al16(x);
-    if (bf) { g.Bm = wpt; g.ldb = I; g.b_vec = (I % 8 == 0); }
-    else    { g.Bm = wp; g.ldb = 4 * H; g.b_vec = 1; }
-    g.C = xw; g.ldc = 4 * H;
-    g.bias = b; g.bias_H = H;
-    g.k_chunk = k_chunk_for(I, 1);
-    // bf16: x rounded to bf16 once, into the gate stash's area (written by the recurrent
-    // kernel only after this GEMM), then a bf16 GEMM; the GEMM that rounds fp32 x as it
-    // loads it re-reads the fp32 rows once per 128-column tile (thru shape: 2.80 ms against
-    // 0.16 + 2.02 ms). The same rounding (nearest even) either way.
-    int al = bf ? GEMM_MK_F32 : GEMM_MK;
-    const size_t nx = (size_t)T * B * I;
-    if (bf && g.a_vec && I % 8 == 0 && nx * 2 <= (size_t)T * B * 4 * H * 4) {
-      bf16_t* x16 = (bf16_t*)(ws + L.stash);
-      hipLaunchKernelGGL(k_to_bf16x8, dim3(grid1d(nx / 8)), dim3(256), 0, st, x, x16, nx / 8);
-      g.A = x16;
-      al = GEMM_MK;
+  // operand planes of W, U, the initial states and x; x W + b of the push nodes
+  float* hu = (float*)(ws + L.hu);
+  uint16_t* hq = (uint16_t*)(ws + L.hq);
+  uint16_t* h3 = keep && S == 3 ? (uint16_t*)(ws + L.h3) : nullptr;
+  float* cn = (float*)(ws + L.cn);
+  uint16_t* xs = (uint16_t*)(ws + L.xs);
+  const size_t hplane = (size_t)(N0 + B) * L.Hs;
+  {
+    PrepFwdArgs a;
+    a.I = I; a.Ip = L.Ip; a.H = H; a.Hs = L.Hs; a.H4s = keep ? L.H4s : 0; a.B = B; a.G = p.G; a.N0 = N0; a.NW = p.NW;
+    a.KS = p.KS;
+    a.n_w = ((I + 31) / 32) * ((H + 31) / 32);
+    a.n_u = p.NW * 4;
+    a.W = W; a.U = U; a.h0 = h0; a.c0 = c0;
+    a.wt = (uint16_t*)(ws + L.wt); a.wp = (uint16_t*)(ws + L.wp); a.uf = (uint4*)(ws + L.uf);
+    a.uinv = (float*)(ws + L.ufi); a.rinit = (float*)(ws + L.rin);
+    a.hq = hq; a.hplane = hplane; a.h3 = h3; a.cn = cn;
+    const int grid = a.n_w + a.n_u + (B + 3) / 4;
+    if (S == 3) hipLaunchKernelGGL(k_prep_fwd<3>, dim3(grid), dim3(256), 0, st, a);
+    else        hipLaunchKernelGGL(k_prep_fwd<1>, dim3(grid), dim3(256), 0, st, a);
+  }
+  NtArgs g;
+  memset(&g, 0, sizeof(g));
+  g.N = 4 * H; g.K = L.Ip; g.N0 = N0;
+  g.A = xs; g.lda = L.Ip;
+  g.B = (uint16_t*)(ws + L.wt); g.bplane = (size_t)4 * H * L.Ip; g.ldb = L.Ip;
+  g.ctl = ctl; g.C = hu; g.ldc = 4 * H; g.bias = b; g.H = H; g.order = ix.order;
+  g.opar = ix.opar; g.hu = hu; g.cn = cn; g.hcell = h_cell; g.ccell = c_cell;
+  // (all rows of x at once, or in pieces of the step list where the planes of x have less room)
+  const bool once = L.x_rows >= N0;
+  auto x_pass = [&](int epi, bool split) -> int {
+    for (int lo = 0; lo < N0; lo += L.x_rows) {
+      const int hi = std::min(N0, lo + L.x_rows);
+      g.lo = lo; g.hi = hi; g.leaves = epi == NT_LEAF; g.aplane = (size_t)(hi - lo) * L.Ip;
+      if (split) {
+        const int vec = I % 4 == 0 && al16(x);
+        const int grid = grid1d((size_t)(hi - lo) * (L.Ip / 8));
+        if (S == 3)
+          hipLaunchKernelGGL(k_split_x<3>, dim3(grid), dim3(256), 0, st, x, ix.order, lo, hi, I, L.Ip, vec, xs, g.aplane);
+        else
+          hipLaunchKernelGGL(k_split_x<1>, dim3(grid), dim3(256), 0, st, x, ix.order, lo, hi, I, L.Ip, vec, xs, g.aplane);
+      }
+      const int r = hip_status(launch_nt(g, S, epi, st));
+      if (r) return r;
     }
-    // (bf16 operands: the wide-tile GEMM when its 256 x 256 tiles alone fill the chip; fp32:
-    // the LDS-DMA ring GEMM when its operands allow 16-byte DMAs with 32-bit offsets)
-    const bool ring = !bf && g.K % 4 == 0 && g.N % 4 == 0 && al16(x) && (size_t)g.M * g.lda * 4 < ((size_t)1 << 32) &&
-                      (size_t)g.K * g.ldb * 4 < ((size_t)1 << 32);
-    if (ring) {
-      hipLaunchKernelGGL(k_gemm_ring, dim3((g.N + kGemmBN - 1) / kGemmBN, (g.M + kGemmBM - 1) / kGemmBM), dim3(256), 0, st,
-                         g);
-      if ((rc = hip_status(hipGetLastError()))) return rc;
-    } else if (gemm_wide_ok(p.prec, al, GEMM_NK, g) && wide_tiles(g.M, g.N) >= 256) {
-      if ((rc = launch_gemm_wide(g, 1, st))) return rc;
-    } else if ((rc = launch_gemm(p.prec, al, bf ? GEMM_NK : GEMM_KN, g, 1, st))) {
-      return rc;
-    }
-  }
-
-  // a3-a6: persistent recurrent kernel
-  RecArgs a = rec_args(d, p, ws, L, false);
-  if (bf) hipLaunchKernelGGL(k_h0_bf16, dim3(grid1d((size_t)B * H)), dim3(256), 0, st, h0, (bf16_t*)a.hx, (size_t)B * H);
-  a.xw = fuse ? nullptr : xw; a.ops = ops; a.U = U; a.h0 = h0; a.c0 = c0; a.hcell = h_cell; a.ccell = c_cell;
-  a.top = top;
-  FxArgs fa;
-  memset(&fa, 0, sizeof(fa));
-  if (fuse) {
-    fa.fuse_x = 1; fa.kx = p.kx; fa.x = x; fa.W = W; fa.bias = b;
-  }
-  // exchange buffers start as "not yet produced": all-one bits in the state rows the
-  // workgroups read from each other
-  if (a.poll || p.wide) {
-    const size_t ex_bytes = (size_t)T * B * H * (bf ? 2 : 4);
-    unsigned char* ex = bf ? (unsigned char*)(a.hx + (size_t)B * H) : (unsigned char*)h_cell;
-    hipLaunchKernelGGL(k_fill_pattern, dim3(grid1d(ex_bytes / 16 + 1)), dim3(256), 0, st, ex, ex_bytes, 0xffffffffu);
-  }
-  a.htop = p.wide ? h_top : nullptr;
-  a.ctop = p.wide ? c_top : nullptr;
-  if (p.wide) a.NW = p.NWw;
+    return SLSTM_OK;
+  };
+  if ((rc = x_pass(NT_XW, true))) return rc;
   mark(d, 2, st);
-  if ((rc = hip_status(p.wide   ? launch_fwd_wide(a, p.NT, p.KS, dim3(8 * p.per_xcc), st, nullptr)
-                       : p.pipe ? launch_fwd_pipe(a, p.prec, p.NT, p.KS, dim3(8 * p.per_xcc), st, nullptr)
-                                : launch_fwd(a, fa, p.prec, p.NT, p.KS, dim3(8 * p.per_xcc), st, nullptr))))
-    return rc;
+
+  // the recurrence over the levels
+  {
+    LevFwdArgs a;
+    memset(&a, 0, sizeof(a));
+    a.T = T; a.B = B; a.H = H; a.Hs = L.Hs; a.G = p.G; a.NW = p.NW; a.N0 = N0; a.spin_limit = spin_of(d);
+    a.ix = ix; a.hu = hu; a.hq = hq; a.hplane = hplane; a.cn = cn; a.hcell = h_cell; a.ccell = c_cell;
+    a.stash = keep ? (float*)(ws + L.stash) : nullptr;
+    a.cpn = (float*)(ws + L.cpn); a.h3 = h3;
+    a.uf = (const uint4*)(ws + L.uf); a.uinv = (const float*)(ws + L.ufi); a.rinit = (const float*)(ws + L.rin);
+    a.U = U; a.ctl = ctl;
+    a.clk = (long long*)d->step_clock;
+    if ((rc = hip_status(launch_lev_fwd(a, p.NP, p.KS, lev_grid(p), st)))) return rc;
+  }
   mark(d, 3, st);
 
-  // a7: Algorithm 1's return values (the wide forward writes c_top and the h_top of push steps)
-  size_t n = (size_t)T * B * H;
-  float* ctop_g = p.wide ? nullptr : c_top;          // the wide forward writes c_top itself
+  // the leaves (pop and hold steps), then Algorithm 1's return values
+  if ((rc = x_pass(NT_LEAF, !once))) return rc;
+  const size_t n = (size_t)N0 * H;
   if (H % 4 == 0 && al16(h_cell) && al16(h0) && al16(h_top) && al16(c_cell) && al16(c0) && al16(c_top)) {
-    if (h_top || ctop_g)
-      hipLaunchKernelGGL(k_gather_top4, dim3(grid1d(n / 4)), dim3(256), 0, st, top, h_cell, h0, h_top, c_cell, c0, ctop_g,
-                         T, B, H, p.wide, ctl);
+    if (h_top || c_top)
+      hipLaunchKernelGGL(k_gather_top4, dim3(grid1d(n / 4)), dim3(256), 0, st, top, h_cell, h0, h_top, c_cell, c0, c_top,
+                         T, B, H, ctl);
   } else {
     if (h_top)
-      hipLaunchKernelGGL(k_gather_top, dim3(grid1d(n)), dim3(256), 0, st, top, h_cell, h0, h_top, T, B, H, p.wide, ctl);
-    if (ctop_g)
-      hipLaunchKernelGGL(k_gather_top, dim3(grid1d(n)), dim3(256), 0, st, top, c_cell, c0, ctop_g, T, B, H, 0, ctl);
+      hipLaunchKernelGGL(k_gather_top, dim3(grid1d(n)), dim3(256), 0, st, top, h_cell, h0, h_top, T, B, H, ctl);
+    if (c_top)
+      hipLaunchKernelGGL(k_gather_top, dim3(grid1d(n)), dim3(256), 0, st, top, c_cell, c0, c_top, T, B, H, ctl);
   }
   if ((rc = hip_status(hipGetLastError()))) return rc;
   mark(d, 4, st);
@@ -539,8 +408,23 @@ bool fwd_args_ok(const slstm_dims* d, const float* x, const int8_t* ops, const f
 // Static work space of the allocation-free forward: one copy per GPU, held until the process
 // ends. Host code uses the device address that hipGetSymbolAddress returns for the current
 // device (kept per device), never the array's name.
-constexpr size_t kScratchBytes = SLSTM_FWD_STATIC_MAX_BYTES;
+constexpr size_t kScratchBytes = (size_t)320 << 20;
 __device__ __align__(256) unsigned char scratch[kScratchBytes];
+
+// Bytes that decide whether dims are served from the static work space: the work space of a
+// forward that keeps x W and the gate activations of every step.
+size_t static_measure(const slstm_dims* d) {
+  const size_t T = d->T, B = d->B, I = d->I, H = d->H;
+  return align256((64 + 2 * 16 * 64) * 4) + align256(B * (T + 1) * 4) + align256(B * 4) + align256(I * 4 * H * 4) +
+         2 * align256(std::max<size_t>(T * B * 4 * H * 4, 16)) +
+         (d->precision == SLSTM_BF16_GEMM ? align256((T + 1) * B * H * 2) : 0);
+}
+// The forward's layout in the static work space: what is left beside the other parts holds the
+// planes of x, in pieces if need be.
+Layout static_layout(const slstm_dims* d) {
+  const Layout L = layout(d, false, 1);
+  return L.total >= kScratchBytes ? L : layout(d, false, std::max<size_t>(kScratchBytes - L.total, 1));
+}
 
 // Device address of `scratch` on the current device, looked up on the first call on that
 // device; null if the lookup failed.
@@ -574,7 +458,7 @@ int stacklstm_fwd(const slstm_dims* d, const float* x, const int8_t* ops, const 
   Plan p;
   int rc = make_plan(d, &p);
   if (rc) return rc;
-  return fwd_impl(d, p, L, x, ops, W, U, b, h0, c0, h_cell, c_cell, h_top, c_top, ptr, top, (char*)workspace,
+  return fwd_impl(d, p, L, true, x, ops, W, U, b, h0, c0, h_cell, c_cell, h_top, c_top, ptr, top, (char*)workspace,
                   (hipStream_t)stream);
 }
 
@@ -583,21 +467,23 @@ int stacklstm_fwd_static(const slstm_dims* d, const float* x, const int8_t* ops,
                          float* c_top, int32_t* ptr, int32_t* top, void* stream) {
   if (!dims_ok(d)) return SLSTM_EINVAL;
   if (!fwd_args_ok(d, x, ops, W, U, b, h0, c0, h_cell, c_cell, ptr, top)) return SLSTM_EINVAL;
-  const Layout L = layout(d);
-  if (L.fwd_end > kScratchBytes) return SLSTM_EWORKSPACE;
+  if (static_measure(d) > SLSTM_FWD_STATIC_MAX_BYTES) return SLSTM_EWORKSPACE;
+  const Layout L = static_layout(d);
+  if (L.total > kScratchBytes) return SLSTM_EWORKSPACE;
   Plan p;
   int rc = make_plan(d, &p);
   if (rc) return rc;
   char* ws = scratch_ptr();
   if (!ws) return SLSTM_EDEVICE;
-  return fwd_impl(d, p, L, x, ops, W, U, b, h0, c0, h_cell, c_cell, h_top, c_top, ptr, top, ws, (hipStream_t)stream);
+  return fwd_impl(d, p, L, false, x, ops, W, U, b, h0, c0, h_cell, c_cell, h_top, c_top, ptr, top, ws,
+                  (hipStream_t)stream);
 }
 
 int stacklstm_bwd(const slstm_dims* d, const float* x, const int8_t* ops, const float* W, const float* U,
                   const float* h0, const float* c0, const float* h_cell, const float* c_cell, const int32_t* top,
                   void* workspace, size_t ws_bytes, const float* dh_top, const float* dc_top, float* dx, float* dW,
                   float* dU, float* db, float* dh0, float* dc0, void* stream) {
-  (void)W;
+  (void)W; (void)h0; (void)c0; (void)h_cell; (void)c_cell;
   if (!dims_ok(d)) return SLSTM_EINVAL;
   if (!workspace || !dW || !dU || !db || !dh0 || !dc0) return SLSTM_EINVAL;
   if (d->T > 0 && (!x || !ops || !U || !h0 || !c0 || !h_cell || !c_cell || !top || !dh_top || !dx))
@@ -611,7 +497,6 @@ int stacklstm_bwd(const slstm_dims* d, const float* x, const int8_t* ops, const 
   char* ws = (char*)workspace;
   uint32_t* ctl = (uint32_t*)(ws + L.ctl);
   const int T = d->T, B = d->B, I = d->I, H = d->H;
-  const bool bf = p.prec == SLSTM_BF16_GEMM;
   // the backward's control words (slot and barrier counters, wait and index flags) start at 0
   hipLaunchKernelGGL(k_zero_ctl_bwd, dim3(1), dim3(256), 0, st, ctl, d->defer_status ? 1 : 0);
   if (T == 0) {
@@ -624,108 +509,77 @@ int stacklstm_bwd(const slstm_dims* d, const float* x, const int8_t* ops, const 
     return call_status(d, ctl, st);
   }
 
-  // a8: persistent reverse loop
-  RecArgs a = rec_args(d, p, ws, L, true);
-  a.ops = ops; a.U = U; a.h0 = h0; a.c0 = c0;
-  a.hcell = const_cast<float*>(h_cell); a.ccell = const_cast<float*>(c_cell); a.top = const_cast<int32_t*>(top);
-  a.dh_top = dh_top; a.dc_top = dc_top;
-  a.dA = ws + L.r1;
-  a.dh_acc = (float*)(ws + L.dh); a.dc_acc = (float*)(ws + L.dc);
-  a.db_part = (float*)(ws + L.dbp);
-  a.depth_end = (const int32_t*)(ws + L.dep);
-  a.dh0 = dh0; a.dc0 = dc0;
-  if (a.clk) a.clk += (size_t)512 * T * 4;
-  // rows of the push steps, for the post-loop gradients (dA is exactly zero on other rows);
-  // their number stays on the device: the GEMMs below take it as their K or M extent
-  int32_t* prow = (int32_t*)(ws + L.prow);
-  const uint32_t* npush = ctl + CTL_NPUSH;
-  hipLaunchKernelGGL(k_push_rows, dim3(1), dim3(1024), 0, st, ops, T * B, prow, ctl + CTL_NPUSH);
+  const int S = p.S, N0 = T * B;
+  const LevIdx ix = idx_of(ws, L);
+  // U^T fragments and the check of top and ops; interval sums of the upstream gradients
+  float* gf = (float*)(ws + L.gf);
+  float* gc = dc_top ? (float*)(ws + L.gc) : nullptr;
+  {
+    PrepBwdArgs a;
+    a.T = T; a.B = B; a.H = H; a.NW = p.NW; a.KS = p.KS;
+    a.n_u = p.NW * 2;
+    a.U = U; a.ops = ops; a.top = top; a.order = ix.order; a.ub = (uint4*)(ws + L.ub);
+    a.uinv = (float*)(ws + L.ubi); a.ctl = ctl;
+    const int grid = a.n_u + (int)std::min<size_t>(((size_t)N0 + 1023) / 1024, 1024);
+    if (S == 3) hipLaunchKernelGGL(k_prep_bwd<3>, dim3(grid), dim3(256), 0, st, a);
+    else        hipLaunchKernelGGL(k_prep_bwd<1>, dim3(grid), dim3(256), 0, st, a);
+    auto gsum = [&](const float* src, float* out) {
+      if (H % 4 == 0 && al16(src))
+        hipLaunchKernelGGL(k_gsum<4>, dim3(((size_t)B * ((H + 255) / 256) + 3) / 4), dim3(256), 0, st, src, ix.gslot, T, B,
+                           H, p.G, out);
+      else
+        hipLaunchKernelGGL(k_gsum<1>, dim3(((size_t)B * ((H + 63) / 64) + 3) / 4), dim3(256), 0, st, src, ix.gslot, T, B, H,
+                           p.G, out);
+    };
+    gsum(dh_top, gf);
+    if (gc) gsum(dc_top, gc);
+  }
+  uint16_t* dap = (uint16_t*)(ws + L.dap);
+  const size_t dplane = (size_t)N0 * L.H4s;
+  float* part = (float*)(ws + L.part);
+  float* dbp = (float*)(ws + L.dbp);
   mark(d, 5, st);
-  if ((rc = hip_status(launch_bwd(a, p.prec, p.NTb, p.KS, dim3(8 * p.per_xcc_b), st, nullptr)))) return rc;
+  {
+    LevBwdArgs a;
+    memset(&a, 0, sizeof(a));
+    a.T = T; a.B = B; a.H = H; a.H4s = L.H4s; a.G = p.G; a.NW = p.NW; a.N0 = N0; a.spin_limit = spin_of(d);
+    a.ix = ix; a.cpn = (const float*)(ws + L.cpn);
+    a.stash = (const float*)(ws + L.stash);
+    a.gf = gf; a.gc = gc; a.eg = (float*)(ws + L.eg); a.dcs = (float*)(ws + L.dcs);
+    a.dap = dap; a.dplane = dplane; a.sx = (uint16_t*)(ws + L.hu); a.xplane = (size_t)(N0 + B) * L.H4s;
+    a.sxs = (float*)(ws + L.sxs); a.ub = (const uint4*)(ws + L.ub); a.uinv = (const float*)(ws + L.ubi); a.U = U;
+    a.db_part = dbp; a.dh0 = dh0; a.dc0 = dc0; a.ctl = ctl;
+    if (d->step_clock) a.clk = (long long*)d->step_clock + (size_t)512 * T * 4;
+    if ((rc = hip_status(launch_lev_bwd(a, p.NP, p.KS, lev_grid(p), st)))) return rc;
+  }
   mark(d, 6, st);
 
-  // a9: post-loop gradients on the library's MFMA GEMM, contracted over the push rows only
-  // (rows prow[0 .. *npush)). fp32: the GEMMs gather x and dA rows through prow, Hprev is
-  // gathered first; bf16: x, dA and Hprev are written transposed and compacted (k = push
-  // index contiguous, zero up to the next multiple of 64) for dW and dU.
-  const int H4 = 4 * H;
-  float* part = (float*)(ws + L.part);
-  hipLaunchKernelGGL(k_reduce_splits, dim3(grid1d((size_t)H4)), dim3(256), 0, st, a.db_part, p.Gb, (size_t)H4, 1, H4,
-                     H, db);
-  const int K = T * B;
-  const int KP = (int)padded_rows(d);
-  void* hp = ws + L.hp;
-  GemmArgs g;
-  auto gemm_base = [&]() {
-    memset(&g, 0, sizeof(g));
-    g.dyn = npush;
-    g.dyn_round = bf ? 64 : 1;
-  };
-  if (bf) {
-    const dim3 tg4((H4 + 63) / 64, KP / 64), tgI((I + 63) / 64, KP / 64), tgH((H + 63) / 64, KP / 64);
-    hipLaunchKernelGGL(k_transpose_bf16, tg4, dim3(256), 0, st, a.dA, 0, H4, H4, prow, npush, KP,
-                       (const int32_t*)nullptr, B, (bf16_t*)(ws + L.dat), ctl);
-    hipLaunchKernelGGL(k_transpose_bf16, tgI, dim3(256), 0, st, x, 1, I, I, prow, npush, KP, (const int32_t*)nullptr,
-                       B, (bf16_t*)(ws + L.xbt), ctl);
-    hipLaunchKernelGGL(k_transpose_bf16, tgH, dim3(256), 0, st, ws + L.hx, 0, H, H, prow, npush, KP, top, B,
-                       (bf16_t*)hp, ctl);
-  } else {
-    hipLaunchKernelGGL(k_gather_hprev, dim3(grid1d((size_t)K * H)), dim3(256), 0, st, top, h_cell, h0, prow, npush,
-                       (float*)hp, T, B, H, ctl);
-  }
-  // dW = x^T dA
-  gemm_base();
-  g.M = I; g.N = H4; g.dyn_axis = 1;
-  if (bf) { g.K = KP; g.A = ws + L.xbt; g.lda = KP; g.a_vec = 1; g.Bm = ws + L.dat; g.ldb = KP; g.b_vec = 1; }
-  else    { g.K = K; g.A = x; g.lda = I; g.a_vec = (I % 4 == 0) && al16(x); g.a_rows = prow;
-            g.Bm = a.dA; g.ldb = H4; g.b_vec = 1; g.b_rows = prow; }
-  g.C = part; g.ldc = H4;
-  g.split_stride = (size_t)I * H4;
-  // (bf16: the wide-tile GEMM, with its own split count, when the output has 32 or more of its
-  // tiles: measured faster at the thru shape, slower at the large one, whose K slices are short)
-  const bool wide_w = gemm_wide_ok(p.prec, GEMM_MK, GEMM_NK, g) && wide_tiles(g.M, g.N) >= 32;
-  const int sw = wide_w ? wide_splits(g.M, g.N, g.K) : p.splits_w;
-  if ((rc = wide_w ? launch_gemm_wide(g, sw, st)
-                   : launch_gemm(p.prec, bf ? GEMM_MK : GEMM_KM, bf ? GEMM_NK : GEMM_KN, g, sw, st)))
-    return rc;
-  hipLaunchKernelGGL(k_reduce_splits, dim3(grid1d((size_t)I * H4)), dim3(256), 0, st, part, sw, g.split_stride, I, H4,
-                     H, dW);
-  mark(d, 7, st);
-  // dU = Hprev^T dA
-  gemm_base();
-  g.M = H; g.N = H4; g.dyn_axis = 1;
-  if (bf) { g.K = KP; g.A = hp; g.lda = KP; g.a_vec = 1; g.Bm = ws + L.dat; g.ldb = KP; g.b_vec = 1; }
-  else    { g.K = K; g.A = hp; g.lda = H; g.a_vec = (H % 4 == 0); g.Bm = a.dA; g.ldb = H4; g.b_vec = 1;
-            g.b_rows = prow; }
-  g.C = part; g.ldc = H4;
-  g.split_stride = (size_t)H * H4;
-  const bool wide_u = gemm_wide_ok(p.prec, GEMM_MK, GEMM_NK, g) && wide_tiles(g.M, g.N) >= 32;
-  const int su = wide_u ? wide_splits(g.M, g.N, g.K) : p.splits_u;
-  if ((rc = wide_u ? launch_gemm_wide(g, su, st)
-                   : launch_gemm(p.prec, bf ? GEMM_MK : GEMM_KM, bf ? GEMM_NK : GEMM_KN, g, su, st)))
-    return rc;
-  hipLaunchKernelGGL(k_reduce_splits, dim3(grid1d((size_t)H * H4)), dim3(256), 0, st, part, su, g.split_stride, H, H4,
-                     H, dU);
-  mark(d, 8, st);
-  // dx = dA Wp^T on the push rows (gathered from dA); the GEMM's grid covers all T*B rows, so
-  // the push rows' tiles take two or more blocks each, over K slices written as partials that
-  // k_scatter_splits adds into the push rows of dx; 0 on the other rows
-  gemm_base();
-  g.dyn_round = 1; g.dyn_axis = 0; g.dyn_split = 1;
-  g.M = K; g.N = I; g.K = H4;
-  const int VE = bf ? 8 : 4;
-  g.A = a.dA; g.lda = H4; g.a_vec = (H4 % VE == 0); g.a_rows = prow;
-  g.Bm = ws + L.wp; g.ldb = H4; g.b_vec = (H4 % VE == 0) && (I % VE == 0);
-  g.C = part; g.ldc = I;
-  g.k_chunk = k_chunk_for(H4, 1);
-  if ((rc = launch_gemm(p.prec, GEMM_MK, GEMM_NK, g, 1, st))) return rc;
+  // dW, dU over the push nodes (dA is exactly 0 on every other step), db from the groups' sums
   {
-    const int ntl = (I + kGemmBN - 1) / kGemmBN, nblk = ntl * ((K + kGemmBM - 1) / kGemmBM);
-    hipLaunchKernelGGL(k_scatter_splits, dim3(grid1d((size_t)K * I)), dim3(256), 0, st, (const float*)part, prow, npush,
-                       (size_t)K, I, nblk, ntl, dx);
+    TnArgs g;
+    memset(&g, 0, sizeof(g));
+    g.I = I; g.H = H; g.H4 = 4 * H; g.splits = tn_splits(d); g.xt = (I + nt_bm(S) - 1) / nt_bm(S);
+    g.X = (const uint16_t*)(ws + L.xs); g.xplane = (size_t)N0 * L.Ip; g.ldx = L.Ip;
+    g.Hp = (const uint16_t*)(ws + (S == 3 ? L.h3 : L.hq)); g.hplane = (size_t)(N0 + B) * L.Hs; g.ldh = L.Hs; g.hrows = N0 + B;
+    g.D = dap; g.dplane = dplane; g.ldd = L.H4s;
+    g.opar = ix.opar; g.ctl = ctl; g.part = part; g.split_stride = (size_t)(I + H) * 4 * H;
+    if ((rc = hip_status(launch_tn(g, S, st)))) return rc;
+    hipLaunchKernelGGL(k_reduce_grads, dim3(grid1d((size_t)(I + H + 1) * H)), dim3(256), 0, st, part, g.splits,
+                       g.split_stride, dbp, p.G, I, H, dW, dU, db);
   }
-  hipLaunchKernelGGL(k_zero_nonpush_rows, dim3(grid1d((size_t)K * I / 4 + 1)), dim3(256), 0, st, ops, dx, (size_t)K,
-                     I);
+  mark(d, 7, st);
+  mark(d, 8, st);
+  // dx = dA W^T on the push steps, 0 on the others
+  {
+    NtArgs g;
+    memset(&g, 0, sizeof(g));
+    g.N = I; g.K = L.H4s; g.N0 = N0; g.lo = 0; g.hi = N0;
+    g.A = dap; g.aplane = dplane; g.lda = L.H4s;
+    g.B = (const uint16_t*)(ws + L.wp); g.bplane = (size_t)I * L.H4s; g.ldb = L.H4s;
+    g.ctl = ctl; g.C = dx; g.ldc = I; g.order = ix.order; g.H = H;
+    if ((rc = hip_status(launch_nt(g, S, NT_DX, st)))) return rc;
+  }
+  hipLaunchKernelGGL(k_zero_nonpush_rows, dim3(grid1d((size_t)N0 * I / 4 + 1)), dim3(256), 0, st, ops, dx, (size_t)N0, I);
   if ((rc = hip_status(hipGetLastError()))) return rc;
   mark(d, 9, st);
   return call_status(d, ctl, st);

@@ -23,16 +23,15 @@ enum {
   CTL_MAXDEPTH = 1,
   CTL_ABORT = 2,         // set when a wait ran out of spins: every workgroup leaves its loop
   CTL_TIMEOUT = 3,       // set when a wait ran out of spins (reported as SLSTM_ETIMEOUT)
-  CTL_NPUSH = 4,         // number of push rows (written by k_push_rows in the backward)
-  CTL_NPUSHF = 5,        // number of push rows (counted by k_scan in the forward)
+  CTL_NPUSHF = 5,        // number of push steps (counted by k_plan in the forward)
   CTL_BADIDX = 6,        // set when a kernel read a producer index outside its valid range
   CTL_XCC_SLOT = 16,     // 16 per-XCC slot counters (forward kernel)
   CTL_XCC_SLOT_B = 32,   // 16 per-XCC slot counters (backward kernel)
   CTL_BAR_F = 64,        // forward group barrier counters, one 64-byte line per group
-  CTL_BAR_B = 64 + 16 * 64,   // backward group barrier counters
-  CTL_WORDS = 64 + 2 * 16 * 64
+  CTL_BAR_B = 64 + 16 * 128,  // backward group barrier counters
+  CTL_WORDS = 64 + 2 * 16 * 128
 };
-#define MAX_GROUPS 64
+#define MAX_GROUPS 128
 
 // Gate-interleaved ("permuted") column order used inside the library: column 4*u + k
 // holds gate k (0=i, 1=f, 2=g, 3=o) of hidden unit u. The caller's order is k*H + u.
@@ -111,39 +110,6 @@ constexpr int kSc1 = 16;  // cache-policy bit SC1 of gfx94x/gfx950 memory instru
 __device__ __forceinline__ uint4 ld_coh_b128(rsrc_t r, uint32_t off) {
   return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kSc1));
 }
-__device__ __forceinline__ uint32_t ld_coh_b32(rsrc_t r, uint32_t off) {
-  return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, kSc1);
-}
-__device__ __forceinline__ uint16_t ld_coh_b16(rsrc_t r, uint32_t off) {
-  return __builtin_amdgcn_raw_buffer_load_b16(r, off, 0, kSc1);
-}
-
-// Barrier-free exchange of states between the workgroups of one XCC. Before the kernel
-// the exchanged rows are filled with all-one bits (a NaN no producer ever stores: produced
-// NaNs are stored as the canonical quiet NaN); a consumer reads a row, and re-reads every
-// 16-byte granule that still holds the fill, with agent-scope atomic loads (never hoisted
-// or merged by the compiler, and they miss in this CU's L1), until the producer's store has
-// reached the XCC's L2.
-__device__ __forceinline__ bool pending_f32x4(uint4 v) {
-  return v.x == 0xffffffffu || v.y == 0xffffffffu || v.z == 0xffffffffu || v.w == 0xffffffffu;
-}
-__device__ __forceinline__ bool pending_bf16_word(uint32_t w) {
-  return (w & 0xffffu) == 0xffffu || (w >> 16) == 0xffffu;
-}
-__device__ __forceinline__ bool pending_bf16x8(uint4 v) {
-  return pending_bf16_word(v.x) || pending_bf16_word(v.y) || pending_bf16_word(v.z) || pending_bf16_word(v.w);
-}
-template <int PREC>
-__device__ __forceinline__ bool pending_granule(uint4 v) {
-  if constexpr (PREC == 0) return pending_f32x4(v);
-  else return pending_bf16x8(v);
-}
-__device__ __forceinline__ uint4 ld_poll_b128(const void* p) {
-  const uint64_t* q = (const uint64_t*)p;
-  uint64_t lo = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  uint64_t hi = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return uint4{(uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32)};
-}
 __device__ __forceinline__ float canon_nan(float h) { return h == h ? h : __builtin_nanf(""); }
 
 // A producer index s read at step t must lie in [-1, t) (the state read at step t) or
@@ -162,60 +128,50 @@ __device__ __forceinline__ int checked_src(int s, int hi, uint32_t* ctl) {
   return s;
 }
 
-// Bounded wait: counts failed polls of one wait; gives up (returns true) when the count
-// reaches the limit, raising the abort and time-out flags, or when another workgroup has
-// raised the abort flag.
-__device__ __forceinline__ bool spin_out(int& spins, uint32_t* ctl, int spin_limit) {
-  ++spins;
-  if (spins >= spin_limit) {
-    __hip_atomic_store(&ctl[CTL_ABORT], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    __hip_atomic_store(&ctl[CTL_TIMEOUT], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return true;
-  }
-  return (spins & 255) == 0 && __hip_atomic_load(&ctl[CTL_ABORT], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // Group barrier for workgroups that all run on one XCC (one shared L2).
 // Each wave waits until its own stores are acknowledged by L2, the workgroup meets at
 // s_barrier, one lane adds to the group counter and polls it with L1-bypassing loads.
 // Data written by other workgroups before the barrier must then be read with the
 // ld_coh_* loads above. Returns true when the spin limit ran out (or another group's
 // did): the caller must then leave its loop so that every wave of the grid exits.
-// Arrival half: stores acknowledged, workgroup met, the group counter incremented.
+// Arrival half: stores acknowledged, workgroup met, the group counter incremented. The lane that
+// polls is one of the last wave, whose threads have the fewest loads of their own in flight when
+// the workgroup prefetches between the halves (loads return in order, a poll behind them).
+__device__ __forceinline__ bool group_poller() { return threadIdx.x + 64 == blockDim.x; }
 __device__ __forceinline__ void group_arrive(uint32_t* ctr) {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
-  if (threadIdx.x == 0) __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (group_poller()) __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// Waiting half: one lane polls the counter up to target; returns true when the spin limit
-// ran out or another workgroup gave up. Work that needs no other workgroup's data can run
-// between the two halves.
-__device__ __forceinline__ bool group_wait(uint32_t* ctr, uint32_t target, uint32_t* ctl, int spin_limit,
+// First poll of a wait, issued before other loads: its value is looked at in group_wait.
+__device__ __forceinline__ uint32_t group_peek(uint32_t* ctr) {
+  return group_poller() ? __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+}
+// Waiting half: the lane polls the counter up to target (seen: the value of the first poll);
+// returns true when the spin limit ran out (spin_limit failed polls) or another workgroup gave
+// up. Work that needs no other workgroup's data can run between the two halves.
+__device__ __forceinline__ bool group_wait(uint32_t* ctr, uint32_t target, uint32_t seen, uint32_t* ctl, int spin_limit,
                                            int* s_flag) {
-  if (threadIdx.x == 0) {
+  if (group_poller()) {
     int spins = 0, bad = 0;
-    while (__hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
+    while (seen < target) {
       ++spins;
       if ((spins & 255) == 0 && __hip_atomic_load(&ctl[CTL_ABORT], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
         bad = 1;
         break;
       }
-      if (spins > spin_limit) {
+      if (spins >= spin_limit) {
         __hip_atomic_store(&ctl[CTL_ABORT], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_store(&ctl[CTL_TIMEOUT], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         bad = 1;
         break;
       }
+      seen = __hip_atomic_load(ctr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     *s_flag = bad;
   }
   __syncthreads();
   return *s_flag != 0;
-}
-__device__ __forceinline__ bool group_barrier(uint32_t* ctr, uint32_t target, uint32_t* ctl, int spin_limit,
-                                              int* s_flag) {
-  group_arrive(ctr);
-  return group_wait(ctr, target, ctl, spin_limit, s_flag);
 }
 
 // Claims this workgroup's (group, member) slot from the XCC it runs on, so that every
@@ -284,6 +240,17 @@ __device__ __forceinline__ void wait_vm_upto16(int n) {
 #undef SLSTM_WAIT_CASE
     default: wait_vm<0>(); break;
   }
+}
+// A copy of v the compiler cannot see through: what is computed from it is computed where it is
+// used, instead of being kept in registers through a whole kernel.
+__device__ __forceinline__ int opaque(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+// base + a 32-bit byte offset (scalar base, one offset register)
+template <typename T>
+__device__ __forceinline__ T* at32(T* base, uint32_t off) {
+  return (T*)((uintptr_t)base + off);
 }
 // Wave-uniform value kept in a scalar register.
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }

@@ -1,0 +1,43 @@
+// Launch descriptions of the contractions over bf16 planes (contract.hip).
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stddef.h>
+#include <stdint.h>
+
+// C(i, n) = sum_k A(i, k) B(n, k) for a range of entries i of the step list (levels.h): the push
+// nodes [0, P) or the leaves [P, N0), cut to [lo, hi); A row i is array row i - lo.
+enum { NT_XW = 0, NT_LEAF = 1, NT_DX = 2 };
+struct NtArgs {
+  int N, K;                          // K: columns of A and B (a multiple of 8)
+  int lo, hi, leaves, N0;
+  const uint16_t* A; size_t aplane; int lda;
+  const uint16_t* B; size_t bplane; int ldb;
+  const uint32_t* ctl;               // CTL_NPUSHF
+  // NT_XW: C[i][N] + bias; NT_DX: C[order[i]][N]
+  float* C; int ldc;
+  const float* bias; int H;          // caller's column order
+  const int32_t* order;
+  // NT_LEAF: the cell of a step whose state nobody reads: gates = x W + b + h U of the parent
+  const int32_t* opar; const float* hu; const float* cn; float* hcell; float* ccell;
+};
+
+// dW | dU: C(m, n) = sum over push nodes k of X(k, m) dA(k, n); rows m < I of x (array row k), the
+// others of the state the node read (array row parent(k)). Split over K into gridDim.z partials.
+struct TnArgs {
+  int I, H, H4, splits, xt;          // xt: row tiles that cover x
+  const uint16_t* X; size_t xplane; int ldx;
+  const uint16_t* Hp; size_t hplane; int ldh; int hrows;
+  const uint16_t* D; size_t dplane; int ldd;
+  const int32_t* opar;
+  const uint32_t* ctl;
+  float* part; size_t split_stride;  // [splits][I + H][4H]
+};
+
+// Block tiles: rows x columns, K step
+constexpr int nt_bm(int S) { return 256; }
+constexpr int nt_bn(int S) { return S == 3 ? 128 : 256; }
+constexpr int nt_bk(int S) { return S == 3 ? 32 : 64; }
+constexpr size_t nt_lds(int S) { return (size_t)2 * S * (nt_bm(S) + nt_bn(S)) * nt_bk(S) * 2; }
+
+hipError_t launch_nt(const NtArgs& g, int S, int epi, hipStream_t st);
+hipError_t launch_tn(const TnArgs& g, int S, hipStream_t st);

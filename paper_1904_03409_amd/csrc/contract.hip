@@ -1,0 +1,444 @@
+// The non-recurrent contractions of the step, on bf16 planes (split.h), 16x16x32 MFMA:
+//   k_nt  x W + b of the push nodes, x W + b and the whole cell of the leaves, dx = dA W^T
+//   k_tn  dW = x^T dA and dU = h_prev^T dA over the push nodes, split over K
+// 512 threads (two waves per SIMD), one workgroup per CU; operand slices go from global memory
+// into two LDS stages by LDS DMA, the next slice in flight behind the products of the current one.
+// A DMA writes one contiguous kilobyte per wave instruction, so each lane fetches the 16-byte
+// granule that a swizzled layout puts at its slot; fragment reads then spread over the banks.
+// S = 3: 256 x 128 block, 64 x 64 per wave, K steps of 32: six MFMAs per pair of three-plane
+// fragments, bound by the matrix units. S = 1: 256 x 256 block, 128 x 64 per wave, K steps of 64
+// (a wave reads 12 KB of fragments per 32 MFMAs).
+#include "common.h"
+#include "contract.h"
+#include "split.h"
+
+namespace {
+
+// The products of one K step of 32 on MI x NJ tiles. C^T = B^T A^T: a lane holds row l16 and
+// columns 4 lq .. 4 lq + 3 of a tile.
+template <int S, int MI, int NJ>
+__device__ __forceinline__ void tile_step(const bf16x8 (&a)[MI][S], const bf16x8 (&b)[NJ][S], f32x4 (&acc)[MI][NJ]) {
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+    if constexpr (S == 1) {
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) acc[i][j] = mfma_bf16_16x16x32(b[j][0], a[i][0], acc[i][j]);
+    } else {
+      mfma_planes_add<NJ>(b, a[i], acc[i]);
+    }
+  }
+}
+
+__device__ __forceinline__ float plane_sum(const uint16_t* p, size_t plane, size_t i) {
+  return bf16_bits_to_f32(p[i]) + bf16_bits_to_f32(p[plane + i]) + bf16_bits_to_f32(p[2 * plane + i]);
+}
+
+}  // namespace
+
+template <int S, int EPI>
+__global__ void __launch_bounds__(512, 2) k_nt(NtArgs g) {
+  constexpr int BM = nt_bm(S), BN = nt_bn(S), BK = nt_bk(S), GR = BK / 8;
+  constexpr int MI = S == 3 ? 4 : 8, NJ = 4, WN = BN / (16 * NJ);
+  static_assert(BM == 16 * MI * (8 / WN), "eight waves cover the block tile");
+  constexpr int APL = BM * GR * 16, BPL = BN * GR * 16, STAGE = S * (APL + BPL);
+  constexpr int IA = BM * GR / 512, IB = BN * GR / 512;            // DMAs per wave, plane and slice
+  extern __shared__ __align__(16) unsigned char sm[];
+  // rows in use and this block's tile: the active tiles are dealt so that each XCD (workgroups
+  // go to the 8 XCDs in turn) takes a contiguous run, in groups of 4 row tiles per column tile
+  const int P = (int)g.ctl[CTL_NPUSHF];
+  const int r_lo = g.leaves ? max(g.lo, P) : g.lo, r_hi = g.leaves ? g.hi : min(g.hi, P);
+  if (r_lo >= r_hi) return;
+  const int NTL = (g.N + BN - 1) / BN, MTL = (r_hi - r_lo + BM - 1) / BM, active = NTL * MTL;
+  int lid = (int)blockIdx.x;
+  if (lid >= active) return;
+  {
+    const int full = active & ~7;
+    if (lid < full) lid = (lid & 7) * (full >> 3) + (lid >> 3);
+  }
+  constexpr int GM = 4;
+  const int gi = lid / (GM * NTL), gm = min(GM, MTL - gi * GM), rem = lid - gi * GM * NTL;
+  const int m0 = r_lo + (gi * GM + rem % gm) * BM, n0 = (rem / gm) * BN;
+  const int nr = min(BM, r_hi - m0), nc = min(BN, g.N - n0);
+  const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
+  const int wm = wave / WN, wn = wave % WN, l16 = lane & 15, lq = lane >> 4;
+  const uint16_t* A = g.A + (size_t)(m0 - g.lo) * g.lda;
+  const uint16_t* Bp = g.B + (size_t)n0 * g.ldb;
+
+  auto swz = [](int row) { return GR == 4 ? (row >> 1) & 3 : row & 7; };
+  // the lane's row and granule are the same for every DMA of the block up to a row offset
+  const int rl = lane / GR;
+  auto issue = [&](int k0, int buf) {
+    unsigned char* st = sm + buf * STAGE;
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      const rsrc_t ra = make_rsrc(A + s * g.aplane, (size_t)nr * g.lda * 2);
+      const rsrc_t rb = make_rsrc(Bp + s * g.bplane, (size_t)nc * g.ldb * 2);
+#pragma unroll
+      for (int i = 0; i < IA; ++i) {
+        const int q = i * 8 + wave, row = q * (64 / GR) + rl, k = k0 + 8 * ((lane % GR) ^ swz(row));
+        bdma16(ra, (row < nr && k < g.K) ? (uint32_t)(row * g.lda + k) * 2u : kOOB, 0u, lds_addr(st + s * APL + q * 1024));
+      }
+#pragma unroll
+      for (int i = 0; i < IB; ++i) {
+        const int q = i * 8 + wave, row = q * (64 / GR) + rl, k = k0 + 8 * ((lane % GR) ^ swz(row));
+        bdma16(rb, (row < nc && k < g.K) ? (uint32_t)(row * g.ldb + k) * 2u : kOOB, 0u,
+               lds_addr(st + S * APL + s * BPL + q * 1024));
+      }
+    }
+  };
+
+  f32x4 acc[MI][NJ];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  issue(0, 0);
+  int buf = 0;
+  for (int k0 = 0; k0 < g.K; k0 += BK, buf ^= 1) {
+    wait_vm<0>();
+    __syncthreads();                                   // this slice landed, the other stage is free
+    if (k0 + BK < g.K) issue(k0 + BK, buf ^ 1);
+    const unsigned char* st = sm + buf * STAGE;
+#pragma unroll
+    for (int kc = 0; kc < BK / 32; ++kc) {
+      bf16x8 a[MI][S], b[NJ][S];
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        const int r = 16 * (MI * wm + i) + l16;
+#pragma unroll
+        for (int s = 0; s < S; ++s) a[i][s] = *(const bf16x8*)(st + s * APL + (r * GR + ((4 * kc + lq) ^ swz(r))) * 16);
+      }
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const int r = 16 * (NJ * wn + j) + l16;
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+          b[j][s] = *(const bf16x8*)(st + S * APL + s * BPL + (r * GR + ((4 * kc + lq) ^ swz(r))) * 16);
+      }
+      tile_step<S, MI, NJ>(a, b, acc);
+    }
+  }
+  __syncthreads();                                     // the stages are free
+
+  float* ws = reinterpret_cast<float*>(sm) + wave * (16 * 68);   // 16 rows x 64 columns (+ 4) of this wave
+  if constexpr (S == 3) {
+    // An infinite operand has no second and third plane, and products of infinities with planes of
+    // both signs or with zero planes give NaN where the fp32 product is infinite: NaN results are
+    // computed again from the values themselves.
+    bool bad = false;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) bad |= acc[i][j][q] != acc[i][j][q];
+    if (__ballot(bad)) {
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) *(f32x4*)&ws[l16 * 68 + j * 16 + 4 * lq] = acc[i][j];
+        for (int e = 0; e < 16; ++e) {
+          float& v = ws[l16 * 68 + (e >> 2) * 16 + 4 * lq + (e & 3)];
+          const int m = 16 * (MI * wm + i) + l16, n = 16 * (NJ * wn + (e >> 2)) + 4 * lq + (e & 3);
+          if (v == v || m >= nr || n >= nc) continue;
+          float t = 0.f;
+          for (int k = 0; k < g.K; ++k)
+            t = fmaf(plane_sum(A, g.aplane, (size_t)m * g.lda + k), plane_sum(Bp, g.bplane, (size_t)n * g.ldb + k), t);
+          v = t;
+        }
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] = *(const f32x4*)&ws[l16 * 68 + j * 16 + 4 * lq];
+      }
+    }
+  }
+
+  float bias[NJ][4];
+#pragma unroll
+  for (int j = 0; j < NJ; ++j)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int n = n0 + 16 * (NJ * wn + j) + 4 * lq + q;
+      bias[j][q] = (EPI != NT_DX && n < g.N) ? g.bias[perm_to_orig(n, g.H)] : 0.f;
+    }
+
+  if constexpr (EPI == NT_LEAF) {
+    // a lane's four columns are the four gates of one unit: the cell runs on the accumulators,
+    // h and c go through LDS and out as whole 4 BN / 4-byte row pieces
+    constexpr int UN = BN / 4;
+    float* hs = reinterpret_cast<float*>(sm);
+    float* cs = hs + BM * UN;
+    const int H = g.H;
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      const int r = 16 * (MI * wm + i) + l16;
+      const int par = g.opar[m0 + min(r, nr - 1)];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const int ul = 4 * (NJ * wn + j) + lq, u = min(n0 / 4 + ul, H - 1);
+        const f32x4 hu = *(const f32x4*)(g.hu + (size_t)par * (4 * H) + 4 * u);
+        const float cp = g.cn[(size_t)par * H + u];
+        const float gi = sigmoidf_(acc[i][j][0] + bias[j][0] + hu[0]);
+        const float gf = sigmoidf_(acc[i][j][1] + bias[j][1] + hu[1]);
+        const float gg = tanhf_(acc[i][j][2] + bias[j][2] + hu[2]);
+        const float go = sigmoidf_(acc[i][j][3] + bias[j][3] + hu[3]);
+        const float c = gf * cp + gi * gg;
+        hs[r * UN + ul] = canon_nan(go * tanhf_(c));
+        cs[r * UN + ul] = c;
+      }
+    }
+    __syncthreads();
+    const int uw = min(UN, H - n0 / 4);                // units of this block
+    const bool vec = (H & 3) == 0 && ((((uintptr_t)g.hcell) | ((uintptr_t)g.ccell)) & 15u) == 0;
+    for (int e = tid; e < nr * (UN / 4); e += 512) {
+      const int r = e / (UN / 4), v = (e % (UN / 4)) * 4;
+      if (v >= uw) continue;
+      const size_t o = (size_t)g.order[m0 + r] * H + n0 / 4 + v;
+      const f32x4 h4 = *(const f32x4*)&hs[r * UN + v], c4 = *(const f32x4*)&cs[r * UN + v];
+      if (vec) {
+        __builtin_nontemporal_store(h4, (f32x4*)(g.hcell + o));
+        __builtin_nontemporal_store(c4, (f32x4*)(g.ccell + o));
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (v + q < uw) {
+            g.hcell[o + q] = h4[q];
+            g.ccell[o + q] = c4[q];
+          }
+      }
+    }
+  } else {
+    // each wave turns 16 rows x 64 columns at a time into 256-byte row pieces through LDS
+    const bool vec = (g.ldc & 3) == 0 && (((uintptr_t)g.C) & 15u) == 0;
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+        *(f32x4*)&ws[l16 * 68 + j * 16 + 4 * lq] =
+            f32x4{acc[i][j][0] + bias[j][0], acc[i][j][1] + bias[j][1], acc[i][j][2] + bias[j][2],
+                  acc[i][j][3] + bias[j][3]};
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int r = 4 * e + (lane >> 4), m = 16 * (MI * wm + i) + r, n = n0 + 64 * wn + 4 * l16;
+        if (m >= nr) continue;
+        const f32x4 v = *(const f32x4*)&ws[r * 68 + 4 * l16];
+        float* dst = g.C + (size_t)(EPI == NT_DX ? g.order[m0 + m] : m0 + m) * g.ldc + n;
+        if (vec && n + 3 < g.N) {
+          *(f32x4*)dst = v;
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (n + q < g.N) dst[q] = v[q];
+        }
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+  }
+}
+
+// dW | dU. Both operands are stored with the contraction index as rows, so a fragment is read from
+// LDS by transposing reads (four k of a column per lane and read). Rows of a stage are whole block
+// widths; granule c of row k sits at c ^ 2 p(k), p = k & 3 with bit 3 of k above it, so that the eight
+// rows that half a wave reads at once fall into different banks.
+template <int S>
+__global__ void __launch_bounds__(512, 2) k_tn(TnArgs g) {
+  constexpr int BM = nt_bm(S), BN = nt_bn(S), BK = nt_bk(S);
+  constexpr int MI = S == 3 ? 4 : 8, NJ = 4, WN = BN / (16 * NJ);
+  constexpr int AG = BM / 8, BG = BN / 8;                          // granules per row
+  constexpr int APL = BK * BM * 2, BPL = BK * BN * 2, STAGE = S * (APL + BPL);
+  constexpr int IA = BK * AG / 512, IB = BK * BG / 512;
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  extern __shared__ __align__(16) unsigned char sm[];
+  const int NTL = (g.H4 + BN - 1) / BN, MTL = g.xt + (g.H + BM - 1) / BM, per = NTL * MTL, nblk = per * g.splits;
+  int lid = (int)blockIdx.x;
+  {
+    const int full = nblk & ~7;
+    if (lid < full) lid = (lid & 7) * (full >> 3) + (lid >> 3);
+  }
+  const int z = lid / per, rem = lid % per, tm = rem % MTL, n0 = (rem / MTL) * BN;
+  const bool is_x = tm < g.xt;
+  const int m0 = (is_x ? tm : tm - g.xt) * BM, mlim = is_x ? g.I : g.H;   // columns of the operand array
+  const int P = (int)g.ctl[CTL_NPUSHF];
+  const int chunk = ((P + g.splits - 1) / g.splits + BK - 1) / BK * BK;
+  const int kbeg = min(P, z * chunk), kend = min(P, kbeg + chunk);
+  const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
+  const int wm = wave / WN, wn = wave % WN, l16 = lane & 15, lq = lane >> 4;
+  const uint16_t* A = is_x ? g.X : g.Hp;
+  const size_t aplane = is_x ? g.xplane : g.hplane;
+  const int lda = is_x ? g.ldx : g.ldh;
+
+  auto sw2 = [](int k) { return 2 * ((k & 3) | (((k >> 3) & 1) << 2)); };
+  // array row of each of this lane's A rows in a slice (h_prev: the parent, looked up a slice ahead)
+  int arow[IA];
+  auto rows = [&](int k0) {
+#pragma unroll
+    for (int i = 0; i < IA; ++i) {
+      const int k = k0 + ((i * 8 + wave) * 64 + lane) / AG;
+      int r = k;
+      if (!is_x) {
+        r = g.opar[min(k, P - 1)];
+      }
+      arow[i] = k < kend ? r : -1;
+    }
+  };
+  auto issue = [&](int k0, int buf) {
+    unsigned char* st = sm + buf * STAGE;
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      // x rows are consecutive: offsets from the slice's first row
+      const uint16_t* ab = A + s * aplane + (is_x ? (size_t)k0 * lda : 0);
+      const rsrc_t ra = make_rsrc(ab, (size_t)(is_x ? min(BK, kend - k0) : g.hrows) * lda * 2);
+      const rsrc_t rb = make_rsrc(g.D + s * g.dplane + (size_t)k0 * g.ldd, (size_t)min(BK, kend - k0) * g.ldd * 2);
+#pragma unroll
+      for (int i = 0; i < IA; ++i) {
+        const int L = (i * 8 + wave) * 64 + lane, kr = L / AG, col = m0 + 8 * ((L % AG) ^ sw2(kr));
+        const uint32_t row = (uint32_t)(is_x ? arow[i] - k0 : arow[i]);
+        bdma16(ra, (arow[i] >= 0 && col < lda) ? (row * (uint32_t)lda + (uint32_t)col) * 2u : kOOB, 0u,
+               lds_addr(st + s * APL + (i * 8 + wave) * 1024));
+      }
+#pragma unroll
+      for (int i = 0; i < IB; ++i) {
+        const int L = (i * 8 + wave) * 64 + lane, kr = L / BG, col = n0 + 8 * ((L % BG) ^ sw2(kr));
+        bdma16(rb, (k0 + kr < kend && col < g.ldd) ? (uint32_t)(kr * g.ldd + col) * 2u : kOOB, 0u,
+               lds_addr(st + S * APL + s * BPL + (i * 8 + wave) * 1024));
+      }
+    }
+  };
+
+  f32x4 acc[MI][NJ];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // transposing reads: lane group lq holds k = 8 lq .. 8 lq + 7; a lane gives the address of row
+  // 8 lq + l16 / 4, columns 4 (l16 % 4) of the tile, and gets column l16, four consecutive k
+  const int kf = 8 * lq + (l16 >> 2), pf = sw2(kf);
+  auto addr = [&](int tile, int G) { return kf * (G * 16) + (((2 * tile + ((l16 & 3) >> 1)) ^ pf) * 16) + (l16 & 1) * 8; };
+  auto frag = [&](const unsigned char* p, int G) {
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(p));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(p + 4 * G * 16));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+  if (kbeg < kend) {
+    rows(kbeg);
+    issue(kbeg, 0);
+    rows(kbeg + BK);
+  }
+  int buf = 0;
+  for (int k0 = kbeg; k0 < kend; k0 += BK, buf ^= 1) {
+    wait_vm<0>();
+    __syncthreads();
+    if (k0 + BK < kend) {
+      issue(k0 + BK, buf ^ 1);
+      rows(k0 + 2 * BK);
+    }
+    const unsigned char* st = sm + buf * STAGE;
+#pragma unroll
+    for (int kc = 0; kc < BK / 32; ++kc) {
+      bf16x8 a[MI][S], b[NJ][S];
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        const unsigned char* p = st + kc * 32 * AG * 16 + addr(MI * wm + i, AG);
+#pragma unroll
+        for (int s = 0; s < S; ++s) a[i][s] = frag(p + s * APL, AG);
+      }
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const unsigned char* p = st + S * APL + kc * 32 * BG * 16 + addr(NJ * wn + j, BG);
+#pragma unroll
+        for (int s = 0; s < S; ++s) b[j][s] = frag(p + s * BPL, BG);
+      }
+      tile_step<S, MI, NJ>(a, b, acc);
+    }
+  }
+  __syncthreads();
+  float* ws = reinterpret_cast<float*>(sm) + wave * (16 * 68);
+  float* out = g.part + (size_t)z * g.split_stride + (size_t)(is_x ? 0 : g.I) * g.H4;
+#pragma unroll
+  for (int i = 0; i < MI; ++i) {
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) *(f32x4*)&ws[l16 * 68 + j * 16 + 4 * lq] = acc[i][j];
+    __builtin_amdgcn_wave_barrier();
+    if constexpr (S == 3) {                             // NaN: as in k_nt
+      bool bad = false;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) bad |= acc[i][j][q] != acc[i][j][q];
+      if (__ballot(bad)) {
+        for (int e = 0; e < 16; ++e) {
+          float& v = ws[l16 * 68 + (e >> 2) * 16 + 4 * lq + (e & 3)];
+          const int m = m0 + 16 * (MI * wm + i) + l16, n = n0 + 16 * (NJ * wn + (e >> 2)) + 4 * lq + (e & 3);
+          if (v == v || m >= mlim || n >= g.H4) continue;
+          float t = 0.f;
+          for (int k = kbeg; k < kend; ++k) {
+            const int r = is_x ? k : g.opar[k];
+            t = fmaf(plane_sum(A, aplane, (size_t)r * lda + m), plane_sum(g.D, g.dplane, (size_t)k * g.ldd + n), t);
+          }
+          v = t;
+        }
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = 4 * e + (lane >> 4), m = m0 + 16 * (MI * wm + i) + r, n = n0 + 64 * wn + 4 * l16;
+      if (m < mlim && n < g.H4) *(f32x4*)(out + (size_t)m * g.H4 + n) = *(const f32x4*)&ws[r * 68 + 4 * l16];
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
+// dW [I][4H], dU [H][4H] and db [4H] in the caller's column order: the partials of k_tn, and of the
+// groups for db, added in order.
+__global__ void __launch_bounds__(256) k_reduce_grads(const float* __restrict__ part, int splits, size_t stride,
+                                                      const float* __restrict__ db_part, int groups, int I, int H,
+                                                      float* __restrict__ dW, float* __restrict__ dU,
+                                                      float* __restrict__ db) {
+  const int H4 = 4 * H;
+  const size_t n_w = (size_t)I * H, n = n_w + (size_t)H * H + H;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+    const size_t row = i / H;
+    const int u = (int)(i - row * H);
+    const bool bias = row == (size_t)(I + H);
+    const float* src = bias ? db_part : part + row * H4;
+    const size_t st = bias ? (size_t)H4 : stride;
+    const int cnt = bias ? groups : splits;
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
+    for (int z = 0; z < cnt; ++z) s += *(const f32x4*)(src + (size_t)z * st + 4 * u);
+    float* dst = bias ? db : (row < (size_t)I ? dW + row * H4 : dU + (row - I) * H4);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) dst[(size_t)k * H + u] = s[k];
+  }
+}
+
+template <int S, int EPI>
+static hipError_t launch_nt_t(const NtArgs& g, hipStream_t st) {
+  auto kern = k_nt<S, EPI>;
+  constexpr int shm = (int)nt_lds(S);
+  const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, shm);
+  if (e != hipSuccess) return e;
+  // the grid covers the static range; blocks past the rows in use leave at once
+  const int tiles = ((g.N + nt_bn(S) - 1) / nt_bn(S)) * ((g.hi - g.lo + nt_bm(S) - 1) / nt_bm(S));
+  hipLaunchKernelGGL(kern, dim3(tiles), dim3(512), shm, st, g);
+  return hipGetLastError();
+}
+hipError_t launch_nt(const NtArgs& g, int S, int epi, hipStream_t st) {
+  if (g.hi <= g.lo) return hipSuccess;
+#define CASE(S_, E_) \
+  if (S == S_ && epi == E_) return launch_nt_t<S_, E_>(g, st);
+  CASE(1, NT_XW) CASE(1, NT_LEAF) CASE(1, NT_DX) CASE(3, NT_XW) CASE(3, NT_LEAF) CASE(3, NT_DX)
+#undef CASE
+  return hipErrorInvalidValue;
+}
+template <int S>
+static hipError_t launch_tn_t(const TnArgs& g, hipStream_t st) {
+  auto kern = k_tn<S>;
+  constexpr int shm = (int)nt_lds(S);
+  const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, shm);
+  if (e != hipSuccess) return e;
+  const int tiles = ((g.H4 + nt_bn(S) - 1) / nt_bn(S)) * (g.xt + (g.H + nt_bm(S) - 1) / nt_bm(S));
+  hipLaunchKernelGGL(kern, dim3(tiles * g.splits), dim3(512), shm, st, g);
+  return hipGetLastError();
+}
+hipError_t launch_tn(const TnArgs& g, int S, hipStream_t st) { return S == 3 ? launch_tn_t<3>(g, st) : launch_tn_t<1>(g, st); }

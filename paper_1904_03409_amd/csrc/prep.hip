@@ -1,0 +1,260 @@
+// Operand preparation: bf16 planes (split.h) of x, W, U and the initial states in the layouts the
+// contractions read, and the interval sums of the upstream gradient. All bandwidth bound.
+#include "common.h"
+#include "levels.h"
+#include "prep.h"
+#include "split.h"
+
+// Rows lo .. hi-1 of the step list (push nodes, then leaves) of x as planes [S][hi - lo][Ip],
+// zero past I.
+template <int S>
+__global__ void __launch_bounds__(256) k_split_x(const float* __restrict__ x, const int32_t* __restrict__ order, int lo,
+                                                 int hi, int I, int Ip, int vec, bf16_t* __restrict__ out, size_t plane) {
+  const int gr = Ip / 8;
+  const size_t n = (size_t)(hi - lo) * gr;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+    const size_t row = i / gr;
+    const int k = (int)(i - row * gr) * 8;
+    const float* src = x + (size_t)order[lo + row] * I + k;
+    float v[8];
+    if (vec && k + 8 <= I) {
+      const float4 p = *(const float4*)src, q = *(const float4*)(src + 4);
+      v[0] = p.x; v[1] = p.y; v[2] = p.z; v[3] = p.w; v[4] = q.x; v[5] = q.y; v[6] = q.z; v[7] = q.w;
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = k + j < I ? src[j] : 0.f;
+    }
+    uint4 g[S];
+    split_granule<S>(v, g);
+#pragma unroll
+    for (int s = 0; s < S; ++s) *(uint4*)(out + s * plane + row * Ip + k) = g[s];
+  }
+}
+template __global__ void k_split_x<1>(const float*, const int32_t*, int, int, int, int, int, bf16_t*, size_t);
+template __global__ void k_split_x<3>(const float*, const int32_t*, int, int, int, int, int, bf16_t*, size_t);
+
+// Forward operands, by block range:
+//  * W tiles of 32 inputs x 32 units: wt [S][4H][Ip] (rows n = 4u + gate) and wp [S][I][H4s]
+//    (columns n), through LDS so that both are written along their rows;
+//  * U fragments (MFMA A operand) of the forward, per 8 units of a workgroup:
+//    uf[w][wave][tile][chunk][plane][lane], wave = column pair + 4 K half, a lane's eight values
+//    U[32 (half KS / 2 + chunk) + 8 lq + j][column of (unit 32 w + 8 pair + 4 tile + l16 / 4, gate
+//    l16 % 4)]; fp32 mode: scaled per unit, odd chunks as mfma_rec takes them (split.h);
+//  * the initial states as nodes (planes of h0 and a copy of c0), one wave per element.
+template <int S>
+__global__ void __launch_bounds__(256) k_prep_fwd(PrepFwdArgs a) {
+  __shared__ float tile[32][129];
+  const int tid = threadIdx.x, H = a.H, I = a.I;
+  int blk = blockIdx.x;
+  if (blk < a.n_w) {
+    const int ut = (H + 31) / 32, i0 = (blk / ut) * 32, u0 = (blk % ut) * 32;
+    for (int e = tid; e < 32 * 128; e += 256) {
+      const int i = e >> 7, k = (e >> 5) & 3, u = e & 31;
+      tile[i][4 * u + k] = (i0 + i < I && u0 + u < H) ? a.W[(size_t)(i0 + i) * 4 * H + (size_t)k * H + u0 + u] : 0.f;
+    }
+    __syncthreads();
+    for (int e = tid; e < 32 * 16; e += 256) {
+      const int i = e >> 4, c = (e & 15) * 8, n = 4 * u0 + c;
+      if (i0 + i >= I || n >= a.H4s) continue;
+      float v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = tile[i][c + j];
+      uint4 g[S];
+      split_granule<S>(v, g);
+#pragma unroll
+      for (int s = 0; s < S; ++s) *(uint4*)(a.wp + (size_t)s * I * a.H4s + (size_t)(i0 + i) * a.H4s + n) = g[s];
+    }
+    for (int e = tid; e < 128 * 4; e += 256) {
+      const int c = e >> 2, i = (e & 3) * 8, n = 4 * u0 + c;
+      if (n >= 4 * H || i0 + i >= a.Ip) continue;
+      float v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) v[j] = tile[i + j][c];
+      uint4 g[S];
+      split_granule<S>(v, g);
+#pragma unroll
+      for (int s = 0; s < S; ++s) *(uint4*)(a.wt + ((size_t)s * 4 * H + n) * a.Ip + i0 + i) = g[s];
+    }
+    return;
+  }
+  blk -= a.n_w;
+  constexpr int NP = S == 3 ? 2 : 1;
+  const int lane = tid & 63;
+  if (blk < a.n_u) {
+    const int w = blk >> 2, pair = blk & 3, u0 = 32 * w + 8 * pair;
+    __shared__ float s_max[256];
+    float m = 0.f;
+    if (S == 3) {
+      const int unit = u0 + (tid & 7), gate = (tid >> 3) & 3;
+      if (unit < H)
+        for (int k = tid >> 5; k < H; k += 8) m = fmaxf(m, fabsf(a.U[(size_t)k * 4 * H + (size_t)gate * H + unit]));
+      s_max[tid] = m;
+      __syncthreads();
+      for (int k = 8; k < 256; k += 8) m = fmaxf(m, s_max[(tid & 7) + k]);
+      m = fmaxf(m, s_max[tid & 7]);
+      __syncthreads();
+      const float sc = rec_scale(m);
+      s_max[tid] = sc;
+      if (tid < 8) a.uinv[u0 + tid] = 1.f / (sc * kHScale);
+      __syncthreads();
+    }
+    const int KH = a.KS / 2;
+    for (int f = tid; f < 4 * KH * 64; f += 256) {       // (half, tile, chunk, lane)
+      const int c = (f >> 6) % KH, tile = (f >> 6) / KH & 1, half = (f >> 6) / KH >> 1;
+      const int ul = 4 * tile + ((lane & 15) >> 2), unit = u0 + ul, gate = lane & 3, kc = half * KH + c;
+      const float sc = S == 3 ? s_max[ul] : 1.f;
+      float v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int k = 32 * kc + 8 * (lane >> 4) + j;
+        v[j] = (k < H && unit < H) ? a.U[(size_t)k * 4 * H + (size_t)gate * H + unit] : 0.f;
+      }
+      uint4 g[NP];
+      split_rec_granule<NP>(v, sc, g);
+      if (S == 3 && (kc & 1)) g[0] = rec_negated(g[0]);
+#pragma unroll
+      for (int s = 0; s < NP; ++s)
+        a.uf[((((size_t)(w * 8 + pair + 4 * half) * 2 + tile) * KH + c) * NP + s) * 64 + lane] = g[s];
+    }
+    return;
+  }
+  blk -= a.n_u;
+  const int b = blk * 4 + (tid >> 6);
+  if (b >= a.B) return;
+  const int init = lev_goff(a.B, a.G, b % a.G) + b / a.G;
+  const size_t node = (size_t)a.N0 + init;
+  float sc = 1.f;
+  if (S == 3) {
+    float m = 0.f;
+    for (int k = lane; k < H; k += 64) m = fmaxf(m, fabsf(a.h0[(size_t)b * H + k]));
+#pragma unroll
+    for (int d = 32; d; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, 64));
+    sc = m < 1.f ? kHScale : rec_scale(m);
+    if (lane == 0) a.rinit[init] = kHScale / sc;
+  }
+  for (int k = lane; k < a.Hs; k += 64) {
+    const float v = k < H ? a.h0[(size_t)b * H + k] : 0.f;
+    if (k < H) a.cn[node * H + k] = a.c0[(size_t)b * H + k];
+    uint16_t p[NP];
+    split_rec<NP>(v, sc, p);
+#pragma unroll
+    for (int s = 0; s < NP; ++s) a.hq[s * a.hplane + node * a.Hs + k] = p[s];
+    if (S == 3 && a.h3) {
+      bf16_t q[3];
+      split_bf16<3>(v, q);
+#pragma unroll
+      for (int s = 0; s < 3; ++s) a.h3[s * a.hplane + node * a.Hs + k] = q[s];
+    }
+  }
+}
+template __global__ void k_prep_fwd<1>(PrepFwdArgs);
+template __global__ void k_prep_fwd<3>(PrepFwdArgs);
+
+// Backward operands: the U^T fragments (MFMA A operand) ub[w][wave][tile][chunk][plane][lane], a
+// lane's eight values U[unit 32 w + 16 tile + l16][column of gate column 32 (wave KS / 2 + chunk) +
+// 8 lq + j], in fp32 mode scaled per unit, odd chunks as mfma_rec takes them; and the check of the caller's top and
+// ops: a producer index outside [-1, t], or an op that is a push where the forward's was not (or
+// the reverse), raises CTL_BADIDX.
+template <int S>
+__global__ void __launch_bounds__(256) k_prep_bwd(PrepBwdArgs a) {
+  constexpr int NP = S == 3 ? 2 : 1;
+  const int H = a.H, H4 = 4 * H, tid = threadIdx.x, lane = tid & 63;
+  if (blockIdx.x < (unsigned)a.n_u) {
+    const int w = blockIdx.x >> 1, tile = blockIdx.x & 1, u0 = 32 * w + 16 * tile, KH = a.KS / 2;
+    __shared__ float s_sc[16];
+    if (S == 3) {
+      const int unit = u0 + (tid >> 4);
+      float m = 0.f;
+      if (unit < H)
+        for (int n = tid & 15; n < H4; n += 16) m = fmaxf(m, fabsf(a.U[(size_t)unit * H4 + n]));
+#pragma unroll
+      for (int d = 8; d; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, 16));
+      if ((tid & 15) == 0) {
+        const float sc = rec_scale(m);
+        s_sc[tid >> 4] = sc;
+        a.uinv[unit] = 1.f / sc;
+      }
+      __syncthreads();
+    }
+    const int unit = u0 + (lane & 15);
+    for (int f = tid; f < 8 * KH * 64; f += 256) {       // (wave, chunk, lane)
+      const int c = (f >> 6) % KH, wave = (f >> 6) / KH, kc = wave * KH + c;
+      const float sc = S == 3 ? s_sc[lane & 15] : 1.f;
+      float v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int np = 32 * kc + 8 * (lane >> 4) + j;
+        v[j] = (unit < H && np < H4) ? a.U[(size_t)unit * H4 + perm_to_orig(np, H)] : 0.f;
+      }
+      uint4 g[NP];
+      split_rec_granule<NP>(v, sc, g);
+      if (S == 3 && (kc & 1)) g[0] = rec_negated(g[0]);
+#pragma unroll
+      for (int s = 0; s < NP; ++s)
+        a.ub[((((size_t)(w * 8 + wave) * 2 + tile) * KH + c) * NP + s) * 64 + lane] = g[s];
+    }
+    return;
+  }
+  const size_t f = (size_t)blockIdx.x * 256 + tid;
+  const size_t n = (size_t)a.T * a.B, step = (size_t)(gridDim.x - a.n_u) * 256;
+  const size_t P = a.ctl[CTL_NPUSHF];
+  bool bad = false;
+  for (size_t i = f - (size_t)a.n_u * 256; i < n; i += step) {
+    const int s = a.top[i];
+    bad |= s < -1 || s > (int)(i / a.B);
+    bad |= (a.ops[a.order[i]] == 1) != (i < P);
+  }
+  if (bad) raise_badidx(a.ctl);
+}
+template __global__ void k_prep_bwd<1>(PrepBwdArgs);
+template __global__ void k_prep_bwd<3>(PrepBwdArgs);
+
+// Sums of an upstream gradient [T][B][H] over the intervals of steps during which one state stays
+// on top: G[gslot][:] (slots: a push node's first interval; N0 + B + the popped node for the
+// interval of its parent that follows; an initial state's first interval). An interval is a run
+// of consecutive steps of one element, so a thread that walks the element's steps for V units
+// writes every slot once, with no atomics, and loads ahead of the sums. One wave per element
+// and 64 V units.
+template <int V>
+__global__ void __launch_bounds__(256) k_gsum(const float* __restrict__ d, const int32_t* __restrict__ gslot, int T, int B,
+                                              int H, int G, float* __restrict__ out) {
+  constexpr int UN = 16;
+  typedef float fv __attribute__((ext_vector_type(V)));
+  const int lane = threadIdx.x & 63, parts = (H + 64 * V - 1) / (64 * V);
+  const int wv = uni((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+  if (wv >= B * parts) return;
+  const int b = wv / parts, u = (wv % parts) * 64 * V + lane * V;
+  const bool on = u < H;
+  const size_t rs = (size_t)B * H;
+  const float* src = d + (size_t)b * H + u;
+  int cur = T * B + lev_goff(B, G, b % G) + b / G;
+  fv acc = 0.f;
+  for (int t0 = 0; t0 < T; t0 += 64) {
+    const int ts = t0 + lane;
+    const int sl = ts < T ? gslot[(size_t)ts * B + b] : 0;
+    const int tn = min(64, T - t0);
+    for (int k0 = 0; k0 < tn; k0 += UN) {
+      fv v[UN];
+#pragma unroll
+      for (int k = 0; k < UN; ++k)
+        if (on && k0 + k < tn) v[k] = __builtin_nontemporal_load((const fv*)(src + (size_t)(t0 + k0 + k) * rs));
+        else v[k] = 0.f;
+#pragma unroll
+      for (int k = 0; k < UN; ++k) {
+        if (k0 + k < tn) {
+          const int s = __builtin_amdgcn_readlane(sl, k0 + k);
+          if (s != cur) {
+            if (on) *(fv*)(out + (size_t)cur * H + u) = acc;
+            cur = s;
+            acc = v[k];
+          } else {
+            acc += v[k];
+          }
+        }
+      }
+    }
+  }
+  if (on) *(fv*)(out + (size_t)cur * H + u) = acc;
+}
+template __global__ void k_gsum<1>(const float*, const int32_t*, int, int, int, int, float*);
+template __global__ void k_gsum<4>(const float*, const int32_t*, int, int, int, int, float*);
