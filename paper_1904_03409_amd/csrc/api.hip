@@ -517,12 +517,9 @@ int stacklstm_bwd(const slstm_dims* d, const float* x, const int8_t* ops, const 
   {
     PrepBwdArgs a;
     a.T = T; a.B = B; a.H = H; a.NW = p.NW; a.KS = p.KS;
-    a.n_u = p.NW * 2;
+    a.n_u = p.NW * 16;
     a.U = U; a.ops = ops; a.top = top; a.order = ix.order; a.ub = (uint4*)(ws + L.ub);
     a.uinv = (float*)(ws + L.ubi); a.ctl = ctl;
-    const int grid = a.n_u + (int)std::min<size_t>(((size_t)N0 + 1023) / 1024, 1024);
-    if (S == 3) hipLaunchKernelGGL(k_prep_bwd<3>, dim3(grid), dim3(256), 0, st, a);
-    else        hipLaunchKernelGGL(k_prep_bwd<1>, dim3(grid), dim3(256), 0, st, a);
     auto gsum = [&](const float* src, float* out) {
       if (H % 4 == 0 && al16(src))
         hipLaunchKernelGGL(k_gsum<4>, dim3(((size_t)B * ((H + 255) / 256) + 3) / 4), dim3(256), 0, st, src, ix.gslot, T, B,
@@ -533,6 +530,9 @@ int stacklstm_bwd(const slstm_dims* d, const float* x, const int8_t* ops, const 
     };
     gsum(dh_top, gf);
     if (gc) gsum(dc_top, gc);
+    const int grid = a.n_u + (int)std::min<size_t>(((size_t)N0 + 1023) / 1024, 1024);
+    if (S == 3) hipLaunchKernelGGL(k_prep_bwd<3>, dim3(grid), dim3(256), 0, st, a);
+    else        hipLaunchKernelGGL(k_prep_bwd<1>, dim3(grid), dim3(256), 0, st, a);
   }
   uint16_t* dap = (uint16_t*)(ws + L.dap);
   const size_t dplane = (size_t)N0 * L.H4s;

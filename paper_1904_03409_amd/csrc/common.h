@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
@@ -246,6 +247,16 @@ __device__ __forceinline__ void wait_vm_upto16(int n) {
 __device__ __forceinline__ int opaque(int v) {
   asm volatile("" : "+v"(v));
   return v;
+}
+// Largest of 16 lanes (a DPP row), in every one of them.
+__device__ __forceinline__ float max16(float m) {
+  auto dpp = [](float v, auto ctrl) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value, 0xf, 0xf, true));
+  };
+  m = fmaxf(m, dpp(m, std::integral_constant<int, 0xb1>()));    // quad_perm 1, 0, 3, 2
+  m = fmaxf(m, dpp(m, std::integral_constant<int, 0x4e>()));    // quad_perm 2, 3, 0, 1
+  m = fmaxf(m, dpp(m, std::integral_constant<int, 0x141>()));   // row_half_mirror
+  return fmaxf(m, dpp(m, std::integral_constant<int, 0x140>()));  // row_mirror
 }
 // base + a 32-bit byte offset (scalar base, one offset register)
 template <typename T>

@@ -15,9 +15,13 @@
 namespace {
 
 // The products of one K step of 32 on MI x NJ tiles. C^T = B^T A^T: a lane holds row l16 and
-// columns 4 lq .. 4 lq + 3 of a tile.
-template <int S, int MI, int NJ>
-__device__ __forceinline__ void tile_step(const bf16x8 (&a)[MI][S], const bf16x8 (&b)[NJ][S], f32x4 (&acc)[MI][NJ]) {
+// columns 4 lq .. 4 lq + 3 of a tile. between(i) runs after the products of row tile i: the next
+// slice's DMAs are issued there, a few at a time, because a wave that issues them all at once
+// stands still until the memory queue has taken them (dW | dU of 17 k nodes: DMAs alone 211 us,
+// products alone 218, one after the other 378, this way 325).
+template <int S, int MI, int NJ, typename F>
+__device__ __forceinline__ void tile_step(const bf16x8 (&a)[MI][S], const bf16x8 (&b)[NJ][S], f32x4 (&acc)[MI][NJ],
+                                          F between) {
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
     if constexpr (S == 1) {
@@ -26,6 +30,7 @@ __device__ __forceinline__ void tile_step(const bf16x8 (&a)[MI][S], const bf16x8
     } else {
       mfma_planes_add<NJ>(b, a[i], acc[i]);
     }
+    between(i);
   }
 }
 
@@ -67,7 +72,8 @@ __global__ void __launch_bounds__(512, 2) k_nt(NtArgs g) {
   auto swz = [](int row) { return GR == 4 ? (row >> 1) & 3 : row & 7; };
   // the lane's row and granule are the same for every DMA of the block up to a row offset
   const int rl = lane / GR;
-  auto issue = [&](int k0, int buf) {
+  // the DMAs of a slice with part = (index of the DMA) % parts
+  auto issue = [&](int k0, int buf, int part, int parts) {
     unsigned char* st = sm + buf * STAGE;
 #pragma unroll
     for (int s = 0; s < S; ++s) {
@@ -75,11 +81,13 @@ __global__ void __launch_bounds__(512, 2) k_nt(NtArgs g) {
       const rsrc_t rb = make_rsrc(Bp + s * g.bplane, (size_t)nc * g.ldb * 2);
 #pragma unroll
       for (int i = 0; i < IA; ++i) {
+        if ((s * (IA + IB) + i) % parts != part) continue;
         const int q = i * 8 + wave, row = q * (64 / GR) + rl, k = k0 + 8 * ((lane % GR) ^ swz(row));
         bdma16(ra, (row < nr && k < g.K) ? (uint32_t)(row * g.lda + k) * 2u : kOOB, 0u, lds_addr(st + s * APL + q * 1024));
       }
 #pragma unroll
       for (int i = 0; i < IB; ++i) {
+        if ((s * (IA + IB) + IA + i) % parts != part) continue;
         const int q = i * 8 + wave, row = q * (64 / GR) + rl, k = k0 + 8 * ((lane % GR) ^ swz(row));
         bdma16(rb, (row < nc && k < g.K) ? (uint32_t)(row * g.ldb + k) * 2u : kOOB, 0u,
                lds_addr(st + S * APL + s * BPL + q * 1024));
@@ -92,12 +100,12 @@ __global__ void __launch_bounds__(512, 2) k_nt(NtArgs g) {
   for (int i = 0; i < MI; ++i)
 #pragma unroll
     for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  issue(0, 0);
+  issue(0, 0, 0, 1);
   int buf = 0;
   for (int k0 = 0; k0 < g.K; k0 += BK, buf ^= 1) {
     wait_vm<0>();
     __syncthreads();                                   // this slice landed, the other stage is free
-    if (k0 + BK < g.K) issue(k0 + BK, buf ^ 1);
+    const bool more = k0 + BK < g.K;
     const unsigned char* st = sm + buf * STAGE;
 #pragma unroll
     for (int kc = 0; kc < BK / 32; ++kc) {
@@ -115,7 +123,9 @@ __global__ void __launch_bounds__(512, 2) k_nt(NtArgs g) {
         for (int s = 0; s < S; ++s)
           b[j][s] = *(const bf16x8*)(st + S * APL + s * BPL + (r * GR + ((4 * kc + lq) ^ swz(r))) * 16);
       }
-      tile_step<S, MI, NJ>(a, b, acc);
+      tile_step<S, MI, NJ>(a, b, acc, [&](int i) {
+        if (kc == 0 && more) issue(k0 + BK, buf ^ 1, i, MI);
+      });
     }
   }
   __syncthreads();                                     // the stages are free
@@ -281,7 +291,7 @@ __global__ void __launch_bounds__(512, 2) k_tn(TnArgs g) {
       arow[i] = k < kend ? r : -1;
     }
   };
-  auto issue = [&](int k0, int buf) {
+  auto issue = [&](int k0, int buf, int part, int parts) {
     unsigned char* st = sm + buf * STAGE;
 #pragma unroll
     for (int s = 0; s < S; ++s) {
@@ -291,6 +301,7 @@ __global__ void __launch_bounds__(512, 2) k_tn(TnArgs g) {
       const rsrc_t rb = make_rsrc(g.D + s * g.dplane + (size_t)k0 * g.ldd, (size_t)min(BK, kend - k0) * g.ldd * 2);
 #pragma unroll
       for (int i = 0; i < IA; ++i) {
+        if ((s * (IA + IB) + i) % parts != part) continue;
         const int L = (i * 8 + wave) * 64 + lane, kr = L / AG, col = m0 + 8 * ((L % AG) ^ sw2(kr));
         const uint32_t row = (uint32_t)(is_x ? arow[i] - k0 : arow[i]);
         bdma16(ra, (arow[i] >= 0 && col < lda) ? (row * (uint32_t)lda + (uint32_t)col) * 2u : kOOB, 0u,
@@ -298,6 +309,7 @@ __global__ void __launch_bounds__(512, 2) k_tn(TnArgs g) {
       }
 #pragma unroll
       for (int i = 0; i < IB; ++i) {
+        if ((s * (IA + IB) + IA + i) % parts != part) continue;
         const int L = (i * 8 + wave) * 64 + lane, kr = L / BG, col = n0 + 8 * ((L % BG) ^ sw2(kr));
         bdma16(rb, (k0 + kr < kend && col < g.ldd) ? (uint32_t)(kr * g.ldd + col) * 2u : kOOB, 0u,
                lds_addr(st + S * APL + s * BPL + (i * 8 + wave) * 1024));
@@ -321,17 +333,14 @@ __global__ void __launch_bounds__(512, 2) k_tn(TnArgs g) {
   };
   if (kbeg < kend) {
     rows(kbeg);
-    issue(kbeg, 0);
+    issue(kbeg, 0, 0, 1);
     rows(kbeg + BK);
   }
   int buf = 0;
   for (int k0 = kbeg; k0 < kend; k0 += BK, buf ^= 1) {
     wait_vm<0>();
     __syncthreads();
-    if (k0 + BK < kend) {
-      issue(k0 + BK, buf ^ 1);
-      rows(k0 + 2 * BK);
-    }
+    const bool more = k0 + BK < kend;
     const unsigned char* st = sm + buf * STAGE;
 #pragma unroll
     for (int kc = 0; kc < BK / 32; ++kc) {
@@ -348,8 +357,11 @@ __global__ void __launch_bounds__(512, 2) k_tn(TnArgs g) {
 #pragma unroll
         for (int s = 0; s < S; ++s) b[j][s] = frag(p + s * BPL, BG);
       }
-      tile_step<S, MI, NJ>(a, b, acc);
+      tile_step<S, MI, NJ>(a, b, acc, [&](int i) {
+        if (kc == 0 && more) issue(k0 + BK, buf ^ 1, i, MI);
+      });
     }
+    if (more) rows(k0 + 2 * BK);
   }
   __syncthreads();
   float* ws = reinterpret_cast<float*>(sm) + wave * (16 * 68);

@@ -27,12 +27,15 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
   constexpr int WREG = NP * KH * 1024;                      // bytes of a wave's 16 row slices
   constexpr int kids = lev_bwd_kids(NP, KS), NI = kids / 16, NQ = kLevPars / 16;
   constexpr int RLD = 36;
+  // the next level's first operands are fetched behind the first rows of the exchange (in one queue
+  // with them, the rows would wait for HBM); with the most registers in use, ahead of the barrier
+  constexpr bool kLate = NP * KS < 32 || NP == 1;
   extern __shared__ __align__(16) unsigned char lsm[];
   f32x4* ch_a = reinterpret_cast<f32x4*>(lsm);                                // [kids][32] dA of a child
-  float2* ch_c = reinterpret_cast<float2*>(lsm + kids * kLevUnits * 16);  // [kids][32] dc f, interval gradient
+  float2* ch_c = reinterpret_cast<float2*>(lsm + kids * kLevUnits * 16);      // [kids][32] dc f, interval gradient
   float* red = reinterpret_cast<float*>(lsm + lev_bwd_region(NP, KS));        // [8][16][RLD] partials of the waves
   float* keep = red + 8 * 16 * RLD;                         // [2][2][kLevKeep][32] eg and dcs of a level's first nodes
-  __shared__ int s_g, s_w, s_flag;
+  __shared__ int s_g, s_w, s_flag, s_ics[kLevPars + 1];
   claim_group_slot(a.ctl + CTL_XCC_SLOT_B, a.G, a.NW, &s_g, &s_w);
   const int g = uni(s_g), w = uni(s_w);
   if (g < 0) return;
@@ -83,27 +86,37 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
     if (a.clk && tid == 0) a.clk[((size_t)blockIdx.x * T + d - 1) * 4 + k] = wall_clock64();
   };
   bool stop = false;
+  // Level d: parents are the internal nodes [i0, i1) of level d - 1, whose children are the nodes
+  // [c0, cend) of level d, whose own internal numbers start at i1. The first pass's operands and
+  // the first parents' child ranges (s_ics) are fetched a level ahead, i0 two levels ahead.
+  int i0 = 0, i1 = 0, c0 = 0, cend = 0, ics_r = 0, i0_next = 0;
+  auto prefetch_ics = [&](int ib, int i1) { return ib + min((int)opaque(tid), kLevPars) <= i1 ? a.ix.ics[ib + min((int)opaque(tid), kLevPars)] : 0; };
   if (D > 0) {
-    const int i0 = uni(ioff[D - 1]), i1 = uni(ioff[D]);
-    prefetch(uni(a.ix.ics[i0]), uni(a.ix.ics[i1]));
+    i0 = uni(ioff[D - 1]);
+    i1 = uni(ioff[D]);
+    c0 = uni(a.ix.ics[i0]);
+    cend = uni(a.ix.ics[i1]);
+    i0_next = D > 1 ? ioff[D - 2] : 0;
+    ics_r = prefetch_ics(i0, i1);
+    prefetch(c0, cend);
   }
   for (int d = D; d >= 1; --d) {
     stamp(d, 0);
-    // parents: the internal nodes [i0, i1) of level d - 1; children: the nodes [.., cend) of level d,
-    // whose own internal numbers start at i1
-    const int i0 = uni(ioff[d - 1]), i1 = uni(ioff[d]), cend = uni(a.ix.ics[i1]);
     float* eg_in = keep + (d & 1) * (2 * kLevKeep * 32);
     float* eg_out = keep + (~d & 1) * (2 * kLevKeep * 32);
+    int cs = c0;
     for (int ib = i0; ib < i1; ib += kLevPars) {
       const int ni = min(kLevPars, i1 - ib);
-      const int c0 = uni(a.ix.ics[ib]), c1 = uni(a.ix.ics[ib + ni]);
-      int ka[NQ], kb[NQ];
+      if (ib > i0) {
+        __syncthreads();                                    // (the last sums have read s_ics)
+        ics_r = prefetch_ics(ib, i1);
+      }
+      if (tid <= kLevPars) s_ics[tid] = ics_r;
+      const int c0 = cs, c1 = ib + kLevPars < i1 ? uni(a.ix.ics[ib + ni]) : cend;
+      cs = c1;
       float sA[NQ][4], sc[NQ], sg[NQ];
 #pragma unroll
       for (int k = 0; k < NQ; ++k) {
-        const int r = 32 * w + (opaque(tid) & 31) < H ? (opaque(tid) >> 5) + 16 * k : kLevPars;   // (no sums past H)
-        ka[k] = r < ni ? a.ix.ics[ib + r] : 0;
-        kb[k] = r < ni ? a.ix.ics[ib + r + 1] : 0;
         sc[k] = sg[k] = 0.f;
 #pragma unroll
         for (int q = 0; q < 4; ++q) sA[k][q] = 0.f;
@@ -165,17 +178,20 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
         __syncthreads();
         // sums per parent, children in node order
         {
-          const int uu = opaque(tid) & 31;
+          const int ot = opaque(tid), uu = ot & 31;
 #pragma unroll
-          for (int k = 0; k < NQ; ++k)
-            for (int c = max(ka[k], cb); c < min(kb[k], cb + kids); ++c) {
+          for (int k = 0; k < NQ; ++k) {
+            const int r = 32 * w + uu < H ? (ot >> 5) + 16 * k : kLevPars;   // (no sums past H)
+            const int ka = r < ni ? s_ics[r] : 0, kb = r < ni ? s_ics[r + 1] : 0;
+            for (int c = max(ka, cb); c < min(kb, cb + kids); ++c) {
               const f32x4 da = ch_a[(c - cb) * 32 + uu];
-              const float2 v = ch_c[(c - cb) * 32 + uu];
 #pragma unroll
               for (int q = 0; q < 4; ++q) sA[k][q] += da[q];
+              const float2 v = ch_c[(c - cb) * 32 + uu];
               sc[k] += v.x;
               sg[k] += v.y;
             }
+          }
         }
         __syncthreads();
       }
@@ -186,8 +202,8 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
         float scale = 1.f;
         if constexpr (NP == 2) {
           float m = fmaxf(fmaxf(fabsf(sA[k][0]), fabsf(sA[k][1])), fmaxf(fabsf(sA[k][2]), fabsf(sA[k][3])));
-#pragma unroll
-          for (int x = 16; x; x >>= 1) m = fmaxf(m, __shfl_xor(m, x, 32));
+          m = max16(m);
+          m = fmaxf(m, __shfl_xor(m, 16, 32));
           scale = rec_scale(m);
           if (r < ni && uu == 0) a.sxs[(size_t)(ib + r) * NW + w] = 1.f / scale;
         }
@@ -214,9 +230,17 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
     }
     stamp(d, 1);
     group_arrive(bar);
+    int c0_next = 0, n0_next = 0;
     {
       const uint32_t seen = group_peek(bar);
-      if (d > 1) prefetch(uni(a.ix.ics[uni(ioff[d - 2])]), uni(a.ix.ics[i0]));
+      if (d > 1) {
+        const int n0 = uni(i0_next);
+        ics_r = prefetch_ics(n0, i0);
+        i0_next = d > 2 ? ioff[d - 3] : 0;
+        c0_next = uni(a.ix.ics[n0]);
+        n0_next = n0;
+        if constexpr (!kLate) prefetch(c0_next, c0);
+      }
       if (group_wait(bar, (uint32_t)(NW * (D - d + 1)), seen, a.ctl, a.spin_limit, &s_flag)) {
         stop = true;
         break;
@@ -257,6 +281,7 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
         }
       }
       wait_vm<0>();
+      if (kLate && row0 == i0 && d > 1) prefetch(c0_next, c0);
       f32x4 sum[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
       // (KS = 2: the one chunk of an odd wave is an odd one)
       const float sgn = (KH & 1) && (wave & 1) ? -1.f : 1.f;
@@ -316,6 +341,10 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
       __syncthreads();
     }
     stamp(d, 3);
+    i1 = i0;
+    i0 = n0_next;
+    cend = c0;
+    c0 = c0_next;
   }
   // bias gradient of the group: the 16 threads of a unit in order
   __syncthreads();

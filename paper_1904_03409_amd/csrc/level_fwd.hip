@@ -173,9 +173,9 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_fwd(LevFwdArgs a) {
     if (a.clk && tid == 0 && d < T) a.clk[((size_t)blockIdx.x * T + d) * 4 + k] = wall_clock64();
   };
   int q0 = n_init, q1 = n_init + Bg;
-  int cend = uni(loff[2]);
+  int c0 = uni(loff[1]), cend = uni(loff[2]);               // children of the level: nodes [c0, cend)
   Pre pre;
-  prefetch(pre, q0, q1, uni(loff[1]), cend);
+  prefetch(pre, q0, q1, c0, cend);
   prefetch_c(pre, q0, q1);
   int hb = 0;                                               // buffer of hu_s and c_s
   for (int d = 0;; ++d) {
@@ -185,9 +185,7 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_fwd(LevFwdArgs a) {
     __syncthreads();                                        // the level's first rows landed
     stamp(d, 1);
     if (q0 + ROWS < q1) issue(q0 + ROWS, q1, 1);
-    // the next level
-    const int n0 = d < D ? uni(loff[d + 1]) : 0, n1 = d < D ? uni(loff[d + 2]) : 0;
-    const int nend = d < D ? uni(loff[min(d + 3, D + 2)]) : 0;
+    const int next_end = loff[min(d + 3, D + 2)];           // (in flight until the level is done)
     int buf = 0;
     for (int row0 = q0; row0 < q1; row0 += ROWS, buf ^= 1, hb ^= 1) {
       const int nr = min(ROWS, q1 - row0), kh = wave >> 2;
@@ -261,12 +259,12 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_fwd(LevFwdArgs a) {
     }
     stamp(d, 3);
     if (d >= D) break;
-    q0 = n0;
-    q1 = n1;
-    cend = nend;
     group_arrive(bar);
     const uint32_t seen = group_peek(bar);
-    prefetch(pre, q0, q1, q1, cend);                        // (a level's children begin where it ends)
+    q0 = c0;
+    q1 = c0 = cend;                                         // (levels follow each other)
+    cend = uni(next_end);
+    prefetch(pre, q0, q1, c0, cend);
     prefetch_c(pre, q0, q1);
     if (group_wait(bar, (uint32_t)(a.NW * (d + 1)), seen, a.ctl, a.spin_limit, &s_flag)) break;
   }

@@ -87,6 +87,7 @@ __global__ void __launch_bounds__(256) k_prep_fwd(PrepFwdArgs a) {
     if (S == 3) {
       const int unit = u0 + (tid & 7), gate = (tid >> 3) & 3;
       if (unit < H)
+#pragma unroll 8
         for (int k = tid >> 5; k < H; k += 8) m = fmaxf(m, fabsf(a.U[(size_t)k * 4 * H + (size_t)gate * H + unit]));
       s_max[tid] = m;
       __syncthreads();
@@ -152,33 +153,33 @@ template __global__ void k_prep_fwd<3>(PrepFwdArgs);
 
 // Backward operands: the U^T fragments (MFMA A operand) ub[w][wave][tile][chunk][plane][lane], a
 // lane's eight values U[unit 32 w + 16 tile + l16][column of gate column 32 (wave KS / 2 + chunk) +
-// 8 lq + j], in fp32 mode scaled per unit, odd chunks as mfma_rec takes them; and the check of the caller's top and
-// ops: a producer index outside [-1, t], or an op that is a push where the forward's was not (or
+// 8 lq + j], in fp32 mode scaled per unit, odd chunks as mfma_rec takes them; and the check of the caller's top and ops: a producer index outside [-1, t], or an op that is a push where the forward's was not (or
 // the reverse), raises CTL_BADIDX.
 template <int S>
 __global__ void __launch_bounds__(256) k_prep_bwd(PrepBwdArgs a) {
   constexpr int NP = S == 3 ? 2 : 1;
   const int H = a.H, H4 = 4 * H, tid = threadIdx.x, lane = tid & 63;
   if (blockIdx.x < (unsigned)a.n_u) {
-    const int w = blockIdx.x >> 1, tile = blockIdx.x & 1, u0 = 32 * w + 16 * tile, KH = a.KS / 2;
+    const int blk = blockIdx.x, wave = blk & 7, tile = (blk >> 3) & 1, w = blk >> 4, u0 = 32 * w + 16 * tile, KH = a.KS / 2;
     __shared__ float s_sc[16];
     if (S == 3) {
       const int unit = u0 + (tid >> 4);
       float m = 0.f;
       if (unit < H)
+#pragma unroll 8
         for (int n = tid & 15; n < H4; n += 16) m = fmaxf(m, fabsf(a.U[(size_t)unit * H4 + n]));
 #pragma unroll
       for (int d = 8; d; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, 16));
       if ((tid & 15) == 0) {
         const float sc = rec_scale(m);
         s_sc[tid >> 4] = sc;
-        a.uinv[unit] = 1.f / sc;
+        if (wave == 0) a.uinv[unit] = 1.f / sc;
       }
       __syncthreads();
     }
     const int unit = u0 + (lane & 15);
-    for (int f = tid; f < 8 * KH * 64; f += 256) {       // (wave, chunk, lane)
-      const int c = (f >> 6) % KH, wave = (f >> 6) / KH, kc = wave * KH + c;
+    for (int f = tid; f < KH * 64; f += 256) {           // (chunk, lane)
+      const int c = f >> 6, kc = wave * KH + c;
       const float sc = S == 3 ? s_sc[lane & 15] : 1.f;
       float v[8];
 #pragma unroll
@@ -195,11 +196,9 @@ __global__ void __launch_bounds__(256) k_prep_bwd(PrepBwdArgs a) {
     }
     return;
   }
-  const size_t f = (size_t)blockIdx.x * 256 + tid;
-  const size_t n = (size_t)a.T * a.B, step = (size_t)(gridDim.x - a.n_u) * 256;
-  const size_t P = a.ctl[CTL_NPUSHF];
+  const size_t P = a.ctl[CTL_NPUSHF], n = (size_t)a.T * a.B, step = (size_t)(gridDim.x - a.n_u) * 256;
   bool bad = false;
-  for (size_t i = f - (size_t)a.n_u * 256; i < n; i += step) {
+  for (size_t i = (size_t)(blockIdx.x - a.n_u) * 256 + tid; i < n; i += step) {
     const int s = a.top[i];
     bad |= s < -1 || s > (int)(i / a.B);
     bad |= (a.ops[a.order[i]] == 1) != (i < P);
