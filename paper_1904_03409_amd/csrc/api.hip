@@ -21,10 +21,7 @@ template <int S> __global__ void k_prep_fwd(PrepFwdArgs a);
 template <int S> __global__ void k_prep_bwd(PrepBwdArgs a);
 template <int V>
 __global__ void k_gsum(const float* d, const int32_t* gslot, int T, int B, int H, int G, float* out);
-__global__ void k_gather_top(const int32_t* top, const float* cellv, const float* init, float* out, int T, int B,
-                             int H, uint32_t* ctl);
-__global__ void k_gather_top4(const int32_t* top, const float* hcell, const float* h0, float* htop, const float* ccell,
-                              const float* c0, float* ctop, int T, int B, int H, uint32_t* ctl);
+template <int V> __global__ void k_gather_top(GatherArgs a);
 __global__ void k_fill_f32(float* p, size_t n, float v);
 __global__ void k_zero_ctl_bwd(uint32_t* ctl, int keep_errors);
 __global__ void k_zero_nonpush_rows(const int8_t* ops, float* out, size_t n, int cols);
@@ -383,16 +380,16 @@ int fwd_impl(const slstm_dims* d, const Plan& p, const Layout& L, bool keep, con
 
   // the leaves (pop and hold steps), then Algorithm 1's return values
   if ((rc = x_pass(NT_LEAF, !once))) return rc;
-  const size_t n = (size_t)N0 * H;
-  if (H % 4 == 0 && al16(h_cell) && al16(h0) && al16(h_top) && al16(c_cell) && al16(c0) && al16(c_top)) {
-    if (h_top || c_top)
-      hipLaunchKernelGGL(k_gather_top4, dim3(grid1d(n / 4)), dim3(256), 0, st, top, h_cell, h0, h_top, c_cell, c0, c_top,
-                         T, B, H, ctl);
-  } else {
-    if (h_top)
-      hipLaunchKernelGGL(k_gather_top, dim3(grid1d(n)), dim3(256), 0, st, top, h_cell, h0, h_top, T, B, H, ctl);
-    if (c_top)
-      hipLaunchKernelGGL(k_gather_top, dim3(grid1d(n)), dim3(256), 0, st, top, c_cell, c0, c_top, T, B, H, ctl);
+  if (h_top || c_top) {
+    GatherArgs a;
+    a.top = top; a.ctl = ctl; a.hcell = h_cell; a.h0 = h0; a.ccell = c_cell; a.c0 = c0;
+    a.htop = h_top; a.ctop = c_top; a.T = T; a.B = B; a.H = H;
+    const bool vec = H % 4 == 0 && al16(h_cell) && al16(h0) && al16(h_top) && al16(c_cell) && al16(c0) && al16(c_top);
+    for (a.ll = 2; a.ll < 6 && (1 << a.ll) < (vec ? H / 4 : H);) ++a.ll;
+    const int rows = 4 * 8 * (64 >> a.ll);             // of a workgroup
+    const dim3 grid(((size_t)N0 + rows - 1) / rows);
+    if (vec) hipLaunchKernelGGL(k_gather_top<4>, grid, dim3(256), 0, st, a);
+    else     hipLaunchKernelGGL(k_gather_top<1>, grid, dim3(256), 0, st, a);
   }
   if ((rc = hip_status(hipGetLastError()))) return rc;
   mark(d, 4, st);
@@ -407,8 +404,9 @@ bool fwd_args_ok(const slstm_dims* d, const float* x, const int8_t* ops, const f
 
 // Static work space of the allocation-free forward: one copy per GPU, held until the process
 // ends. Host code uses the device address that hipGetSymbolAddress returns for the current
-// device (kept per device), never the array's name.
-constexpr size_t kScratchBytes = (size_t)320 << 20;
+// device (kept per device), never the array's name. The largest need beside the planes of x among
+// the dims that static_measure admits is 370 MiB (3.7 M steps of one element at H = 1).
+constexpr size_t kScratchBytes = (size_t)448 << 20;
 __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 // Bytes that decide whether dims are served from the static work space: the work space of a
@@ -520,12 +518,13 @@ int stacklstm_bwd(const slstm_dims* d, const float* x, const int8_t* ops, const 
     a.n_u = p.NW * 16;
     a.U = U; a.ops = ops; a.top = top; a.order = ix.order; a.ub = (uint4*)(ws + L.ub);
     a.uinv = (float*)(ws + L.ubi); a.ctl = ctl;
+    const size_t segs = (T + 31) / 32;
     auto gsum = [&](const float* src, float* out) {
       if (H % 4 == 0 && al16(src))
-        hipLaunchKernelGGL(k_gsum<4>, dim3(((size_t)B * ((H + 255) / 256) + 3) / 4), dim3(256), 0, st, src, ix.gslot, T, B,
+        hipLaunchKernelGGL(k_gsum<4>, dim3((B * ((H + 255) / 256) * segs + 3) / 4), dim3(256), 0, st, src, ix.gslot, T, B,
                            H, p.G, out);
       else
-        hipLaunchKernelGGL(k_gsum<1>, dim3(((size_t)B * ((H + 63) / 64) + 3) / 4), dim3(256), 0, st, src, ix.gslot, T, B, H,
+        hipLaunchKernelGGL(k_gsum<1>, dim3((B * ((H + 63) / 64) * segs + 3) / 4), dim3(256), 0, st, src, ix.gslot, T, B, H,
                            p.G, out);
     };
     gsum(dh_top, gf);

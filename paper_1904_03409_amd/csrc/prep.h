@@ -4,6 +4,13 @@
 #include <stdint.h>
 #include <hip/hip_runtime.h>
 
+struct GatherArgs {
+  const int32_t* top; uint32_t* ctl;
+  const float *hcell, *h0, *ccell, *c0;
+  float *htop, *ctop;              // [T][B][H], null: not wanted
+  int T, B, H, ll;                 // 2^ll lanes per row
+};
+
 struct PrepFwdArgs {
   int I, Ip, H, Hs, H4s, B, G, N0, NW, KS;
   int n_w, n_u;                    // blocks of the W tiles and of the U fragments; the rest: initial states

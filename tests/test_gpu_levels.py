@@ -1,0 +1,78 @@
+"""The level-scheduled kernels at the sizes where they can go wrong: both sides of each compiled
+width, nodes with more children than one pass takes, levels of several passes, intervals that
+cross the 32-step pieces of the gradient sums and the 64-step pieces of the schedule, sequences
+whose walk arrays leave LDS, and an infinite input. Against the oracle, at the tolerances of
+the parity tests."""
+import numpy as np
+import pytest
+
+from paper_1904_03409_amd import workloads as wk
+from tests.gpu_helpers import TOL, compare, need_gpu, run_gpu
+from tests.torch_ref import normwise
+
+pytestmark = pytest.mark.gpu
+
+
+def _ops(kind, T, B):
+    rng = np.random.default_rng(T + B)
+    if kind == "alternate":          # T / 2 children of the initial state, all in one level
+        o = np.zeros((T, B), np.int8)
+        o[0::2] = 1
+        o[1::2] = -1
+        return o
+    if kind == "held":               # runs of holds from 1 to 100 steps between pushes and pops
+        o = np.zeros((T, B), np.int8)
+        for b in range(B):
+            t, depth = int(rng.integers(0, 70)), 0
+            while t < T:
+                o[t, b] = -1 if depth and rng.random() < 0.4 else 1
+                depth += int(o[t, b])
+                t += int(rng.integers(1, 100))
+        return o
+    if kind == "deep":               # one node per level
+        o = np.ones((T, B), np.int8)
+        o[(T + 1) // 2:] = -1
+        return o
+    return wk.ops_random_valid(rng, T, B)
+
+
+CASES = [
+    # (ops, T, B, I, H, precision)
+    ("random", 33, 5, 9, 32, 0), ("random", 33, 5, 9, 33, 0), ("random", 40, 9, 40, 65, 0),
+    ("random", 40, 9, 40, 129, 0), ("random", 40, 20, 33, 257, 0), ("random", 24, 20, 300, 511, 0),
+    ("random", 40, 20, 65, 257, 1), ("random", 24, 20, 129, 385, 1), ("random", 24, 20, 31, 513, 1),
+    ("random", 20, 20, 257, 769, 1), ("random", 20, 12, 8, 1023, 1),
+    ("alternate", 300, 3, 16, 40, 0), ("alternate", 300, 3, 16, 40, 1), ("alternate", 40, 300, 8, 512, 0),
+    ("alternate", 40, 300, 8, 516, 1),
+    ("held", 333, 7, 12, 36, 0), ("held", 333, 7, 12, 37, 1), ("held", 64, 7, 12, 36, 0), ("held", 97, 3, 4, 260, 0),
+    ("deep", 321, 2, 8, 24, 0), ("random", 20000, 1, 4, 8, 0),
+]
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_levels(oracle_mod, case):
+    need_gpu()
+    kind, T, B, I, H, precision = case
+    print(f"[gpu] {case}", flush=True)
+    wl = wk.custom(T=T, B=B, I=I, H=H, seed=T + H, ops=_ops(kind, T, B), wscale=0.3 if H < 300 else 0.1,
+                   random_state=True, dc_top=True)
+    gpu, _ = run_gpu(wl, precision=precision)
+    ref = oracle_mod.run(wl, bf16=precision == 1)
+    compare(wl, gpu, ref, precision, alg1=oracle_mod.alg1(wl, bf16=precision == 1))
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_infinite_input(oracle_mod, precision):
+    """An infinite input saturates gates; the states stay finite and other rows keep their values."""
+    need_gpu()
+    from paper_1904_03409_amd.stacklstm import DeviceRun
+    print(f"[gpu] infinite input prec={precision}", flush=True)
+    wl = wk.custom(T=24, B=4, I=40, H=48, seed=2, wscale=0.3)
+    wl.x[0, 0, 3] = np.inf
+    wl.x[5, 1, 39] = -np.inf
+    r = DeviceRun.from_workload(wl, precision=precision)
+    r.forward()
+    a1 = oracle_mod.alg1(wl, bf16=precision == 1)
+    for k in ("h_cell", "c_cell"):
+        got = getattr(r, k).cpu().numpy()
+        assert np.all(np.isfinite(a1[k])) and normwise(got, a1[k]) <= TOL[precision], k
