@@ -12,21 +12,16 @@
 #include "levels.h"
 #include "prep.h"
 
-__global__ void k_init_ctl(uint32_t* ctl, int keep_errors);
+__global__ void k_ctl(uint32_t* ctl, int keep_errors, int bwd);
 template <bool LDS> __global__ void k_plan(PlanArgs a);
 template <int S>
 __global__ void k_split_x(const float* x, const int32_t* order, int lo, int hi, int I, int Ip, int vec, bf16_t* out,
                           size_t plane);
 template <int S> __global__ void k_prep_fwd(PrepFwdArgs a);
-template <int S> __global__ void k_prep_bwd(PrepBwdArgs a);
-template <int V>
-__global__ void k_gsum(const float* d, const int32_t* gslot, int T, int B, int H, int G, float* out);
+template <int S, int V> __global__ void k_prep_bwd(PrepBwdArgs a);
 template <int V> __global__ void k_gather_top(GatherArgs a);
 __global__ void k_fill_f32(float* p, size_t n, float v);
-__global__ void k_zero_ctl_bwd(uint32_t* ctl, int keep_errors);
-__global__ void k_zero_nonpush_rows(const int8_t* ops, float* out, size_t n, int cols);
-__global__ void k_reduce_grads(const float* part, int splits, size_t stride, const float* db_part, int groups, int I,
-                               int H, float* dW, float* dU, float* db);
+__global__ void k_reduce_grads(ReduceArgs a);
 
 namespace {
 
@@ -290,10 +285,33 @@ int fwd_impl(const slstm_dims* d, const Plan& p, const Layout& L, bool keep, con
   const int T = d->T, B = d->B, I = d->I, H = d->H, S = p.S, N0 = T * B;
   const LevIdx ix = idx_of(ws, L);
 
+  // control words; operand planes of W, U and the initial states
+  mark(d, 0, st);
+  float* hu = (float*)(ws + L.hu);
+  uint16_t* hq = (uint16_t*)(ws + L.hq);
+  uint16_t* h3 = keep && S == 3 ? (uint16_t*)(ws + L.h3) : nullptr;
+  float* cn = (float*)(ws + L.cn);
+  uint16_t* xs = (uint16_t*)(ws + L.xs);
+  const size_t hplane = (size_t)(N0 + B) * L.Hs;
+  if (T == 0) {
+    hipLaunchKernelGGL(k_ctl, dim3(1), dim3(256), 0, st, ctl, d->defer_status ? 1 : 0, 0);
+  } else {
+    PrepFwdArgs a;
+    a.I = I; a.Ip = L.Ip; a.H = H; a.Hs = L.Hs; a.H4s = keep ? L.H4s : 0; a.B = B; a.G = p.G; a.N0 = N0; a.NW = p.NW;
+    a.KS = p.KS;
+    a.n_w = ((I + 31) / 32) * ((H + 31) / 32);
+    a.n_u = p.NW * 4;
+    a.W = W; a.U = U; a.h0 = h0; a.c0 = c0;
+    a.wt = (uint16_t*)(ws + L.wt); a.wp = (uint16_t*)(ws + L.wp); a.uf = (uint4*)(ws + L.uf);
+    a.uinv = (float*)(ws + L.ufi); a.rinit = (float*)(ws + L.rin);
+    a.hq = hq; a.hplane = hplane; a.h3 = h3; a.cn = cn;
+    a.ctl = ctl; a.keep_errors = d->defer_status ? 1 : 0;
+    const int grid = a.n_w + a.n_u + (B + 3) / 4;
+    if (S == 3) hipLaunchKernelGGL(k_prep_fwd<3>, dim3(grid), dim3(256), 0, st, a);
+    else        hipLaunchKernelGGL(k_prep_fwd<1>, dim3(grid), dim3(256), 0, st, a);
+  }
   // op validation, pointer scan, producer trace and level schedule. One workgroup per group; as
   // many waves as have walk arrays in LDS (at most one per element of the group)
-  mark(d, 0, st);
-  hipLaunchKernelGGL(k_init_ctl, dim3(1), dim3(256), 0, st, ctl, d->defer_status ? 1 : 0);
   {
     PlanArgs a;
     a.T = T; a.B = B; a.G = p.G; a.cap = L.cap;
@@ -313,27 +331,7 @@ int fwd_impl(const slstm_dims* d, const Plan& p, const Layout& L, bool keep, con
   mark(d, 1, st);
   if (T == 0) return call_status(d, ctl, st);
 
-  // operand planes of W, U, the initial states and x; x W + b of the push nodes
-  float* hu = (float*)(ws + L.hu);
-  uint16_t* hq = (uint16_t*)(ws + L.hq);
-  uint16_t* h3 = keep && S == 3 ? (uint16_t*)(ws + L.h3) : nullptr;
-  float* cn = (float*)(ws + L.cn);
-  uint16_t* xs = (uint16_t*)(ws + L.xs);
-  const size_t hplane = (size_t)(N0 + B) * L.Hs;
-  {
-    PrepFwdArgs a;
-    a.I = I; a.Ip = L.Ip; a.H = H; a.Hs = L.Hs; a.H4s = keep ? L.H4s : 0; a.B = B; a.G = p.G; a.N0 = N0; a.NW = p.NW;
-    a.KS = p.KS;
-    a.n_w = ((I + 31) / 32) * ((H + 31) / 32);
-    a.n_u = p.NW * 4;
-    a.W = W; a.U = U; a.h0 = h0; a.c0 = c0;
-    a.wt = (uint16_t*)(ws + L.wt); a.wp = (uint16_t*)(ws + L.wp); a.uf = (uint4*)(ws + L.uf);
-    a.uinv = (float*)(ws + L.ufi); a.rinit = (float*)(ws + L.rin);
-    a.hq = hq; a.hplane = hplane; a.h3 = h3; a.cn = cn;
-    const int grid = a.n_w + a.n_u + (B + 3) / 4;
-    if (S == 3) hipLaunchKernelGGL(k_prep_fwd<3>, dim3(grid), dim3(256), 0, st, a);
-    else        hipLaunchKernelGGL(k_prep_fwd<1>, dim3(grid), dim3(256), 0, st, a);
-  }
+  // planes of x, x W + b of the push nodes
   NtArgs g;
   memset(&g, 0, sizeof(g));
   g.N = 4 * H; g.K = L.Ip; g.N0 = N0;
@@ -495,9 +493,9 @@ int stacklstm_bwd(const slstm_dims* d, const float* x, const int8_t* ops, const 
   char* ws = (char*)workspace;
   uint32_t* ctl = (uint32_t*)(ws + L.ctl);
   const int T = d->T, B = d->B, I = d->I, H = d->H;
-  // the backward's control words (slot and barrier counters, wait and index flags) start at 0
-  hipLaunchKernelGGL(k_zero_ctl_bwd, dim3(1), dim3(256), 0, st, ctl, d->defer_status ? 1 : 0);
+  const int keep_errors = d->defer_status ? 1 : 0;
   if (T == 0) {
+    hipLaunchKernelGGL(k_ctl, dim3(1), dim3(256), 0, st, ctl, keep_errors, 1);
     hipLaunchKernelGGL(k_fill_f32, dim3(grid1d((size_t)I * 4 * H)), dim3(256), 0, st, dW, (size_t)I * 4 * H, 0.f);
     hipLaunchKernelGGL(k_fill_f32, dim3(grid1d((size_t)H * 4 * H)), dim3(256), 0, st, dU, (size_t)H * 4 * H, 0.f);
     hipLaunchKernelGGL(k_fill_f32, dim3(grid1d((size_t)4 * H)), dim3(256), 0, st, db, (size_t)4 * H, 0.f);
@@ -509,29 +507,26 @@ int stacklstm_bwd(const slstm_dims* d, const float* x, const int8_t* ops, const 
 
   const int S = p.S, N0 = T * B;
   const LevIdx ix = idx_of(ws, L);
-  // U^T fragments and the check of top and ops; interval sums of the upstream gradients
+  // control words, U^T fragments, interval sums of the upstream gradients
   float* gf = (float*)(ws + L.gf);
   float* gc = dc_top ? (float*)(ws + L.gc) : nullptr;
   {
     PrepBwdArgs a;
-    a.T = T; a.B = B; a.H = H; a.NW = p.NW; a.KS = p.KS;
-    a.n_u = p.NW * 16;
-    a.U = U; a.ops = ops; a.top = top; a.order = ix.order; a.ub = (uint4*)(ws + L.ub);
-    a.uinv = (float*)(ws + L.ubi); a.ctl = ctl;
-    const size_t segs = (T + 31) / 32;
-    auto gsum = [&](const float* src, float* out) {
-      if (H % 4 == 0 && al16(src))
-        hipLaunchKernelGGL(k_gsum<4>, dim3((B * ((H + 255) / 256) * segs + 3) / 4), dim3(256), 0, st, src, ix.gslot, T, B,
-                           H, p.G, out);
-      else
-        hipLaunchKernelGGL(k_gsum<1>, dim3((B * ((H + 63) / 64) * segs + 3) / 4), dim3(256), 0, st, src, ix.gslot, T, B, H,
-                           p.G, out);
+    a.T = T; a.B = B; a.H = H; a.G = p.G; a.NW = p.NW; a.KS = p.KS;
+    a.U = U; a.ub = (uint4*)(ws + L.ub); a.uinv = (float*)(ws + L.ubi);
+    a.gslot = ix.gslot; a.keep_errors = keep_errors;
+    auto prep = [&](int n_u, const float* src, float* sums, uint32_t* zero) {
+      a.n_u = n_u; a.d = src; a.sums = sums; a.ctl = zero;
+      const bool vec = H % 4 == 0 && al16(src);
+      const size_t parts = (H + (vec ? 255 : 63)) / (vec ? 256 : 64), segs = (T + 31) / 32;
+      const dim3 grid(n_u + (B * parts * segs + 3) / 4);
+      if (S == 3 && vec)  hipLaunchKernelGGL((k_prep_bwd<3, 4>), grid, dim3(256), 0, st, a);
+      else if (S == 3)    hipLaunchKernelGGL((k_prep_bwd<3, 1>), grid, dim3(256), 0, st, a);
+      else if (vec)       hipLaunchKernelGGL((k_prep_bwd<1, 4>), grid, dim3(256), 0, st, a);
+      else                hipLaunchKernelGGL((k_prep_bwd<1, 1>), grid, dim3(256), 0, st, a);
     };
-    gsum(dh_top, gf);
-    if (gc) gsum(dc_top, gc);
-    const int grid = a.n_u + (int)std::min<size_t>(((size_t)N0 + 1023) / 1024, 1024);
-    if (S == 3) hipLaunchKernelGGL(k_prep_bwd<3>, dim3(grid), dim3(256), 0, st, a);
-    else        hipLaunchKernelGGL(k_prep_bwd<1>, dim3(grid), dim3(256), 0, st, a);
+    prep(p.NW * 16, dh_top, gf, ctl);
+    if (gc) prep(0, dc_top, gc, nullptr);
   }
   uint16_t* dap = (uint16_t*)(ws + L.dap);
   const size_t dplane = (size_t)N0 * L.H4s;
@@ -563,12 +558,17 @@ int stacklstm_bwd(const slstm_dims* d, const float* x, const int8_t* ops, const 
     g.D = dap; g.dplane = dplane; g.ldd = L.H4s;
     g.opar = ix.opar; g.ctl = ctl; g.part = part; g.split_stride = (size_t)(I + H) * 4 * H;
     if ((rc = hip_status(launch_tn(g, S, st)))) return rc;
-    hipLaunchKernelGGL(k_reduce_grads, dim3(grid1d((size_t)(I + H + 1) * H)), dim3(256), 0, st, part, g.splits,
-                       g.split_stride, dbp, p.G, I, H, dW, dU, db);
+    ReduceArgs r;
+    r.part = part; r.splits = g.splits; r.stride = g.split_stride; r.db_part = dbp; r.groups = p.G; r.I = I; r.H = H;
+    r.dW = dW; r.dU = dU; r.db = db;
+    r.T = T; r.B = B; r.n_red = grid1d((size_t)(I + H + 1) * H);
+    r.ops = ops; r.top = top; r.order = ix.order; r.ctl = ctl;
+    const int checks = (int)std::min<size_t>(((size_t)N0 + 1023) / 1024, 1024);
+    hipLaunchKernelGGL(k_reduce_grads, dim3(r.n_red + checks), dim3(256), 0, st, r);
   }
   mark(d, 7, st);
   mark(d, 8, st);
-  // dx = dA W^T on the push steps, 0 on the others
+  // dx = dA W^T on the push steps, 0 on the others (in the same launch)
   {
     NtArgs g;
     memset(&g, 0, sizeof(g));
@@ -578,7 +578,6 @@ int stacklstm_bwd(const slstm_dims* d, const float* x, const int8_t* ops, const 
     g.ctl = ctl; g.C = dx; g.ldc = I; g.order = ix.order; g.H = H;
     if ((rc = hip_status(launch_nt(g, S, NT_DX, st)))) return rc;
   }
-  hipLaunchKernelGGL(k_zero_nonpush_rows, dim3(grid1d((size_t)N0 * I / 4 + 1)), dim3(256), 0, st, ops, dx, (size_t)N0, I);
   if ((rc = hip_status(hipGetLastError()))) return rc;
   mark(d, 9, st);
   return call_status(d, ctl, st);

@@ -34,6 +34,32 @@ enum {
 };
 #define MAX_GROUPS 128
 
+// Control words of a forward call at 0 (status: no error), by one workgroup. With keep_errors (a
+// deferred call) the error words keep what earlier calls on the work space set: the lowest failing
+// element's op status, the time-out and the index flag.
+__device__ __forceinline__ void init_ctl(uint32_t* ctl, int keep_errors) {
+  for (int i = threadIdx.x; i < CTL_WORDS; i += blockDim.x) {
+    const bool err = i == CTL_STATUS || i == CTL_TIMEOUT || i == CTL_BADIDX;
+    if (keep_errors && err) continue;
+    ctl[i] = (i == CTL_STATUS) ? kStatusOk : 0u;
+  }
+}
+// Clears the backward's control words, by one workgroup: slot counters, group barrier counters, the
+// wait flags and the index flag (the op status of the forward goes: the backward reports only its
+// own). keep_errors: a deferred call; the error words stay as earlier calls left them.
+__device__ __forceinline__ void zero_ctl_bwd(uint32_t* ctl, int keep_errors) {
+  for (int i = threadIdx.x; i < 16; i += blockDim.x) ctl[CTL_XCC_SLOT_B + i] = 0u;
+  for (int i = threadIdx.x; i < 16 * MAX_GROUPS; i += blockDim.x) ctl[CTL_BAR_B + i] = 0u;
+  if (threadIdx.x == 0) {
+    ctl[CTL_ABORT] = 0u;
+    if (!keep_errors) {
+      ctl[CTL_STATUS] = kStatusOk;
+      ctl[CTL_TIMEOUT] = 0u;
+      ctl[CTL_BADIDX] = 0u;
+    }
+  }
+}
+
 // Gate-interleaved ("permuted") column order used inside the library: column 4*u + k
 // holds gate k (0=i, 1=f, 2=g, 3=o) of hidden unit u. The caller's order is k*H + u.
 __device__ __forceinline__ int perm_to_orig(int np, int H) { return (np & 3) * H + (np >> 2); }

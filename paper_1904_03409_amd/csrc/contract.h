@@ -13,7 +13,7 @@ struct NtArgs {
   const uint16_t* A; size_t aplane; int lda;
   const uint16_t* B; size_t bplane; int ldb;
   const uint32_t* ctl;               // CTL_NPUSHF
-  // NT_XW: C[i][N] + bias; NT_DX: C[order[i]][N]
+  // NT_XW: C[i][N] + bias; NT_DX: C[order[i]][N], and 0 in the rows of the leaves
   float* C; int ldc;
   const float* bias; int H;          // caller's column order
   const int32_t* order;
@@ -40,4 +40,15 @@ constexpr int nt_bk(int S) { return S == 3 ? 32 : 64; }
 constexpr size_t nt_lds(int S) { return (size_t)2 * S * (nt_bm(S) + nt_bn(S)) * nt_bk(S) * 2; }
 
 hipError_t launch_nt(const NtArgs& g, int S, int epi, hipStream_t st);
+// dW, dU and db from the partials, and the check of the caller's top and ops (contract.hip)
+struct ReduceArgs {
+  const float* part; int splits; size_t stride;
+  const float* db_part; int groups;
+  int I, H;
+  float* dW; float* dU; float* db;
+  int T, B, n_red;                   // n_red: blocks of the sums; the rest check
+  const int8_t* ops; const int32_t* top; const int32_t* order;
+  uint32_t* ctl;
+};
+
 hipError_t launch_tn(const TnArgs& g, int S, hipStream_t st);

@@ -52,10 +52,24 @@ __global__ void __launch_bounds__(512, 2) k_nt(NtArgs g) {
   // go to the 8 XCDs in turn) takes a contiguous run, in groups of 4 row tiles per column tile
   const int P = (int)g.ctl[CTL_NPUSHF];
   const int r_lo = g.leaves ? max(g.lo, P) : g.lo, r_hi = g.leaves ? g.hi : min(g.hi, P);
-  if (r_lo >= r_hi) return;
-  const int NTL = (g.N + BN - 1) / BN, MTL = (r_hi - r_lo + BM - 1) / BM, active = NTL * MTL;
+  const int NTL = (g.N + BN - 1) / BN, MTL = (max(r_hi - r_lo, 0) + BM - 1) / BM, active = NTL * MTL;
   int lid = (int)blockIdx.x;
-  if (lid >= active) return;
+  if (lid >= active) {
+    // dx is exactly 0 on the leaves: the blocks without a tile clear those rows, 16 lanes a row
+    // (behind the products, where the last tiles leave CUs idle)
+    if constexpr (EPI == NT_DX) {
+      const int per = ((int)gridDim.x - active) * 32;
+      const bool vec = (g.N & 3) == 0 && (((uintptr_t)g.C) & 15u) == 0;
+      for (int i = P + (lid - active) * 32 + (int)(threadIdx.x >> 4); i < g.N0; i += per) {
+        float* dst = g.C + (size_t)g.order[i] * g.ldc;
+        if (vec)
+          for (int n = 4 * (threadIdx.x & 15); n < g.N; n += 64) *(f32x4*)(dst + n) = f32x4{0.f, 0.f, 0.f, 0.f};
+        else
+          for (int n = threadIdx.x & 15; n < g.N; n += 16) dst[n] = 0.f;
+      }
+    }
+    return;
+  }
   {
     const int full = active & ~7;
     if (lid < full) lid = (lid & 7) * (full >> 3) + (lid >> 3);
@@ -402,23 +416,33 @@ __global__ void __launch_bounds__(512, 2) k_tn(TnArgs g) {
 }
 
 // dW [I][4H], dU [H][4H] and db [4H] in the caller's column order: the partials of k_tn, and of the
-// groups for db, added in order.
-__global__ void __launch_bounds__(256) k_reduce_grads(const float* __restrict__ part, int splits, size_t stride,
-                                                      const float* __restrict__ db_part, int groups, int I, int H,
-                                                      float* __restrict__ dW, float* __restrict__ dU,
-                                                      float* __restrict__ db) {
-  const int H4 = 4 * H;
+// groups for db, added in order. The blocks past n_red check the caller's top and ops: a producer
+// index outside [-1, t], or an op that is a push where the forward's was not (or the reverse),
+// raises CTL_BADIDX (no kernel of the backward takes an address from either).
+__global__ void __launch_bounds__(256) k_reduce_grads(ReduceArgs a) {
+  const int H = a.H, H4 = 4 * H, I = a.I;
+  if ((int)blockIdx.x >= a.n_red) {
+    const size_t P = a.ctl[CTL_NPUSHF], n = (size_t)a.T * a.B, step = (size_t)(gridDim.x - a.n_red) * 256;
+    bool bad = false;
+    for (size_t i = (size_t)(blockIdx.x - a.n_red) * 256 + threadIdx.x; i < n; i += step) {
+      const int s = a.top[i];
+      bad |= s < -1 || s > (int)(i / a.B);
+      bad |= (a.ops[a.order[i]] == 1) != (i < P);
+    }
+    if (bad) raise_badidx(a.ctl);
+    return;
+  }
   const size_t n_w = (size_t)I * H, n = n_w + (size_t)H * H + H;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+  for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)a.n_red * 256) {
     const size_t row = i / H;
     const int u = (int)(i - row * H);
     const bool bias = row == (size_t)(I + H);
-    const float* src = bias ? db_part : part + row * H4;
-    const size_t st = bias ? (size_t)H4 : stride;
-    const int cnt = bias ? groups : splits;
+    const float* src = bias ? a.db_part : a.part + row * H4;
+    const size_t st = bias ? (size_t)H4 : a.stride;
+    const int cnt = bias ? a.groups : a.splits;
     f32x4 s = {0.f, 0.f, 0.f, 0.f};
     for (int z = 0; z < cnt; ++z) s += *(const f32x4*)(src + (size_t)z * st + 4 * u);
-    float* dst = bias ? db : (row < (size_t)I ? dW + row * H4 : dU + (row - I) * H4);
+    float* dst = bias ? a.db : (row < (size_t)I ? a.dW + row * H4 : a.dU + (row - I) * H4);
 #pragma unroll
     for (int k = 0; k < 4; ++k) dst[(size_t)k * H + u] = s[k];
   }
@@ -430,8 +454,9 @@ static hipError_t launch_nt_t(const NtArgs& g, hipStream_t st) {
   constexpr int shm = (int)nt_lds(S);
   const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, shm);
   if (e != hipSuccess) return e;
-  // the grid covers the static range; blocks past the rows in use leave at once
-  const int tiles = ((g.N + nt_bn(S) - 1) / nt_bn(S)) * ((g.hi - g.lo + nt_bm(S) - 1) / nt_bm(S));
+  // the grid covers the static range; blocks past the rows in use leave at once (NT_DX: clear the
+  // leaves' rows; one row tile more, so that some block does where the push nodes fill every tile)
+  const int tiles = ((g.N + nt_bn(S) - 1) / nt_bn(S)) * ((g.hi - g.lo + nt_bm(S) - 1) / nt_bm(S) + (EPI == NT_DX ? 1 : 0));
   hipLaunchKernelGGL(kern, dim3(tiles), dim3(512), shm, st, g);
   return hipGetLastError();
 }

@@ -22,11 +22,14 @@ struct PrepFwdArgs {
   uint16_t* h3;                    // fp32 mode with a backward: [3][N0 + B][Hs], else null
   float* rinit;
   float* cn;
+  uint32_t* ctl; int keep_errors;
 };
 
 struct PrepBwdArgs {
-  int T, B, H, NW, KS, n_u;
-  const float* U; const int8_t* ops; const int32_t* top; const int32_t* order;
+  int T, B, H, G, NW, KS;
+  int n_u;                         // blocks of the U^T fragments; the rest: interval sums
+  const float* U;
   uint4* ub; float* uinv;
-  uint32_t* ctl;
+  const float* d; const int32_t* gslot; float* sums;   // upstream gradient, its slots, the sums
+  uint32_t* ctl; int keep_errors;  // control words to clear (null: not by this launch)
 };

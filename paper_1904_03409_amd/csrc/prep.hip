@@ -41,11 +41,13 @@ template __global__ void k_split_x<3>(const float*, const int32_t*, int, int, in
 //    U[32 (half KS / 2 + chunk) + 8 lq + j][column of (unit 32 w + 8 pair + 4 tile + l16 / 4, gate
 //    l16 % 4)]; fp32 mode: scaled per unit, odd chunks as mfma_rec takes them (split.h);
 //  * the initial states as nodes (planes of h0 and a copy of c0), one wave per element.
+// The first block also sets up the control words.
 template <int S>
 __global__ void __launch_bounds__(256) k_prep_fwd(PrepFwdArgs a) {
   __shared__ float tile[32][129];
   const int tid = threadIdx.x, H = a.H, I = a.I;
   int blk = blockIdx.x;
+  if (blk == 0) init_ctl(a.ctl, a.keep_errors);
   if (blk < a.n_w) {
     const int ut = (H + 31) / 32, i0 = (blk / ut) * 32, u0 = (blk % ut) * 32;
     for (int e = tid; e < 32 * 128; e += 256) {
@@ -151,63 +153,6 @@ __global__ void __launch_bounds__(256) k_prep_fwd(PrepFwdArgs a) {
 template __global__ void k_prep_fwd<1>(PrepFwdArgs);
 template __global__ void k_prep_fwd<3>(PrepFwdArgs);
 
-// Backward operands: the U^T fragments (MFMA A operand) ub[w][wave][tile][chunk][plane][lane], a
-// lane's eight values U[unit 32 w + 16 tile + l16][column of gate column 32 (wave KS / 2 + chunk) +
-// 8 lq + j], in fp32 mode scaled per unit, odd chunks as mfma_rec takes them; and the check of the caller's top and ops: a producer index outside [-1, t], or an op that is a push where the forward's was not (or
-// the reverse), raises CTL_BADIDX.
-template <int S>
-__global__ void __launch_bounds__(256) k_prep_bwd(PrepBwdArgs a) {
-  constexpr int NP = S == 3 ? 2 : 1;
-  const int H = a.H, H4 = 4 * H, tid = threadIdx.x, lane = tid & 63;
-  if (blockIdx.x < (unsigned)a.n_u) {
-    const int blk = blockIdx.x, wave = blk & 7, tile = (blk >> 3) & 1, w = blk >> 4, u0 = 32 * w + 16 * tile, KH = a.KS / 2;
-    __shared__ float s_sc[16];
-    if (S == 3) {
-      const int unit = u0 + (tid >> 4);
-      float m = 0.f;
-      if (unit < H)
-#pragma unroll 8
-        for (int n = tid & 15; n < H4; n += 16) m = fmaxf(m, fabsf(a.U[(size_t)unit * H4 + n]));
-#pragma unroll
-      for (int d = 8; d; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, 16));
-      if ((tid & 15) == 0) {
-        const float sc = rec_scale(m);
-        s_sc[tid >> 4] = sc;
-        if (wave == 0) a.uinv[unit] = 1.f / sc;
-      }
-      __syncthreads();
-    }
-    const int unit = u0 + (lane & 15);
-    for (int f = tid; f < KH * 64; f += 256) {           // (chunk, lane)
-      const int c = f >> 6, kc = wave * KH + c;
-      const float sc = S == 3 ? s_sc[lane & 15] : 1.f;
-      float v[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int np = 32 * kc + 8 * (lane >> 4) + j;
-        v[j] = (unit < H && np < H4) ? a.U[(size_t)unit * H4 + perm_to_orig(np, H)] : 0.f;
-      }
-      uint4 g[NP];
-      split_rec_granule<NP>(v, sc, g);
-      if (S == 3 && (kc & 1)) g[0] = rec_negated(g[0]);
-#pragma unroll
-      for (int s = 0; s < NP; ++s)
-        a.ub[((((size_t)(w * 8 + wave) * 2 + tile) * KH + c) * NP + s) * 64 + lane] = g[s];
-    }
-    return;
-  }
-  const size_t P = a.ctl[CTL_NPUSHF], n = (size_t)a.T * a.B, step = (size_t)(gridDim.x - a.n_u) * 256;
-  bool bad = false;
-  for (size_t i = (size_t)(blockIdx.x - a.n_u) * 256 + tid; i < n; i += step) {
-    const int s = a.top[i];
-    bad |= s < -1 || s > (int)(i / a.B);
-    bad |= (a.ops[a.order[i]] == 1) != (i < P);
-  }
-  if (bad) raise_badidx(a.ctl);
-}
-template __global__ void k_prep_bwd<1>(PrepBwdArgs);
-template __global__ void k_prep_bwd<3>(PrepBwdArgs);
-
 // Sums of an upstream gradient [T][B][H] over the intervals of steps during which one state stays
 // on top: G[gslot][:] (slots: a push node's first interval; N0 + B + the popped node for the
 // interval of its parent that follows; an initial state's first interval). An interval is a run
@@ -216,12 +161,12 @@ template __global__ void k_prep_bwd<3>(PrepBwdArgs);
 // written once, with no atomics, in the order of the steps. (One wave for all steps of an element
 // left the chip without enough loads in flight: 328 us for 1024 steps of 128 elements at H = 512.)
 template <int V>
-__global__ void __launch_bounds__(256) k_gsum(const float* __restrict__ d, const int32_t* __restrict__ gslot, int T, int B,
-                                              int H, int G, float* __restrict__ out) {
+__device__ __forceinline__ void interval_sums(int blk, const float* __restrict__ d, const int32_t* __restrict__ gslot, int T,
+                                              int B, int H, int G, float* __restrict__ out) {
   constexpr int UN = 16;
   typedef float fv __attribute__((ext_vector_type(V)));
   const int lane = threadIdx.x & 63, parts = (H + 64 * V - 1) / (64 * V);
-  const int wv = uni((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
+  const int wv = uni(blk * 4 + (int)(threadIdx.x >> 6));
   const int seg = wv / (B * parts), bp = wv - seg * (B * parts);
   if (seg * 32 >= T) return;
   const int b = bp / parts, u = (bp - b * parts) * 64 * V + lane * V;
@@ -270,5 +215,58 @@ __global__ void __launch_bounds__(256) k_gsum(const float* __restrict__ d, const
   }
   if (on) *(fv*)(out + (size_t)cur * H + u) = acc;
 }
-template __global__ void k_gsum<1>(const float*, const int32_t*, int, int, int, int, float*);
-template __global__ void k_gsum<4>(const float*, const int32_t*, int, int, int, int, float*);
+
+// Backward operands, by block range: the interval sums of an upstream gradient (interval_sums), and
+// the U^T fragments (MFMA A operand) ub[w][wave][tile][chunk][plane][lane], a
+// lane's eight values U[unit 32 w + 16 tile + l16][column of gate column 32 (wave KS / 2 + chunk) +
+// 8 lq + j], in fp32 mode scaled per unit, odd chunks as mfma_rec takes them.
+// One launch: the fragments' blocks are few and wait on their loads. The first block also clears
+// the control words.
+template <int S, int V>
+__global__ void __launch_bounds__(256) k_prep_bwd(PrepBwdArgs a) {
+  constexpr int NP = S == 3 ? 2 : 1;
+  const int H = a.H, H4 = 4 * H, tid = threadIdx.x, lane = tid & 63;
+  if (blockIdx.x == 0 && a.ctl) zero_ctl_bwd(a.ctl, a.keep_errors);
+  if (blockIdx.x < (unsigned)a.n_u) {
+    const int blk = blockIdx.x, wave = blk & 7, tile = (blk >> 3) & 1, w = blk >> 4, u0 = 32 * w + 16 * tile, KH = a.KS / 2;
+    __shared__ float s_sc[16];
+    if (S == 3) {
+      const int unit = u0 + (tid >> 4);
+      float m = 0.f;
+      if (unit < H)
+#pragma unroll 8
+        for (int n = tid & 15; n < H4; n += 16) m = fmaxf(m, fabsf(a.U[(size_t)unit * H4 + n]));
+#pragma unroll
+      for (int d = 8; d; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, 16));
+      if ((tid & 15) == 0) {
+        const float sc = rec_scale(m);
+        s_sc[tid >> 4] = sc;
+        if (wave == 0) a.uinv[unit] = 1.f / sc;
+      }
+      __syncthreads();
+    }
+    const int unit = u0 + (lane & 15);
+    for (int f = tid; f < KH * 64; f += 256) {           // (chunk, lane)
+      const int c = f >> 6, kc = wave * KH + c;
+      const float sc = S == 3 ? s_sc[lane & 15] : 1.f;
+      float v[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int np = 32 * kc + 8 * (lane >> 4) + j;
+        v[j] = (unit < H && np < H4) ? a.U[(size_t)unit * H4 + perm_to_orig(np, H)] : 0.f;
+      }
+      uint4 g[NP];
+      split_rec_granule<NP>(v, sc, g);
+      if (S == 3 && (kc & 1)) g[0] = rec_negated(g[0]);
+#pragma unroll
+      for (int s = 0; s < NP; ++s)
+        a.ub[((((size_t)(w * 8 + wave) * 2 + tile) * KH + c) * NP + s) * 64 + lane] = g[s];
+    }
+    return;
+  }
+  interval_sums<V>((int)blockIdx.x - a.n_u, a.d, a.gslot, a.T, a.B, H, a.G, a.sums);
+}
+template __global__ void k_prep_bwd<1, 1>(PrepBwdArgs);
+template __global__ void k_prep_bwd<1, 4>(PrepBwdArgs);
+template __global__ void k_prep_bwd<3, 1>(PrepBwdArgs);
+template __global__ void k_prep_bwd<3, 4>(PrepBwdArgs);

@@ -1,17 +1,12 @@
 // Small bandwidth-bound kernels around the contractions: control words, the returned states,
-// zero fills.
+// fills.
 #include "common.h"
 #include "prep.h"
 
-// Control words of a forward call at 0 (status: no error). With keep_errors (a deferred
-// call) the error words keep what earlier calls on the work space set: the lowest failing
-// element's op status, the time-out and the index flag.
-__global__ void __launch_bounds__(256) k_init_ctl(uint32_t* ctl, int keep_errors) {
-  for (int i = threadIdx.x; i < CTL_WORDS; i += blockDim.x) {
-    const bool err = i == CTL_STATUS || i == CTL_TIMEOUT || i == CTL_BADIDX;
-    if (keep_errors && err) continue;
-    ctl[i] = (i == CTL_STATUS) ? kStatusOk : 0u;
-  }
+// Control words of a call without steps (the others: k_prep_fwd, k_prep_bwd).
+__global__ void __launch_bounds__(256) k_ctl(uint32_t* ctl, int keep_errors, int bwd) {
+  if (bwd) zero_ctl_bwd(ctl, keep_errors);
+  else init_ctl(ctl, keep_errors);
 }
 
 // h_top and c_top (either may be null): row (t, b) is a copy of the row of the state on top after
@@ -59,35 +54,4 @@ template __global__ void k_gather_top<4>(GatherArgs);
 
 __global__ void __launch_bounds__(256) k_fill_f32(float* __restrict__ p, size_t n, float v) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = v;
-}
-
-// Clears the backward's control words: slot counters, group barrier counters, the wait flags
-// and the index flag (the op status of the forward stays: the backward reports only its own).
-// (keep_errors: a deferred call; the error words stay as earlier calls left them)
-__global__ void __launch_bounds__(256) k_zero_ctl_bwd(uint32_t* __restrict__ ctl, int keep_errors) {
-  for (int i = threadIdx.x; i < 16; i += blockDim.x) ctl[CTL_XCC_SLOT_B + i] = 0u;
-  for (int i = threadIdx.x; i < 16 * MAX_GROUPS; i += blockDim.x) ctl[CTL_BAR_B + i] = 0u;
-  if (threadIdx.x == 0) {
-    ctl[CTL_ABORT] = 0u;
-    if (!keep_errors) {
-      ctl[CTL_STATUS] = kStatusOk;
-      ctl[CTL_TIMEOUT] = 0u;
-      ctl[CTL_BADIDX] = 0u;
-    }
-  }
-}
-
-// Zeroes the rows of out [n][cols] whose op is not a push (dx is exactly 0 there).
-__global__ void __launch_bounds__(256) k_zero_nonpush_rows(const int8_t* __restrict__ ops, float* __restrict__ out,
-                                                           size_t n, int cols) {
-  const size_t tid = (size_t)blockIdx.x * blockDim.x + threadIdx.x, nth = (size_t)gridDim.x * blockDim.x;
-  if ((cols & 3) == 0 && ((uintptr_t)out & 15) == 0) {
-    const int cv = cols >> 2;
-    const size_t nv = n * cv;
-    for (size_t i = tid; i < nv; i += nth)
-      if (ops[i / cv] != 1) ((float4*)out)[i] = float4{0.f, 0.f, 0.f, 0.f};
-    return;
-  }
-  for (size_t i = tid; i < n * cols; i += nth)
-    if (ops[i / cols] != 1) out[i] = 0.f;
 }
