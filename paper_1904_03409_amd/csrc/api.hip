@@ -94,7 +94,7 @@ int make_plan(const slstm_dims* d, Plan* p) {
 
 // Split K of dW | dU: one workgroup per CU, K slices of at least one 64-row step.
 int tn_tiles(const slstm_dims* d) {
-  const int S = planes_of(d), bm = nt_bm(S), bn = nt_bn(S);
+  const int S = planes_of(d), bm = nt_bm(S, nt_mi(S)), bn = nt_bn(S);
   return ((4 * d->H + bn - 1) / bn) * ((d->I + bm - 1) / bm + (d->H + bm - 1) / bm);
 }
 int tn_splits(const slstm_dims* d) {
@@ -552,7 +552,7 @@ int stacklstm_bwd(const slstm_dims* d, const float* x, const int8_t* ops, const 
   {
     TnArgs g;
     memset(&g, 0, sizeof(g));
-    g.I = I; g.H = H; g.H4 = 4 * H; g.splits = tn_splits(d); g.xt = (I + nt_bm(S) - 1) / nt_bm(S);
+    g.I = I; g.H = H; g.H4 = 4 * H; g.splits = tn_splits(d); g.xt = (I + nt_bm(S, nt_mi(S)) - 1) / nt_bm(S, nt_mi(S));
     g.X = (const uint16_t*)(ws + L.xs); g.xplane = (size_t)N0 * L.Ip; g.ldx = L.Ip;
     g.Hp = (const uint16_t*)(ws + (S == 3 ? L.h3 : L.hq)); g.hplane = (size_t)(N0 + B) * L.Hs; g.ldh = L.Hs; g.hrows = N0 + B;
     g.D = dap; g.dplane = dplane; g.ldd = L.H4s;

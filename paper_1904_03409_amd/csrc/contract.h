@@ -33,13 +33,14 @@ struct TnArgs {
   float* part; size_t split_stride;  // [splits][I + H][4H]
 };
 
-// Block tiles: rows x columns, K step
-constexpr int nt_bm(int S) { return 256; }
+// Block tiles: rows x columns, K step, by the row tiles of 16 per wave (MI: nt_mi, or in k_nt one to
+// three quarters of it; the smallest has room for K steps of 64 in fp32 mode too)
+constexpr int nt_mi(int S) { return S == 3 ? 4 : 8; }
+constexpr int nt_bm(int S, int MI) { return (S == 3 ? 64 : 32) * MI; }
 constexpr int nt_bn(int S) { return S == 3 ? 128 : 256; }
-constexpr int nt_bk(int S) { return S == 3 ? 32 : 64; }
-constexpr size_t nt_lds(int S) { return (size_t)2 * S * (nt_bm(S) + nt_bn(S)) * nt_bk(S) * 2; }
+constexpr int nt_bk(int S, int MI) { return S == 3 && MI > 1 ? 32 : 64; }
+constexpr size_t nt_lds(int S, int MI) { return (size_t)2 * S * (nt_bm(S, MI) + nt_bn(S)) * nt_bk(S, MI) * 2; }
 
-hipError_t launch_nt(const NtArgs& g, int S, int epi, hipStream_t st);
 // dW, dU and db from the partials, and the check of the caller's top and ops (contract.hip)
 struct ReduceArgs {
   const float* part; int splits; size_t stride;
@@ -51,4 +52,5 @@ struct ReduceArgs {
   uint32_t* ctl;
 };
 
+hipError_t launch_nt(const NtArgs& g, int S, int epi, hipStream_t st);
 hipError_t launch_tn(const TnArgs& g, int S, hipStream_t st);

@@ -5,9 +5,11 @@
 // into two LDS stages by LDS DMA, the next slice in flight behind the products of the current one.
 // A DMA writes one contiguous kilobyte per wave instruction, so each lane fetches the 16-byte
 // granule that a swizzled layout puts at its slot; fragment reads then spread over the banks.
-// S = 3: 256 x 128 block, 64 x 64 per wave, K steps of 32: six MFMAs per pair of three-plane
+// S = 3: 256 x 128 block (or fewer rows: k_nt), 64 x 64 per wave, K steps of 32: six MFMAs per pair of three-plane
 // fragments, bound by the matrix units. S = 1: 256 x 256 block, 128 x 64 per wave, K steps of 64
 // (a wave reads 12 KB of fragments per 32 MFMAs).
+#include <algorithm>
+
 #include "common.h"
 #include "contract.h"
 #include "split.h"
@@ -40,36 +42,18 @@ __device__ __forceinline__ float plane_sum(const uint16_t* p, size_t plane, size
 
 }  // namespace
 
-template <int S, int EPI>
-__global__ void __launch_bounds__(512, 2) k_nt(NtArgs g) {
-  constexpr int BM = nt_bm(S), BN = nt_bn(S), BK = nt_bk(S), GR = BK / 8;
-  constexpr int MI = S == 3 ? 4 : 8, NJ = 4, WN = BN / (16 * NJ);
+// One block tile of k_nt: 16 MI x (8 / WN) rows, K steps of BK.
+template <int S, int EPI, int MI>
+__device__ __forceinline__ void nt_tile(const NtArgs& g, int r_lo, int r_hi, int lid, unsigned char* sm) {
+  constexpr int BM = nt_bm(S, MI), BN = nt_bn(S), BK = nt_bk(S, MI), GR = BK / 8;
+  constexpr int NJ = 4, WN = BN / (16 * NJ);
   static_assert(BM == 16 * MI * (8 / WN), "eight waves cover the block tile");
+  static_assert(nt_lds(S, MI) <= nt_lds(S, nt_mi(S)) && BM * BN * 2 <= nt_lds(S, MI) && 8 * 16 * 68 * 4 <= nt_lds(S, MI), "LDS");
   constexpr int APL = BM * GR * 16, BPL = BN * GR * 16, STAGE = S * (APL + BPL);
-  constexpr int IA = BM * GR / 512, IB = BN * GR / 512;            // DMAs per wave, plane and slice
-  extern __shared__ __align__(16) unsigned char sm[];
-  // rows in use and this block's tile: the active tiles are dealt so that each XCD (workgroups
-  // go to the 8 XCDs in turn) takes a contiguous run, in groups of 4 row tiles per column tile
-  const int P = (int)g.ctl[CTL_NPUSHF];
-  const int r_lo = g.leaves ? max(g.lo, P) : g.lo, r_hi = g.leaves ? g.hi : min(g.hi, P);
-  const int NTL = (g.N + BN - 1) / BN, MTL = (max(r_hi - r_lo, 0) + BM - 1) / BM, active = NTL * MTL;
-  int lid = (int)blockIdx.x;
-  if (lid >= active) {
-    // dx is exactly 0 on the leaves: the blocks without a tile clear those rows, 16 lanes a row
-    // (behind the products, where the last tiles leave CUs idle)
-    if constexpr (EPI == NT_DX) {
-      const int per = ((int)gridDim.x - active) * 32;
-      const bool vec = (g.N & 3) == 0 && (((uintptr_t)g.C) & 15u) == 0;
-      for (int i = P + (lid - active) * 32 + (int)(threadIdx.x >> 4); i < g.N0; i += per) {
-        float* dst = g.C + (size_t)g.order[i] * g.ldc;
-        if (vec)
-          for (int n = 4 * (threadIdx.x & 15); n < g.N; n += 64) *(f32x4*)(dst + n) = f32x4{0.f, 0.f, 0.f, 0.f};
-        else
-          for (int n = threadIdx.x & 15; n < g.N; n += 16) dst[n] = 0.f;
-      }
-    }
-    return;
-  }
+  constexpr int IA = (BM * GR + 511) / 512, IB = BN * GR / 512;    // DMAs per wave, plane and slice
+  const int NTL = (g.N + BN - 1) / BN, MTL = (r_hi - r_lo + BM - 1) / BM, active = NTL * MTL;
+  // the tiles are dealt so that each XCD (workgroups go to the 8 XCDs in turn) takes a contiguous
+  // run, in groups of 4 row tiles per column tile
   {
     const int full = active & ~7;
     if (lid < full) lid = (lid & 7) * (full >> 3) + (lid >> 3);
@@ -97,6 +81,7 @@ __global__ void __launch_bounds__(512, 2) k_nt(NtArgs g) {
       for (int i = 0; i < IA; ++i) {
         if ((s * (IA + IB) + i) % parts != part) continue;
         const int q = i * 8 + wave, row = q * (64 / GR) + rl, k = k0 + 8 * ((lane % GR) ^ swz(row));
+        if (BM * GR % 512 != 0 && q * 64 >= BM * GR) continue;
         bdma16(ra, (row < nr && k < g.K) ? (uint32_t)(row * g.lda + k) * 2u : kOOB, 0u, lds_addr(st + s * APL + q * 1024));
       }
 #pragma unroll
@@ -260,14 +245,62 @@ __global__ void __launch_bounds__(512, 2) k_nt(NtArgs g) {
   }
 }
 
+template <int S, int EPI>
+__global__ void __launch_bounds__(512, 2) k_nt(NtArgs g) {
+  extern __shared__ __align__(16) unsigned char sm[];
+  constexpr int BN = nt_bn(S), Q = nt_mi(S) / 4;
+  // rows in use (the number of push nodes is known on the device only) and the row tile: one
+  // workgroup per CU, so the time is the rounds of 256 tiles times a tile's row tiles plus what a
+  // K step costs besides its products (about three quarters of a quarter tile: slices in flight,
+  // the barrier, B fragments).
+  // With 256 rows alone the dx product of 18 k nodes x 256 inputs ran on 144 CUs (176 us, now 141),
+  // that of 2.2 k nodes x 128 inputs on 9 (73 us, now 25).
+  const int P = (int)g.ctl[CTL_NPUSHF];
+  const int r_lo = g.leaves ? max(g.lo, P) : g.lo, r_hi = g.leaves ? g.hi : min(g.hi, P);
+  const int NTL = (g.N + BN - 1) / BN, R = max(r_hi - r_lo, 0);
+  int sel = 4, best = 1 << 30, active = 0;
+#pragma unroll
+  for (int m = 4; m >= 1; --m) {
+    const int bm = nt_bm(S, m * Q), tiles = NTL * ((R + bm - 1) / bm), cost = (tiles + 255) / 256 * (4 * m + 3);
+    if ((m == 4 || tiles < (int)gridDim.x) && cost < best) {
+      sel = m;
+      best = cost;
+      active = tiles;
+    }
+  }
+  const int lid = (int)blockIdx.x;
+  if (lid >= active) {
+    // dx is exactly 0 on the leaves: the blocks without a tile clear those rows, 16 lanes a row
+    // (behind the products, where the last tiles leave CUs idle)
+    if constexpr (EPI == NT_DX) {
+      const int per = ((int)gridDim.x - active) * 32;
+      const bool vec = (g.N & 3) == 0 && (((uintptr_t)g.C) & 15u) == 0;
+      for (int i = P + (lid - active) * 32 + (int)(threadIdx.x >> 4); i < g.N0; i += per) {
+        float* dst = g.C + (size_t)g.order[i] * g.ldc;
+        if (vec)
+          for (int n = 4 * (threadIdx.x & 15); n < g.N; n += 64) *(f32x4*)(dst + n) = f32x4{0.f, 0.f, 0.f, 0.f};
+        else
+          for (int n = threadIdx.x & 15; n < g.N; n += 16) dst[n] = 0.f;
+      }
+    }
+    return;
+  }
+  switch (sel) {
+    case 1: nt_tile<S, EPI, Q>(g, r_lo, r_hi, lid, sm); break;
+    case 2: nt_tile<S, EPI, 2 * Q>(g, r_lo, r_hi, lid, sm); break;
+    case 3: nt_tile<S, EPI, 3 * Q>(g, r_lo, r_hi, lid, sm); break;
+    default: nt_tile<S, EPI, 4 * Q>(g, r_lo, r_hi, lid, sm); break;
+  }
+}
+
 // dW | dU. Both operands are stored with the contraction index as rows, so a fragment is read from
 // LDS by transposing reads (four k of a column per lane and read). Rows of a stage are whole block
 // widths; granule c of row k sits at c ^ 2 p(k), p = k & 3 with bit 3 of k above it, so that the eight
 // rows that half a wave reads at once fall into different banks.
 template <int S>
 __global__ void __launch_bounds__(512, 2) k_tn(TnArgs g) {
-  constexpr int BM = nt_bm(S), BN = nt_bn(S), BK = nt_bk(S);
-  constexpr int MI = S == 3 ? 4 : 8, NJ = 4, WN = BN / (16 * NJ);
+  constexpr int MI = nt_mi(S), BM = nt_bm(S, MI), BN = nt_bn(S), BK = nt_bk(S, MI);
+  constexpr int NJ = 4, WN = BN / (16 * NJ);
   constexpr int AG = BM / 8, BG = BN / 8;                          // granules per row
   constexpr int APL = BK * BM * 2, BPL = BK * BN * 2, STAGE = S * (APL + BPL);
   constexpr int IA = BK * AG / 512, IB = BK * BG / 512;
@@ -451,12 +484,14 @@ __global__ void __launch_bounds__(256) k_reduce_grads(ReduceArgs a) {
 template <int S, int EPI>
 static hipError_t launch_nt_t(const NtArgs& g, hipStream_t st) {
   auto kern = k_nt<S, EPI>;
-  constexpr int shm = (int)nt_lds(S);
+  constexpr int shm = (int)nt_lds(S, nt_mi(S));
   const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, shm);
   if (e != hipSuccess) return e;
-  // the grid covers the static range; blocks past the rows in use leave at once (NT_DX: clear the
-  // leaves' rows; one row tile more, so that some block does where the push nodes fill every tile)
-  const int tiles = ((g.N + nt_bn(S) - 1) / nt_bn(S)) * ((g.hi - g.lo + nt_bm(S) - 1) / nt_bm(S) + (EPI == NT_DX ? 1 : 0));
+  // the grid covers the static range in the largest tiles, or in the smallest up to two rounds of the
+  // chip; blocks past the rows in use leave at once (NT_DX: clear the leaves' rows; one row tile
+  // more, so that some block does where the push nodes fill every tile)
+  auto count = [&](int bm) { return ((g.N + nt_bn(S) - 1) / nt_bn(S)) * ((g.hi - g.lo + bm - 1) / bm + (EPI == NT_DX ? 1 : 0)); };
+  const int tiles = std::max(count(nt_bm(S, nt_mi(S))), std::min(count(nt_bm(S, nt_mi(S) / 4)) + 1, 513));
   hipLaunchKernelGGL(kern, dim3(tiles), dim3(512), shm, st, g);
   return hipGetLastError();
 }
@@ -471,10 +506,10 @@ hipError_t launch_nt(const NtArgs& g, int S, int epi, hipStream_t st) {
 template <int S>
 static hipError_t launch_tn_t(const TnArgs& g, hipStream_t st) {
   auto kern = k_tn<S>;
-  constexpr int shm = (int)nt_lds(S);
+  constexpr int shm = (int)nt_lds(S, nt_mi(S));
   const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, shm);
   if (e != hipSuccess) return e;
-  const int tiles = ((g.H4 + nt_bn(S) - 1) / nt_bn(S)) * (g.xt + (g.H + nt_bm(S) - 1) / nt_bm(S));
+  const int tiles = ((g.H4 + nt_bn(S) - 1) / nt_bn(S)) * (g.xt + (g.H + nt_bm(S, nt_mi(S)) - 1) / nt_bm(S, nt_mi(S)));
   hipLaunchKernelGGL(kern, dim3(tiles * g.splits), dim3(512), shm, st, g);
   return hipGetLastError();
 }

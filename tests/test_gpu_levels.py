@@ -29,6 +29,8 @@ def _ops(kind, T, B):
                 depth += int(o[t, b])
                 t += int(rng.integers(1, 100))
         return o
+    if kind == "push":               # no leaves: push nodes in every row of the last tile, or all but a few
+        return np.ones((T, B), np.int8)
     if kind == "deep":               # one node per level
         o = np.ones((T, B), np.int8)
         o[(T + 1) // 2:] = -1
@@ -46,6 +48,10 @@ CASES = [
     ("alternate", 40, 300, 8, 516, 1),
     ("held", 333, 7, 12, 36, 0), ("held", 333, 7, 12, 37, 1), ("held", 64, 7, 12, 36, 0), ("held", 97, 3, 4, 260, 0),
     ("deep", 321, 2, 8, 24, 0), ("random", 20000, 1, 4, 8, 0),
+    # one to four quarters of the products' row tile (2, 3 and 4 thousand rows of 16 column tiles)
+    ("push", 16, 16, 130, 64, 0), ("push", 13, 20, 33, 64, 1), ("random", 40, 100, 130, 512, 0),
+    ("random", 60, 100, 8, 512, 0), ("random", 80, 100, 8, 500, 0), ("random", 40, 100, 72, 1024, 1),
+    ("random", 60, 100, 8, 1024, 1),
 ]
 
 
