@@ -40,6 +40,7 @@ constexpr int nt_bm(int S, int MI) { return (S == 3 ? 64 : 32) * MI; }
 constexpr int nt_bn(int S) { return S == 3 ? 128 : 256; }
 constexpr int nt_bk(int S, int MI) { return S == 3 && MI > 1 ? 32 : 64; }
 constexpr size_t nt_lds(int S, int MI) { return (size_t)2 * S * (nt_bm(S, MI) + nt_bn(S)) * nt_bk(S, MI) * 2; }
+constexpr size_t nt_leaf_lds(int S, int MI) { return (size_t)2 * nt_bm(S, MI) * (nt_bn(S) / 4 + 4) * 4; }   // h and c of a tile
 
 // dW, dU and db from the partials, and the check of the caller's top and ops (contract.hip)
 struct ReduceArgs {

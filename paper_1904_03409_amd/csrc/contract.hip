@@ -44,11 +44,12 @@ __device__ __forceinline__ float plane_sum(const uint16_t* p, size_t plane, size
 
 // One block tile of k_nt: 16 MI x (8 / WN) rows, K steps of BK.
 template <int S, int EPI, int MI>
-__device__ __forceinline__ void nt_tile(const NtArgs& g, int r_lo, int r_hi, int lid, unsigned char* sm) {
+__device__ __forceinline__ void nt_tile(const NtArgs& g, int r_lo, int r_hi, int lid, unsigned char* sm, int* s_row,
+                                        int* s_par) {
   constexpr int BM = nt_bm(S, MI), BN = nt_bn(S), BK = nt_bk(S, MI), GR = BK / 8;
   constexpr int NJ = 4, WN = BN / (16 * NJ);
   static_assert(BM == 16 * MI * (8 / WN), "eight waves cover the block tile");
-  static_assert(nt_lds(S, MI) <= nt_lds(S, nt_mi(S)) && BM * BN * 2 <= nt_lds(S, MI) && 8 * 16 * 68 * 4 <= nt_lds(S, MI), "LDS");
+  static_assert(nt_lds(S, MI) <= nt_lds(S, nt_mi(S)) && nt_leaf_lds(S, MI) <= nt_leaf_lds(S, nt_mi(S)) && 8 * 16 * 68 * 4 <= nt_lds(S, MI), "LDS");
   constexpr int APL = BM * GR * 16, BPL = BN * GR * 16, STAGE = S * (APL + BPL);
   constexpr int IA = (BM * GR + 511) / 512, IB = BN * GR / 512;    // DMAs per wave, plane and slice
   const int NTL = (g.N + BN - 1) / BN, MTL = (r_hi - r_lo + BM - 1) / BM, active = NTL * MTL;
@@ -64,6 +65,11 @@ __device__ __forceinline__ void nt_tile(const NtArgs& g, int r_lo, int r_hi, int
   const int nr = min(BM, r_hi - m0), nc = min(BN, g.N - n0);
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
   const int wm = wave / WN, wn = wave % WN, l16 = lane & 15, lq = lane >> 4;
+  // steps and parents of the tile's rows, for the epilogue (read after the barriers of the K loop)
+  if (EPI != NT_XW && tid < nr) {
+    s_row[tid] = g.order[m0 + tid];
+    if (EPI == NT_LEAF) s_par[tid] = g.opar[m0 + tid];
+  }
   const uint16_t* A = g.A + (size_t)(m0 - g.lo) * g.lda;
   const uint16_t* Bp = g.B + (size_t)n0 * g.ldb;
 
@@ -173,27 +179,44 @@ __device__ __forceinline__ void nt_tile(const NtArgs& g, int r_lo, int r_hi, int
   if constexpr (EPI == NT_LEAF) {
     // a lane's four columns are the four gates of one unit: the cell runs on the accumulators,
     // h and c go through LDS and out as whole 4 BN / 4-byte row pieces
-    constexpr int UN = BN / 4;
+    // (row stride UN + 4 words: the 16 rows x 4 units that a wave writes at once fall into 64 banks)
+    constexpr int UN = BN / 4, ULD = UN + 4;
     float* hs = reinterpret_cast<float*>(sm);
-    float* cs = hs + BM * UN;
+    float* cs = hs + BM * ULD;
     const int H = g.H;
+    // h U and c of the parents: the loads of PD row tiles are in flight at a time (the compiler's own
+    // order waited for a parent's index and then its rows, row tile by row tile)
+    constexpr int PD = MI < 3 ? MI : 3;
+    f32x4 hu[PD][NJ];
+    float cp[PD][NJ];
+    auto fetch = [&](int i) {
+      const int par = s_par[min(16 * (MI * wm + i) + l16, nr - 1)];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const int u = min(n0 / 4 + 4 * (NJ * wn + j) + lq, H - 1);
+        hu[i % PD][j] = *(const f32x4*)(g.hu + (size_t)par * (4 * H) + 4 * u);
+        cp[i % PD][j] = g.cn[(size_t)par * H + u];
+      }
+    };
+#pragma unroll
+    for (int i = 0; i < PD; ++i) fetch(i);
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
       const int r = 16 * (MI * wm + i) + l16;
-      const int par = g.opar[m0 + min(r, nr - 1)];
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
-        const int ul = 4 * (NJ * wn + j) + lq, u = min(n0 / 4 + ul, H - 1);
-        const f32x4 hu = *(const f32x4*)(g.hu + (size_t)par * (4 * H) + 4 * u);
-        const float cp = g.cn[(size_t)par * H + u];
-        const float gi = sigmoidf_(acc[i][j][0] + bias[j][0] + hu[0]);
-        const float gf = sigmoidf_(acc[i][j][1] + bias[j][1] + hu[1]);
-        const float gg = tanhf_(acc[i][j][2] + bias[j][2] + hu[2]);
-        const float go = sigmoidf_(acc[i][j][3] + bias[j][3] + hu[3]);
-        const float c = gf * cp + gi * gg;
-        hs[r * UN + ul] = canon_nan(go * tanhf_(c));
-        cs[r * UN + ul] = c;
+        const int ul = 4 * (NJ * wn + j) + lq;
+        const f32x4 x = hu[i % PD][j];
+        const float gi = sigmoidf_(acc[i][j][0] + bias[j][0] + x[0]);
+        const float gf = sigmoidf_(acc[i][j][1] + bias[j][1] + x[1]);
+        const float gg = tanhf_(acc[i][j][2] + bias[j][2] + x[2]);
+        const float go = sigmoidf_(acc[i][j][3] + bias[j][3] + x[3]);
+        const float c = gf * cp[i % PD][j] + gi * gg;
+        hs[r * ULD + ul] = canon_nan(go * tanhf_(c));
+        cs[r * ULD + ul] = c;
       }
+      if (i + PD < MI) fetch(i + PD);
+      __builtin_amdgcn_sched_barrier(0);
     }
     __syncthreads();
     const int uw = min(UN, H - n0 / 4);                // units of this block
@@ -201,8 +224,8 @@ __device__ __forceinline__ void nt_tile(const NtArgs& g, int r_lo, int r_hi, int
     for (int e = tid; e < nr * (UN / 4); e += 512) {
       const int r = e / (UN / 4), v = (e % (UN / 4)) * 4;
       if (v >= uw) continue;
-      const size_t o = (size_t)g.order[m0 + r] * H + n0 / 4 + v;
-      const f32x4 h4 = *(const f32x4*)&hs[r * UN + v], c4 = *(const f32x4*)&cs[r * UN + v];
+      const size_t o = (size_t)s_row[r] * H + n0 / 4 + v;
+      const f32x4 h4 = *(const f32x4*)&hs[r * ULD + v], c4 = *(const f32x4*)&cs[r * ULD + v];
       if (vec) {
         __builtin_nontemporal_store(h4, (f32x4*)(g.hcell + o));
         __builtin_nontemporal_store(c4, (f32x4*)(g.ccell + o));
@@ -231,7 +254,7 @@ __device__ __forceinline__ void nt_tile(const NtArgs& g, int r_lo, int r_hi, int
         const int r = 4 * e + (lane >> 4), m = 16 * (MI * wm + i) + r, n = n0 + 64 * wn + 4 * l16;
         if (m >= nr) continue;
         const f32x4 v = *(const f32x4*)&ws[r * 68 + 4 * l16];
-        float* dst = g.C + (size_t)(EPI == NT_DX ? g.order[m0 + m] : m0 + m) * g.ldc + n;
+        float* dst = g.C + (size_t)(EPI == NT_DX ? s_row[m] : m0 + m) * g.ldc + n;
         if (vec && n + 3 < g.N) {
           *(f32x4*)dst = v;
         } else {
@@ -248,6 +271,7 @@ __device__ __forceinline__ void nt_tile(const NtArgs& g, int r_lo, int r_hi, int
 template <int S, int EPI>
 __global__ void __launch_bounds__(512, 2) k_nt(NtArgs g) {
   extern __shared__ __align__(16) unsigned char sm[];
+  __shared__ int s_row[256], s_par[256];
   constexpr int BN = nt_bn(S), Q = nt_mi(S) / 4;
   // rows in use (the number of push nodes is known on the device only) and the row tile: one
   // workgroup per CU, so the time is the rounds of 256 tiles times a tile's row tiles plus what a
@@ -286,10 +310,10 @@ __global__ void __launch_bounds__(512, 2) k_nt(NtArgs g) {
     return;
   }
   switch (sel) {
-    case 1: nt_tile<S, EPI, Q>(g, r_lo, r_hi, lid, sm); break;
-    case 2: nt_tile<S, EPI, 2 * Q>(g, r_lo, r_hi, lid, sm); break;
-    case 3: nt_tile<S, EPI, 3 * Q>(g, r_lo, r_hi, lid, sm); break;
-    default: nt_tile<S, EPI, 4 * Q>(g, r_lo, r_hi, lid, sm); break;
+    case 1: nt_tile<S, EPI, Q>(g, r_lo, r_hi, lid, sm, s_row, s_par); break;
+    case 2: nt_tile<S, EPI, 2 * Q>(g, r_lo, r_hi, lid, sm, s_row, s_par); break;
+    case 3: nt_tile<S, EPI, 3 * Q>(g, r_lo, r_hi, lid, sm, s_row, s_par); break;
+    default: nt_tile<S, EPI, 4 * Q>(g, r_lo, r_hi, lid, sm, s_row, s_par); break;
   }
 }
 
@@ -484,7 +508,8 @@ __global__ void __launch_bounds__(256) k_reduce_grads(ReduceArgs a) {
 template <int S, int EPI>
 static hipError_t launch_nt_t(const NtArgs& g, hipStream_t st) {
   auto kern = k_nt<S, EPI>;
-  constexpr int shm = (int)nt_lds(S, nt_mi(S));
+  constexpr size_t stages = nt_lds(S, nt_mi(S)), leaf = EPI == NT_LEAF ? nt_leaf_lds(S, nt_mi(S)) : 0;
+  constexpr int shm = (int)(leaf > stages ? leaf : stages);
   const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, shm);
   if (e != hipSuccess) return e;
   // the grid covers the static range in the largest tiles, or in the smallest up to two rounds of the
