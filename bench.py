@@ -28,6 +28,12 @@ sys.path.insert(0, ROOT)
 PEAK = {"f32": 157.3, "bf16": 2500.0}           # dense MFMA TFLOP/s (fp32, bf16)
 
 
+def unit_peak(dname, phase):
+    """TFLOP/s of a phase's products on the matrix units they run on: in fp32 mode a product of the
+    recurrences is three fp16 ones, any other six bf16 ones."""
+    return PEAK["bf16"] / (1 if dname == "bf16" else 3 if phase in ("rec_fwd", "rec_bwd") else 6)
+
+
 def hip():
     lib = ctypes.CDLL("libamdhip64.so.7")
     lib.hipEventCreate.argtypes = [ctypes.POINTER(ctypes.c_void_p)]
@@ -129,17 +135,15 @@ def flops(wl):
 
 
 def executed_flops(wl):
-    """Flops of the matrix products on rows that carry work: the gate gradient dA is exactly
-    zero on non-push steps, so the backward contraction dA U^T (run on tiles of push rows)
-    and the dW, dU, dx products (over the push rows) skip those rows. Padding of the last
-    16-row tile of a step is not counted."""
+    """Flops of the matrix products as they run: h U once for each state (a push makes one), dA U^T
+    once for each of them at most, x W of the push steps ahead of the recurrence and of the others
+    with their cell after it (in the phase of the returned states), dW and dU in one launch
+    ("dW+db"), dx, all three over the push steps."""
     T, B, I, H = wl.T, wl.B, wl.I, wl.H
     n_push = float((np.asarray(wl.ops) == 1).sum())
-    out = flops(wl)
-    out["rec_bwd"] = 2.0 * n_push * H * 4 * H
-    for k, width in (("dW+db", I), ("dU", H), ("dx", I)):
-        out[k] = 2.0 * n_push * width * 4 * H
-    return out
+    rec, x = 2.0 * n_push * H * 4 * H, 2.0 * n_push * I * 4 * H
+    return {"rec_fwd": rec + 2.0 * B * H * 4 * H, "rec_bwd": rec, "xw_gemm+prep": x,
+            "top_gather": 2.0 * T * B * I * 4 * H - x, "dW+db": x + rec, "dx": x}
 
 
 def strip_comments(src: str) -> str:
@@ -365,10 +369,11 @@ def main():
     dname = "f32" if prec == 0 else "bf16"
     m = measure(wl, prec, args.steps, args.warmup, torch, args.config, keep_outputs=not args.no_cpu)
     ms = m["ms_per_step"]
-    fl = flops(wl)
+    fx = executed_flops(wl)
     phase = m["phases_ms"]
-    kern = max(fl, key=lambda k: phase.get(k, 0.0))
-    achieved = fl[kern] / (phase[kern] / 1e3) / 1e12
+    kern = max(fx, key=lambda k: phase.get(k, 0.0))
+    achieved = fx[kern] / (phase[kern] / 1e3) / 1e12
+    peak = unit_peak(dname, kern)
     out = {
         "metric": "fwd+bwd batch·timesteps/sec at B=256,H=512; % MFMA peak",
         "value": m["value"], "unit": "element-steps/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,
@@ -377,8 +382,8 @@ def main():
         "config": {"workload": f"{args.config}: StackLSTM fwd+bwd, B={wl.B} T={wl.T} I={wl.I} H={wl.H}, "
                                f"arc-standard op streams, {dname} GEMM operands",
                    "global_batch": wl.B, "seq_len": wl.T, "parallelism": "none (1 GPU)"},
-        "roofline": {"bound": "mfma", "kernel": kern, "achieved": achieved, "peak": PEAK[dname], "unit": "TFLOP/s",
-                     "frac": achieved / PEAK[dname], "traffic": stored_traffic(args.config, dname, kern)},
+        "roofline": {"bound": "mfma", "kernel": kern, "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
+                     "frac": achieved / peak, "traffic": stored_traffic(args.config, dname, kern)},
     }
     out.update({k: v for k, v in m.items() if k not in ("value", "ms_per_step", "out")})
     gpu_out = m.get("out")
@@ -417,7 +422,7 @@ def measure(wl, prec, steps, warmup, torch, cname, keep_outputs=False):
     per_step = phase.pop("_per_step_ms")
     ms = total_ms / steps
     fl, fx = flops(wl), executed_flops(wl)
-    peak = PEAK[dname]
+    peak = unit_peak(dname, "rec_fwd")
     rec_t = (phase["rec_fwd"] + phase["rec_bwd"]) / 1e3
     got = run.results() if keep_outputs else {"ptr": run.ptr.cpu().numpy()}
     ptr = np.vstack([np.zeros((1, wl.B), np.int64), np.cumsum(wl.ops.astype(np.int64), axis=0)])
@@ -427,11 +432,11 @@ def measure(wl, prec, steps, warmup, torch, cname, keep_outputs=False):
          "status": {"code": int(status), "ptr_trace_equal_prefix_sum": bool(np.array_equal(got["ptr"], ptr))},
          "phases_ms": {k: round(v, 4) for k, v in phase.items()},
          "step_ms_median": float(np.median(per_step)), "step_ms_min": float(np.min(per_step)),
-         # algorithmic: every element-step's 2*4H*H per recurrent contraction; executed: the
-         # backward contraction over push rows only (dA is exactly 0 on the others)
+         # of the matrix units the products run on (unit_peak). Algorithmic: every element-step's 2*4H*H
+         # per recurrent contraction; executed: the products that are run (executed_flops)
          "recurrent_mfma_frac": (fl["rec_fwd"] + fl["rec_bwd"]) / rec_t / 1e12 / peak,
          "recurrent_mfma_frac_executed": (fx["rec_fwd"] + fx["rec_bwd"]) / rec_t / 1e12 / peak,
-         "overall_mfma_frac": sum(fx.values()) / (ms / 1e3) / 1e12 / peak,
+         "overall_mfma_frac": sum(v / unit_peak(dname, k) for k, v in fx.items()) / (ms / 1e3) / 1e12,
          "executed_tflops": {k: round(fx[k] / (phase[k] / 1e3) / 1e12, 2) for k in fx if phase.get(k)},
          "push_steps_per_s": st["push_steps"] / (ms / 1e3), "op_stats": st, "wall_s_timed": wall,
          "hbm_gb_s_whole_run": None if step_bytes is None else step_bytes / (ms / 1e3) / 1e9,

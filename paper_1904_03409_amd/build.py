@@ -1,10 +1,10 @@
 """Builds the HIP library ``libstacklstm.so`` in-tree for gfx950 (hipcc, no JIT cache).
 
 Every kernel's resource usage is read from the compiler's resource report, and the build
-fails if a kernel that counts its own outstanding vector-memory operations (the wide
-forward, the LDS-DMA ring GEMM, and the backward variants built with direct dA staging) uses
-scratch memory: spill loads and stores share that counter, so a counted wait would no longer
-wait for the loads it counts.
+fails if a kernel that counts its own outstanding vector-memory operations uses scratch memory:
+spill loads and stores share that counter, so a counted wait would no longer wait for the loads
+it counts. (The kernels built now wait for all of theirs; the names in counted_waits are of
+kernels that did not.)
 
 The device assembly of every source is kept (-save-temps) and scanned for one hazard the
 compiler has been seen to miss: an MFMA chain at the end of a basic block whose results are
@@ -31,8 +31,7 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall",
 
 
 def bwd_direct_built(prec: int, nt: int, ks: int) -> bool:
-    """The rule of rec_bwd_direct_built() in csrc/rec_config.h: backward variants that
-    contain the direct-staging path (LDS DMA with counted waits)."""
+    """Variants of the time-step backward that staged dA rows by LDS DMA with counted waits."""
     seg = ks * (32 if prec else 16) * (2 if prec else 4)
     occ = 2 if (prec == 1 and ks == 32) else 1
     return seg % 1024 == 0 and seg // 1024 <= 2 and occ == 1 and nt <= 4
