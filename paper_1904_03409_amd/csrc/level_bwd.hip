@@ -27,6 +27,7 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
   constexpr int WREG = NP * KH * 1024;                      // bytes of a wave's 16 row slices
   constexpr int kids = lev_bwd_kids(NP, KS), NI = kids / 16, NQ = kLevPars / 16;
   constexpr int RLD = 36;
+  constexpr bool kDefer = NP == 1 && KS >= 24;              // (put_da)
   // the next level's first operands are fetched behind the first rows of the exchange (in one queue
   // with them, the rows would wait for HBM); with the most registers in use, ahead of the barrier
   constexpr bool kLate = NP * KS < 32 || NP == 1;
@@ -85,6 +86,36 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
   auto stamp = [&](int d, int k) {
     if (a.clk && tid == 0) a.clk[((size_t)blockIdx.x * T + d - 1) * 4 + k] = wall_clock64();
   };
+  // dA of a child: the planes that dW, dU and dx read, and the bias gradient. Nobody waits for these
+  // stores. H > 512: a pass that is not the level's last leaves it to the next one, which does it from
+  // LDS while its own operands are on their way (H = 1024, levels of 170 nodes: 50.0 -> 46.7 us a
+  // level). The last pass does it in place (from LDS it costs 0.2 us a level, and after the barrier's
+  // arrival 0.4: the next rows queue behind the stores); so do the others, whose levels gained 1% at
+  // most from it (H = 512) or lost up to 4% (H = 300).
+  auto put_da = [&](int c, int ou, const f32x4& da) {
+    bf16_t p[4][S];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float y = da[q] - dbe[q], z = db[q] + y;
+      dbe[q] = (z - db[q]) - y;
+      db[q] = z;
+      split_bf16<S>(da[q], p[q]);
+    }
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+      bf16_t* dst = at32(a.dap + s * a.dplane, 2u * ((uint32_t)c * (uint32_t)H4s + 4u * ou));
+      *(uint2*)dst = uint2{(uint32_t)p[0][s] | ((uint32_t)p[1][s] << 16), (uint32_t)p[2][s] | ((uint32_t)p[3][s] << 16)};
+      if (ou == H - 1 && (H & 1)) *(uint2*)(dst + 4) = uint2{0u, 0u};   // row padding
+    }
+  };
+  auto flush = [&](int cb, int ce) {
+    const int ot = opaque(tid);
+#pragma unroll
+    for (int j = 0; j < NI; ++j) {
+      const int k = (ot >> 5) + 16 * j;
+      if (cb + k < ce && 32 * w + (ot & 31) < H) put_da(cb + k, 32 * w + (ot & 31), ch_a[k * 32 + (ot & 31)]);
+    }
+  };
   bool stop = false;
   // Level d: parents are the internal nodes [i0, i1) of level d - 1, whose children are the nodes
   // [c0, cend) of level d, whose own internal numbers start at i1. The first pass's operands and
@@ -104,7 +135,7 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
     stamp(d, 0);
     float* eg_in = keep + (d & 1) * (2 * kLevKeep * 32);
     float* eg_out = keep + (~d & 1) * (2 * kLevKeep * 32);
-    int cs = c0;
+    int cs = c0, fb = 0, fe = 0;                            // children whose dA waits in LDS
     for (int ib = i0; ib < i1; ib += kLevPars) {
       const int ni = min(kLevPars, i1 - ib);
       if (ib > i0) {
@@ -122,6 +153,10 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
         for (int q = 0; q < 4; ++q) sA[k][q] = 0.f;
       }
       for (int cb = c0; cb < c1; cb += kids) {
+        const bool defer = kDefer && cb + kids < cend;
+        if constexpr (kDefer) flush(fb, fe);
+        fb = cb;
+        fe = defer ? min(cb + kids, c1) : cb;
         // cell backward of up to 64 (32) children
         {
           const int ot = opaque(tid), uu = ot & 31, u = 32 * w + uu;
@@ -151,6 +186,11 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
                                 dct * ga[0] * (1.f - ga[2] * ga[2]), dh * tc * ga[3] * (1.f - ga[3])};
               ch_a[k * 32 + uu] = da;
               ch_c[k * 32 + uu] = float2{dct * ga[1] + ic, ih};
+              if constexpr (kDefer) {
+                if (!defer) put_da(c, u, da);
+                continue;
+              }
+              // (written out: through put_da the fp32 kernel of H = 512 spills four more registers)
               bf16_t p[4][S];
 #pragma unroll
               for (int q = 0; q < 4; ++q) {
