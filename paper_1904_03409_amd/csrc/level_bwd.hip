@@ -1,7 +1,7 @@
 // Backward recurrence over the level schedule (levels.h), from the deepest level up. Persistent,
 // groups and unit ownership as in the forward.
 //
-// A node's gradient is complete when its children are done: dh = its interval sums (k_gsum) + what
+// A node's gradient is complete when its children are done: dh = its interval sums (k_prep_bwd) + what
 // its children send, dc likewise; the cell backward then gives its gate gradient dA (a push only;
 // every other step's is 0) and dc f for its parent. The parent needs (sum of the children's dA) U^T:
 // the sum first, so one product per node with children. Per level:

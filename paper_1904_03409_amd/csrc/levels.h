@@ -38,7 +38,7 @@ struct LevIdx {
   int32_t* ioff;     // [G][T + 4]: first internal number of level d = 0 .. D + 1
   int32_t* cidx;     // [N0 + B]: internal number of a node; ~(the next internal number) if it has no children
   int32_t* kin;      // [N0]: of a push node, 2 * (its internal number, or -1) + (1 if it was popped)
-  int32_t* gslot;    // [N0]: slot that the upstream gradient of step t*B + b is summed into (k_gsum)
+  int32_t* gslot;    // [N0]: slot that the upstream gradient of step t*B + b is summed into (k_prep_bwd)
 };
 
 struct PlanArgs {
@@ -74,7 +74,7 @@ struct LevBwdArgs {
   int T, B, H, H4s, G, NW, N0, spin_limit;
   LevIdx ix;
   const float* cpn; const float* stash;
-  const float* gf;              // [2 (N0 + B)][H] interval sums of dh_top (k_gsum)
+  const float* gf;              // [2 (N0 + B)][H] interval sums of dh_top (k_prep_bwd)
   const float* gc;              // the same of dc_top, or null
   float* eg;                    // [N0 + B][H] gradient of h that reaches an internal node from its children
   float* dcs;                   // the same of c
