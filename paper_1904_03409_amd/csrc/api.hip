@@ -303,7 +303,7 @@ int fwd_impl(const slstm_dims* d, const Plan& p, const Layout& L, bool keep, con
     a.n_u = p.NW * 4;
     a.W = W; a.U = U; a.h0 = h0; a.c0 = c0;
     a.wt = (uint16_t*)(ws + L.wt); a.wp = (uint16_t*)(ws + L.wp); a.uf = (uint4*)(ws + L.uf);
-    a.uinv = (float*)(ws + L.ufi); a.rinit = (float*)(ws + L.rin);
+    a.uexp = (int32_t*)(ws + L.ufi); a.rinit = (int32_t*)(ws + L.rin);
     a.hq = hq; a.hplane = hplane; a.h3 = h3; a.cn = cn;
     a.ctl = ctl; a.keep_errors = d->defer_status ? 1 : 0;
     const int grid = a.n_w + a.n_u + (B + 3) / 4;
@@ -369,7 +369,7 @@ int fwd_impl(const slstm_dims* d, const Plan& p, const Layout& L, bool keep, con
     a.ix = ix; a.hu = hu; a.hq = hq; a.hplane = hplane; a.cn = cn; a.hcell = h_cell; a.ccell = c_cell;
     a.stash = keep ? (float*)(ws + L.stash) : nullptr;
     a.cpn = (float*)(ws + L.cpn); a.h3 = h3;
-    a.uf = (const uint4*)(ws + L.uf); a.uinv = (const float*)(ws + L.ufi); a.rinit = (const float*)(ws + L.rin);
+    a.uf = (const uint4*)(ws + L.uf); a.uexp = (const int32_t*)(ws + L.ufi); a.rinit = (const int32_t*)(ws + L.rin);
     a.U = U; a.ctl = ctl;
     a.clk = (long long*)d->step_clock;
     if ((rc = hip_status(launch_lev_fwd(a, p.NP, p.KS, lev_grid(p), st)))) return rc;

@@ -244,8 +244,9 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
           float m = fmaxf(fmaxf(fabsf(sA[k][0]), fabsf(sA[k][1])), fmaxf(fabsf(sA[k][2]), fabsf(sA[k][3])));
           m = max16(m);
           m = fmaxf(m, __shfl_xor(m, 16, 32));
-          scale = rec_scale(m);
-          if (r < ni && uu == 0) a.sxs[(size_t)(ib + r) * NW + w] = 1.f / scale;
+          const int e = rec_exp(m);
+          scale = rec_scale(e);
+          if (r < ni && uu == 0) a.sxs[(size_t)(ib + r) * NW + w] = rec_ldexp(1.f, -e - kDaExp);
         }
         if (r < ni && u < H) {
           uint16_t p[4][NP];
@@ -369,7 +370,7 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
               const uint16_t* x = a.sx + (size_t)(row0 + r) * H4s;
               v = 0.f;
               for (int n = 0; n < H4; ++n)
-                v = fmaf(rec_value(x[n], x[a.xplane + n]) * a.sxs[(size_t)(row0 + r) * NW + n / 128],
+                v = fmaf(rec_ldexp(rec_value(x[n], x[a.xplane + n]) * a.sxs[(size_t)(row0 + r) * NW + n / 128], kDaExp),
                          a.U[(size_t)u * H4 + perm_to_orig(n, H)], v);
             }
           }

@@ -42,10 +42,10 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_fwd(LevFwdArgs a) {
 #pragma unroll
         for (int s = 0; s < NP; ++s) uf[t][c][s] = src[((t * KH + c) * NP + s) * 64];
   }
-  float ui[2] = {1.f, 1.f};                                 // inverse scales of this lane's units
+  int ui[2] = {0, 0};                                       // exponents of the inverse scales of this lane's units
   if constexpr (NP == 2) {
-    ui[0] = a.uinv[32 * w + 8 * (wave & 3) + lq];
-    ui[1] = a.uinv[32 * w + 8 * (wave & 3) + 4 + lq];
+    ui[0] = a.uexp[32 * w + 8 * (wave & 3) + lq];
+    ui[1] = a.uexp[32 * w + 8 * (wave & 3) + 4 + lq];
   }
 
   // rows [row0, q1) (at most ROWS) into buffer buf; granule gr of row r sits at slot gr ^ (r & 7).
@@ -109,10 +109,10 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_fwd(LevFwdArgs a) {
           const float v = p[0] + p[HUH];
           if (v == v) continue;
           const uint16_t* h = a.hq + (size_t)(row0 + r) * Hs;
-          const float f = (row0 >= N0 ? a.rinit[row0 + r - N0] : 1.f) / kHScale;
+          const int f = row0 >= N0 ? a.rinit[row0 + r - N0] : -kHExp;
           float s = 0.f;
           for (int k = 0; k < H; ++k)
-            s = fmaf(rec_value(h[k], h[a.hplane + k]) * f, a.U[(size_t)k * H4 + (size_t)q * H + ou], s);
+            s = fmaf(rec_ldexp(rec_value(h[k], h[a.hplane + k]), f), a.U[(size_t)k * H4 + (size_t)q * H + ou], s);
           p[0] = s;
           p[HUH] = 0.f;
         }
@@ -218,14 +218,14 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_fwd(LevFwdArgs a) {
 #pragma unroll
       for (int r = 0; r < RT; ++r) {
         const bool live = 16 * r + l16 < nr;
-        float f = 1.f;
+        int f = -kHExp;
         if (NP == 2 && d == 0 && live) f = a.rinit[row0 + 16 * r + l16 - N0];
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
           f32x4 v = acc[r][t];
           if constexpr (NP == 2) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = (v[q] * sg + lo[r][t][q]) * (ui[t] * f);
+            for (int q = 0; q < 4; ++q) v[q] = rec_ldexp(v[q] * sg + lo[r][t][q], ui[t] + f);
             if (live && (v[0] != v[0] || v[1] != v[1] || v[2] != v[2] || v[3] != v[3])) s_nan = 1;
           }
           *(f32x4*)&hs[kh * HUH + (r * 16 + l16) * HULD + 32 * (wave & 3) + 16 * t + 4 * lq] = v;

@@ -63,8 +63,8 @@ struct LevFwdArgs {
   // for a backward (null: not kept): gate activations [P][4H] and the parent's c [P][H] of a push
   // node, fp32 mode also h as bf16 planes [3][N0 + B][Hs]
   float* stash; float* cpn; uint16_t* h3;
-  const uint4* uf; const float* uinv;   // U fragments and the inverse scales of their units (k_prep_fwd)
-  const float* rinit;           // [B]: inverse scale of an initial state's row, by node (fp32 mode)
+  const uint4* uf; const int32_t* uexp; // U fragments and the exponents of their units' inverse scales (k_prep_fwd)
+  const int32_t* rinit;         // [B]: exponent of the inverse scale of an initial state's row, by node (fp32 mode)
   const float* U;
   uint32_t* ctl;
   long long* clk;
@@ -81,7 +81,7 @@ struct LevBwdArgs {
   uint16_t* dap; size_t dplane; // bf16 planes of dA: [S][P][H4s]
   uint16_t* sx; size_t xplane;  // recurrent planes of the children's dA sums: [NP][N0 + B][H4s]
   float* sxs;                   // [N0 + B][NW]: inverse scale of a row's 128 columns of a workgroup (fp32 mode)
-  const uint4* ub; const float* uinv;   // U^T fragments and the inverse scales of their units (k_prep_bwd)
+  const uint4* ub; const float* uinv;   // U^T fragments and the inverse scales of their units (k_prep_bwd); kDaExp
   const float* U;
   float* db_part;               // [G][4H]
   float* dh0; float* dc0;

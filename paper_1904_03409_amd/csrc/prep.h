@@ -17,10 +17,10 @@ struct PrepFwdArgs {
   const float* W; const float* U; const float* h0; const float* c0;
   uint16_t* wt;                    // [S][4H][Ip]
   uint16_t* wp;                    // [S][I][H4s]
-  uint4* uf; float* uinv;
+  uint4* uf; int32_t* uexp;
   uint16_t* hq; size_t hplane;
   uint16_t* h3;                    // fp32 mode with a backward: [3][N0 + B][Hs], else null
-  float* rinit;
+  int32_t* rinit;
   float* cn;
   uint32_t* ctl; int keep_errors;
 };

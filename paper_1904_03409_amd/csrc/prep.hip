@@ -5,6 +5,9 @@
 #include "prep.h"
 #include "split.h"
 
+// Largest finite magnitude so far and |v| (an infinity is one at any scale)
+__device__ __forceinline__ float max_finite(float m, float v) { return __builtin_isfinite(v) ? fmaxf(m, fabsf(v)) : m; }
+
 // Rows lo .. hi-1 of the step list (push nodes, then leaves) of x as planes [S][hi - lo][Ip],
 // zero past I.
 template <int S>
@@ -90,15 +93,14 @@ __global__ void __launch_bounds__(256) k_prep_fwd(PrepFwdArgs a) {
       const int unit = u0 + (tid & 7), gate = (tid >> 3) & 3;
       if (unit < H)
 #pragma unroll 8
-        for (int k = tid >> 5; k < H; k += 8) m = fmaxf(m, fabsf(a.U[(size_t)k * 4 * H + (size_t)gate * H + unit]));
+        for (int k = tid >> 5; k < H; k += 8) m = max_finite(m, a.U[(size_t)k * 4 * H + (size_t)gate * H + unit]);
       s_max[tid] = m;
       __syncthreads();
       for (int k = 8; k < 256; k += 8) m = fmaxf(m, s_max[(tid & 7) + k]);
       m = fmaxf(m, s_max[tid & 7]);
       __syncthreads();
-      const float sc = rec_scale(m);
-      s_max[tid] = sc;
-      if (tid < 8) a.uinv[u0 + tid] = 1.f / (sc * kHScale);
+      s_max[tid] = rec_scale(rec_exp(m));
+      if (tid < 8) a.uexp[u0 + tid] = -rec_exp(m);
       __syncthreads();
     }
     const int KH = a.KS / 2;
@@ -129,11 +131,11 @@ __global__ void __launch_bounds__(256) k_prep_fwd(PrepFwdArgs a) {
   float sc = 1.f;
   if (S == 3) {
     float m = 0.f;
-    for (int k = lane; k < H; k += 64) m = fmaxf(m, fabsf(a.h0[(size_t)b * H + k]));
+    for (int k = lane; k < H; k += 64) m = max_finite(m, a.h0[(size_t)b * H + k]);
 #pragma unroll
     for (int d = 32; d; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, 64));
-    sc = m < 1.f ? kHScale : rec_scale(m);
-    if (lane == 0) a.rinit[init] = kHScale / sc;
+    sc = rec_scale(rec_exp(m));
+    if (lane == 0) a.rinit[init] = -rec_exp(m);
   }
   for (int k = lane; k < a.Hs; k += 64) {
     const float v = k < H ? a.h0[(size_t)b * H + k] : 0.f;
@@ -235,13 +237,12 @@ __global__ void __launch_bounds__(256) k_prep_bwd(PrepBwdArgs a) {
       float m = 0.f;
       if (unit < H)
 #pragma unroll 8
-        for (int n = tid & 15; n < H4; n += 16) m = fmaxf(m, fabsf(a.U[(size_t)unit * H4 + n]));
+        for (int n = tid & 15; n < H4; n += 16) m = max_finite(m, a.U[(size_t)unit * H4 + n]);
 #pragma unroll
       for (int d = 8; d; d >>= 1) m = fmaxf(m, __shfl_xor(m, d, 16));
       if ((tid & 15) == 0) {
-        const float sc = rec_scale(m);
-        s_sc[tid >> 4] = sc;
-        if (wave == 0) a.uinv[unit] = 1.f / sc;
+        s_sc[tid >> 4] = rec_scale(rec_exp(m));
+        if (wave == 0) a.uinv[unit] = rec_ldexp(1.f, kDaExp - rec_exp(m));
       }
       __syncthreads();
     }

@@ -4,7 +4,8 @@
 // p1 + p2 + p3 = v exactly (8 significant bits each of the 24), and a product is the six
 // bf16 products p1q1 + p1q2 + p2q1 + p1q3 + p2q2 + p3q1 accumulated in fp32; what is left out is
 // below 2^-25 of |v||w|, half an ulp of one fp32 product. The bf16 MFMAs have 16 times the rate of the
-// fp32 ones, so six of them take 3/8 of the time.
+// fp32 ones, so six of them take 3/8 of the time. A plane ends at bf16's smallest number, 2^-133, so values
+// below about 1e-35 keep 2^-134 of absolute precision (gradients of 1e-34: dx 1.5e-6 off, normwise per step).
 #pragma once
 #include "common.h"
 
@@ -70,7 +71,11 @@ __device__ __forceinline__ void mfma_planes_add(const bf16x8 (&a)[N][3], const b
 // significant bits down to 2^-17 of the largest and 2^-40 of the largest below that, and a product
 // is p1q1 + p1q2 + p2q1, three MFMAs and two thirds of the registers of the bf16 planes.
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-constexpr float kHScale = 32768.f;       // scale of h
+constexpr int kHExp = 15;                // exponent of the scale of h
+constexpr float kHScale = 32768.f;
+// A row piece's inverse scale is kept as 2^-(s + kDaExp) and a unit's as 2^(kDaExp - s): both are fp32
+// numbers, and the sums over the pieces, in units of the largest weight, overflow only with dA itself.
+constexpr int kDaExp = 14;
 
 template <int NP>
 __device__ __forceinline__ void split_rec(float v, float scale, uint16_t (&p)[NP]) {
@@ -99,14 +104,17 @@ __device__ __forceinline__ void split_rec_granule(const float (&v)[8], float sca
 #pragma unroll
   for (int s = 0; s < NP; ++s) g[s] = uint4{w[s][0], w[s][1], w[s][2], w[s][3]};
 }
-// Power of two that brings a largest magnitude m into [2^14, 2^15) (1 for zero and non-finite m;
-// limited so that its inverse and the products of two scales stay normal numbers)
-__device__ __forceinline__ float rec_scale(float m) {
+// Exponent s of the power of two that brings a largest magnitude m into [2^14, 2^15): -113 .. 127 (0
+// for zero). At 127 (m below 2^-112) the largest ends under 2^14, and every fp32 number of its size is
+// still a whole number of fp16's smallest steps. A non-finite m gets -114: no finite value becomes
+// infinite. 2^s and 2^-s are fp32 numbers (2^-127 a subnormal one); the two inverse scales of a product
+// together need not be, so they are applied one after the other or as a sum of exponents.
+__device__ __forceinline__ int rec_exp(float m) {
   const int e = (int)((__float_as_uint(m) >> 23) & 0xffu);
-  if (e == 0xff || m == 0.f) return 1.f;
-  const int k = min(max(127 + 14 - (e - 127), 127 - 60), 127 + 60);
-  return __uint_as_float((uint32_t)k << 23);
+  return m == 0.f ? 0 : min(127 + 14 - e, 127);
 }
+__device__ __forceinline__ float rec_scale(int s) { return __uint_as_float((uint32_t)(127 + s) << 23); }
+__device__ __forceinline__ float rec_ldexp(float v, int e) { return __builtin_amdgcn_ldexpf(v, e); }
 // The value of a plane pair.
 __device__ __forceinline__ float rec_value(uint16_t a, uint16_t b) {
   return (float)__builtin_bit_cast(_Float16, a) + (float)__builtin_bit_cast(_Float16, b);
