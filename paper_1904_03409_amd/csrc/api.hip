@@ -370,7 +370,7 @@ int fwd_impl(const slstm_dims* d, const Plan& p, const Layout& L, bool keep, con
     a.stash = keep ? (float*)(ws + L.stash) : nullptr;
     a.cpn = (float*)(ws + L.cpn); a.h3 = h3;
     a.uf = (const uint4*)(ws + L.uf); a.uexp = (const int32_t*)(ws + L.ufi); a.rinit = (const int32_t*)(ws + L.rin);
-    a.U = U; a.ctl = ctl;
+    a.ctl = ctl;
     a.clk = (long long*)d->step_clock;
     if ((rc = hip_status(launch_lev_fwd(a, p.NP, p.KS, lev_grid(p), st)))) return rc;
   }

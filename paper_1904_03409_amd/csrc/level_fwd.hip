@@ -20,8 +20,7 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_fwd(LevFwdArgs a) {
   extern __shared__ __align__(16) unsigned char lsm[];
   float* hu_s = reinterpret_cast<float*>(lsm + 2 * BUF);    // [2][2][ROWS][HULD] h U of the pass, by K half
   float* c_s = hu_s + 4 * HUH;                              // [2][ROWS][32] c of the parents
-  __shared__ int s_g, s_w, s_flag, s_nan;
-  if (threadIdx.x == 0) s_nan = 0;
+  __shared__ int s_g, s_w, s_flag;
   claim_group_slot(a.ctl + CTL_XCC_SLOT, a.G, a.NW, &s_g, &s_w);
   const int g = uni(s_g), w = uni(s_w);
   if (g < 0) return;
@@ -97,28 +96,6 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_fwd(LevFwdArgs a) {
   auto h_u = [&](const float* hs, int r, int uu) {           // h U of row r of the pass, this thread's unit
     const f32x4 x = *(const f32x4*)&hs[r * HULD + 4 * uu], y = *(const f32x4*)&hs[HUH + r * HULD + 4 * uu];
     return f32x4{x[0] + y[0], x[1] + y[1], x[2] + y[2], x[3] + y[3]};
-  };
-  // NaN results of a pass once more from the values: an infinite weight has no second plane, and
-  // its products with planes of both signs give NaN where the fp32 product is infinite.
-  auto redo_nan = [&](float* hs, int row0, int nr) {
-    const int ot = opaque(tid), ouu = ot & 31, ou = 32 * w + ouu;
-    if (ou < H)
-      for (int r = ot >> 5; r < nr; r += 16)
-        for (int q = 0; q < 4; ++q) {
-          float* p = &hs[r * HULD + 4 * ouu + q];
-          const float v = p[0] + p[HUH];
-          if (v == v) continue;
-          const uint16_t* h = a.hq + (size_t)(row0 + r) * Hs;
-          const int f = row0 >= N0 ? a.rinit[row0 + r - N0] : -kHExp;
-          float s = 0.f;
-          for (int k = 0; k < H; ++k)
-            s = fmaf(rec_ldexp(rec_value(h[k], h[a.hplane + k]), f), a.U[(size_t)k * H4 + (size_t)q * H + ou], s);
-          p[0] = s;
-          p[HUH] = 0.f;
-        }
-    __syncthreads();
-    if (tid == 0) s_nan = 0;
-    __syncthreads();
   };
   struct Cell { f32x4 g; float h, cc, cp; };
   auto cell = [&](int c, int row0, const float* hs, const float* cs, const f32x4& xw, int par) {
@@ -215,22 +192,42 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_fwd(LevFwdArgs a) {
       }
       // (KS = 2: the one chunk of the second half is an odd one)
       const float sg = (KH & 1) && kh ? -1.f : 1.f;
+      if constexpr (NP == 2) {
+        bool bad = false;
 #pragma unroll
-      for (int r = 0; r < RT; ++r) {
-        const bool live = 16 * r + l16 < nr;
-        int f = -kHExp;
-        if (NP == 2 && d == 0 && live) f = a.rinit[row0 + 16 * r + l16 - N0];
+        for (int r = 0; r < RT; ++r) {
+          const bool live = 16 * r + l16 < nr;
+          int f = -kHExp;
+          if (d == 0 && live) f = a.rinit[row0 + 16 * r + l16 - N0];
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          f32x4 v = acc[r][t];
-          if constexpr (NP == 2) {
+          for (int t = 0; t < 2; ++t) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) v[q] = rec_ldexp(v[q] * sg + lo[r][t][q], ui[t] + f);
-            if (live && (v[0] != v[0] || v[1] != v[1] || v[2] != v[2] || v[3] != v[3])) s_nan = 1;
+            for (int q = 0; q < 4; ++q) acc[r][t][q] = rec_ldexp(acc[r][t][q] * sg + lo[r][t][q], ui[t] + f);
+            bad |= live && has_nan(acc[r][t]);
           }
-          *(f32x4*)&hs[kh * HUH + (r * 16 + l16) * HULD + 32 * (wave & 3) + 16 * t + 4 * lq] = v;
+        }
+        if (__ballot(bad)) {
+#pragma unroll
+          for (int r = 0; r < RT; ++r)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+              f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+              for (int c = 0; c < KH; ++c) {
+                const uint4 b = *(const uint4*)(bs + ((4 * (kh * KH + c) + lq) ^ (l16 & 7)) * 16 + r * 16 * GRW * 16);
+                mfma_rec_first(c, uf[t][c][0], b, v);
+              }
+#pragma unroll
+              for (int q = 0; q < 4; ++q)
+                if (acc[r][t][q] != acc[r][t][q]) acc[r][t][q] = v[q] * sg;
+            }
         }
       }
+#pragma unroll
+      for (int r = 0; r < RT; ++r)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+          *(f32x4*)&hs[kh * HUH + (r * 16 + l16) * HULD + 32 * (wave & 3) + 16 * t + 4 * lq] = acc[r][t];
       // the next pass's rows and this pass's operands, issued a pass ago (one in-order counter: the
       // stores in between are waited for too)
       wait_vm<0>();
@@ -238,7 +235,6 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_fwd(LevFwdArgs a) {
       for (int r = 0; r < RT; ++r) cs[(opaque(tid) >> 5) * kLevUnits + 16 * r * kLevUnits + (opaque(tid) & 31)] = pre.cp[r];
       __syncthreads();
       if (!more) stamp(d, 2);
-      if (NP == 2 && uni(s_nan)) redo_nan(hs, row0, nr);
       // in flight behind the cell and the next products: the rows after the next (this buffer is free)
       // and the operands of the next pass
       const Pre cur = pre;

@@ -65,7 +65,6 @@ struct LevFwdArgs {
   float* stash; float* cpn; uint16_t* h3;
   const uint4* uf; const int32_t* uexp; // U fragments and the exponents of their units' inverse scales (k_prep_fwd)
   const int32_t* rinit;         // [B]: exponent of the inverse scale of an initial state's row, by node (fp32 mode)
-  const float* U;
   uint32_t* ctl;
   long long* clk;
 };

@@ -123,21 +123,33 @@ __device__ __forceinline__ float rec_value(uint16_t a, uint16_t b) {
 // acc += the products of K chunk c. fp32 mode: the first plane of A is stored negated in odd chunks
 // and its products subtracted, so that what the MFMA cuts off, always towards minus infinity,
 // cancels between chunks; those of the second plane gather in lo.
+__device__ __forceinline__ f32x4 mfma_f16_16x16x32(const uint4& x, const uint4& y, f32x4 z) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, x), __builtin_bit_cast(f16x8, y), z, 0, 0, 0);
+}
 template <int NP>
 __device__ __forceinline__ void mfma_rec(int c, const uint4 (&a)[NP], const uint4 (&b)[NP], f32x4& acc, f32x4& lo) {
   if constexpr (NP == 1) {
     acc = mfma_bf16_16x16x32(__builtin_bit_cast(bf16x8, a[0]), __builtin_bit_cast(bf16x8, b[0]), acc);
   } else {
-    auto mm = [](const uint4& x, const uint4& y, f32x4 z) {
-      return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, x), __builtin_bit_cast(f16x8, y), z, 0, 0, 0);
-    };
-    f32x4 hi = mm(a[0], b[1], f32x4{0.f, 0.f, 0.f, 0.f});
-    lo = mm(a[1], b[0], lo);
-    hi = mm(a[0], b[0], hi);
+    f32x4 hi = mfma_f16_16x16x32(a[0], b[1], f32x4{0.f, 0.f, 0.f, 0.f});
+    lo = mfma_f16_16x16x32(a[1], b[0], lo);
+    hi = mfma_f16_16x16x32(a[0], b[0], hi);
     if (c & 1) acc -= hi;
     else acc += hi;
   }
 }
+// The same of the first planes alone, fp32 mode. A product with an infinity in it is NaN where the
+// fp32 one is infinite, because the infinity also meets the other operand's second plane, of
+// either sign or zero. The sum of the first planes' products is infinite or NaN as the fp32 sum is (but
+// for values so far below the largest of their scale, 2^-40, that their first plane is 0). So a wave
+// that finds NaN among its results takes those from here, on the fragments it has: no other wave
+// needs to know.
+__device__ __forceinline__ void mfma_rec_first(int c, const uint4& a, const uint4& b, f32x4& acc) {
+  const f32x4 hi = mfma_f16_16x16x32(a, b, f32x4{0.f, 0.f, 0.f, 0.f});
+  if (c & 1) acc -= hi;
+  else acc += hi;
+}
+__device__ __forceinline__ bool has_nan(const f32x4& v) { return v[0] != v[0] || v[1] != v[1] || v[2] != v[2] || v[3] != v[3]; }
 // Fragments of an odd chunk: the first plane negated.
 __device__ __forceinline__ uint4 rec_negated(uint4 v) {
   return uint4{v.x ^ 0x80008000u, v.y ^ 0x80008000u, v.z ^ 0x80008000u, v.w ^ 0x80008000u};
