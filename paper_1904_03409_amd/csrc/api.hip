@@ -541,7 +541,7 @@ int stacklstm_bwd(const slstm_dims* d, const float* x, const int8_t* ops, const 
     a.stash = (const float*)(ws + L.stash);
     a.gf = gf; a.gc = gc; a.eg = (float*)(ws + L.eg); a.dcs = (float*)(ws + L.dcs);
     a.dap = dap; a.dplane = dplane; a.sx = (uint16_t*)(ws + L.hu); a.xplane = (size_t)(N0 + B) * L.H4s;
-    a.sxs = (float*)(ws + L.sxs); a.ub = (const uint4*)(ws + L.ub); a.uinv = (const float*)(ws + L.ubi); a.U = U;
+    a.sxs = (float*)(ws + L.sxs); a.ub = (const uint4*)(ws + L.ub); a.uinv = (const float*)(ws + L.ubi);
     a.db_part = dbp; a.dh0 = dh0; a.dc0 = dc0; a.ctl = ctl;
     if (d->step_clock) a.clk = (long long*)d->step_clock + (size_t)512 * T * 4;
     if ((rc = hip_status(launch_lev_bwd(a, p.NP, p.KS, lev_grid(p), st)))) return rc;

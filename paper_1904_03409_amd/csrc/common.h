@@ -274,6 +274,10 @@ __device__ __forceinline__ int opaque(int v) {
   asm volatile("" : "+v"(v));
   return v;
 }
+// Keeps v's register from being used again before this point. The compiler waits for all loads before it
+// reuses the register of one that some path has not waited for (group_peek's value); between
+// LDS DMAs that wait is for each DMA in turn.
+__device__ __forceinline__ void hold(uint32_t v) { asm volatile("" ::"v"(v)); }
 // Largest of 16 lanes (a DPP row), in every one of them.
 __device__ __forceinline__ float max16(float m) {
   auto dpp = [](float v, auto ctrl) {

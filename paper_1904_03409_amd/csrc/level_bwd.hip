@@ -272,8 +272,8 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
     stamp(d, 1);
     group_arrive(bar);
     int c0_next = 0, n0_next = 0;
+    const uint32_t seen = group_peek(bar);
     {
-      const uint32_t seen = group_peek(bar);
       if (d > 1) {
         const int n0 = uni(i0_next);
         ics_r = prefetch_ics(n0, i0);
@@ -322,6 +322,7 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
         }
       }
       wait_vm<0>();
+      hold(seen);
       if (kLate && row0 == i0 && d > 1) prefetch(c0_next, c0);
       f32x4 sum[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
       // (KS = 2: the one chunk of an odd wave is an odd one)
@@ -349,6 +350,21 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
             for (int q = 0; q < 4; ++q) sum[t][q] += (acc[t][q] * sgn + lo[t][q]) * xs[x];
         }
       }
+      if constexpr (NP == 2) {
+        // NaN results once more from the first planes (split.h: mfma_rec_first)
+        if (__ballot(l16 < nr && (has_nan(sum[0]) || has_nan(sum[1])))) {
+#pragma unroll
+          for (int t = 0; t < 2; ++t) {
+            f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int c = 0; c < KH; ++c)
+              mfma_rec_first(c, ub[t][c][0], *(const uint4*)(reg + (l16 * SG + ((4 * c + lq) ^ sw(l16))) * 16), v);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              if (sum[t][q] != sum[t][q] && !__builtin_isfinite(v[q])) sum[t][q] = v[q] * sgn;
+          }
+        }
+      }
       if (row0 + 16 < i1) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the slices have been read
         issue(row0 + 16);
@@ -363,17 +379,6 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
 #pragma unroll
           for (int x = 0; x < 8; ++x) v += red[(x * 16 + r) * RLD + uu];
           v *= ui;
-          if constexpr (NP == 2) {
-            // NaN: an infinite operand has no second plane (its products with planes of both signs
-            // give NaN where the fp32 product is infinite); once more from the values
-            if (v != v) {
-              const uint16_t* x = a.sx + (size_t)(row0 + r) * H4s;
-              v = 0.f;
-              for (int n = 0; n < H4; ++n)
-                v = fmaf(rec_ldexp(rec_value(x[n], x[a.xplane + n]) * a.sxs[(size_t)(row0 + r) * NW + n / 128], kDaExp),
-                         a.U[(size_t)u * H4 + perm_to_orig(n, H)], v);
-            }
-          }
           const int x = row0 + r - i0;
           if (x < kLevKeep) eg_out[x * 32 + uu] += v;
           else a.eg[(size_t)(row0 + r) * H + u] += v;

@@ -81,7 +81,6 @@ struct LevBwdArgs {
   uint16_t* sx; size_t xplane;  // recurrent planes of the children's dA sums: [NP][N0 + B][H4s]
   float* sxs;                   // [N0 + B][NW]: inverse scale of a row's 128 columns of a workgroup (fp32 mode)
   const uint4* ub; const float* uinv;   // U^T fragments and the inverse scales of their units (k_prep_bwd); kDaExp
-  const float* U;
   float* db_part;               // [G][4H]
   float* dh0; float* dc0;
   uint32_t* ctl;

@@ -115,11 +115,6 @@ __device__ __forceinline__ int rec_exp(float m) {
 }
 __device__ __forceinline__ float rec_scale(int s) { return __uint_as_float((uint32_t)(127 + s) << 23); }
 __device__ __forceinline__ float rec_ldexp(float v, int e) { return __builtin_amdgcn_ldexpf(v, e); }
-// The value of a plane pair.
-__device__ __forceinline__ float rec_value(uint16_t a, uint16_t b) {
-  return (float)__builtin_bit_cast(_Float16, a) + (float)__builtin_bit_cast(_Float16, b);
-}
-
 // acc += the products of K chunk c. fp32 mode: the first plane of A is stored negated in odd chunks
 // and its products subtracted, so that what the MFMA cuts off, always towards minus infinity,
 // cancels between chunks; those of the second plane gather in lo.

@@ -68,3 +68,38 @@ def test_infinite_initial_state(oracle_mod, H):
     a1 = oracle_mod.alg1(wl)
     for k in ("h_cell", "c_cell"):
         _same(getattr(r, k).cpu().numpy(), a1[k], k)
+
+
+def _backward(oracle_mod, wl, keys=("dx", "dh0", "dc0", "dW", "dU")):
+    import torch
+    r = _forward(wl)
+    r.backward()
+    torch.cuda.synchronize()
+    got, ref = r.results(), oracle_mod.run(wl)
+    for k in keys:
+        _same(got[k], ref[k], k)
+    return ref
+
+
+@pytest.mark.parametrize("H", [36, 100, 130, 500])
+def test_infinite_upstream_gradient(oracle_mod, H):
+    """Infinite gradients of two steps late in the sequence: their nodes' ancestors get infinities
+    and NaN, the others' gradients stay."""
+    need_gpu()
+    T, B = 400, 2
+    print(f"[gpu] infinite dh_top, H={H}", flush=True)
+    wl = wk.custom(T=T, B=B, I=12, H=H, seed=H, ops=_ops(T, B), wscale=0.3 if H < 300 else 0.1, random_state=True)
+    wl.dh_top[333, 0, 4] = np.inf                        # (t % 8 == 5: the child of a state)
+    wl.dh_top[213, 0, H - 1] = -np.inf
+    ref = _backward(oracle_mod, wl)
+    assert not np.isfinite(ref["dx"][333, 0]).any() and np.isfinite(ref["dx"][:, 1]).all()
+
+
+@pytest.mark.parametrize("H", [36, 130])
+def test_infinite_weight_backward(oracle_mod, H):
+    need_gpu()
+    T, B = 200, 2
+    print(f"[gpu] infinite U, backward, H={H}", flush=True)
+    wl = wk.custom(T=T, B=B, I=12, H=H, seed=H, ops=_ops(T, B), wscale=0.3, random_state=True)
+    wl.U[5, 3 * H + 7] = np.inf
+    _backward(oracle_mod, wl, keys=("dx", "dh0", "dc0"))
