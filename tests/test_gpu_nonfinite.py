@@ -70,7 +70,7 @@ def test_infinite_initial_state(oracle_mod, H):
         _same(getattr(r, k).cpu().numpy(), a1[k], k)
 
 
-def _backward(oracle_mod, wl, keys=("dx", "dh0", "dc0", "dW", "dU")):
+def _backward(oracle_mod, wl, keys=("dx", "dh0", "dc0", "dW", "dU", "db")):
     import torch
     r = _forward(wl)
     r.backward()
