@@ -33,6 +33,9 @@ struct TnArgs {
   float* part; size_t split_stride;  // [splits][I + H][4H]
 };
 
+// Whether a plane of state rows is past the reach of a buffer descriptor and its 32-bit offsets
+constexpr bool tn_far(int rows, int ld) { return (size_t)rows * (size_t)ld * 2 > 0xffffffffu; }
+
 // Block tiles: rows x columns, K step, by the row tiles of 16 per wave (MI: nt_mi, or in k_nt one to
 // three quarters of it; the smallest has room for K steps of 64 in fp32 mode too)
 constexpr int nt_mi(int S) { return S == 3 ? 4 : 8; }

@@ -321,7 +321,9 @@ __global__ void __launch_bounds__(512, 2) k_nt(NtArgs g) {
 // LDS by transposing reads (four k of a column per lane and read). Rows of a stage are whole block
 // widths; granule c of row k sits at c ^ 2 p(k), p = k & 3 with bit 3 of k above it, so that the eight
 // rows that half a wave reads at once fall into different banks.
-template <int S>
+// FAR: the state rows take more than a descriptor's 4 GiB (H of 1 or 2, T*B near 2^28): they are loaded
+// with 64-bit addresses and stored to LDS.
+template <int S, bool FAR>
 __global__ void __launch_bounds__(512, 2) k_tn(TnArgs g) {
   constexpr int MI = nt_mi(S), BM = nt_bm(S, MI), BN = nt_bn(S), BK = nt_bk(S, MI);
   constexpr int NJ = 4, WN = BN / (16 * NJ);
@@ -374,6 +376,14 @@ __global__ void __launch_bounds__(512, 2) k_tn(TnArgs g) {
       for (int i = 0; i < IA; ++i) {
         if ((s * (IA + IB) + i) % parts != part) continue;
         const int L = (i * 8 + wave) * 64 + lane, kr = L / AG, col = m0 + 8 * ((L % AG) ^ sw2(kr));
+        if constexpr (FAR) {
+          if (!is_x) {
+            uint4 v = {0u, 0u, 0u, 0u};
+            if (arow[i] >= 0 && col < lda) v = *(const uint4*)(ab + (size_t)arow[i] * lda + col);
+            *(uint4*)(st + s * APL + L * 16) = v;
+            continue;
+          }
+        }
         const uint32_t row = (uint32_t)(is_x ? arow[i] - k0 : arow[i]);
         bdma16(ra, (arow[i] >= 0 && col < lda) ? (row * (uint32_t)lda + (uint32_t)col) * 2u : kOOB, 0u,
                lds_addr(st + s * APL + (i * 8 + wave) * 1024));
@@ -528,9 +538,9 @@ hipError_t launch_nt(const NtArgs& g, int S, int epi, hipStream_t st) {
 #undef CASE
   return hipErrorInvalidValue;
 }
-template <int S>
+template <int S, bool FAR>
 static hipError_t launch_tn_t(const TnArgs& g, hipStream_t st) {
-  auto kern = k_tn<S>;
+  auto kern = k_tn<S, FAR>;
   constexpr int shm = (int)nt_lds(S, nt_mi(S));
   const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, shm);
   if (e != hipSuccess) return e;
@@ -538,4 +548,8 @@ static hipError_t launch_tn_t(const TnArgs& g, hipStream_t st) {
   hipLaunchKernelGGL(kern, dim3(tiles * g.splits), dim3(512), shm, st, g);
   return hipGetLastError();
 }
-hipError_t launch_tn(const TnArgs& g, int S, hipStream_t st) { return S == 3 ? launch_tn_t<3>(g, st) : launch_tn_t<1>(g, st); }
+hipError_t launch_tn(const TnArgs& g, int S, hipStream_t st) {
+  const bool far = tn_far(g.hrows, g.ldh);
+  if (S == 3) return far ? launch_tn_t<3, true>(g, st) : launch_tn_t<3, false>(g, st);
+  return far ? launch_tn_t<1, true>(g, st) : launch_tn_t<1, false>(g, st);
+}

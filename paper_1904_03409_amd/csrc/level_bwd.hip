@@ -107,7 +107,7 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
     }
 #pragma unroll
     for (int s = 0; s < S; ++s) {
-      bf16_t* dst = at32(a.dap + s * a.dplane, 2u * ((uint32_t)c * (uint32_t)H4s + 4u * ou));
+      bf16_t* dst = (bf16_t*)((char*)(a.dap + s * a.dplane) + lev_da_off<NP>(c, H4s, ou));
       *(uint2*)dst = uint2{(uint32_t)p[0][s] | ((uint32_t)p[1][s] << 16), (uint32_t)p[2][s] | ((uint32_t)p[3][s] << 16)};
       if (ou == H - 1 && (H & 1)) *(uint2*)(dst + 4) = uint2{0u, 0u};   // row padding
     }
@@ -203,7 +203,7 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
               }
 #pragma unroll
               for (int s = 0; s < S; ++s) {
-                bf16_t* dst = at32(a.dap + s * a.dplane, 2u * ((uint32_t)c * (uint32_t)H4s + 4u * u));
+                bf16_t* dst = (bf16_t*)((char*)(a.dap + s * a.dplane) + lev_da_off<NP>(c, H4s, u));
                 *(uint2*)dst =
                     uint2{(uint32_t)p[0][s] | ((uint32_t)p[1][s] << 16), (uint32_t)p[2][s] | ((uint32_t)p[3][s] << 16)};
                 if (u == H - 1 && (H & 1)) *(uint2*)(dst + 4) = uint2{0u, 0u};   // row padding

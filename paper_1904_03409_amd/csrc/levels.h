@@ -24,6 +24,15 @@ constexpr int kLevThreads = 512;
 __host__ __device__ inline int lev_bg(int B, int G, int g) { return B / G + (g < B % G ? 1 : 0); }
 __host__ __device__ inline int lev_goff(int B, int G, int g) { return g * (B / G) + (g < B % G ? g : B % G); }
 
+// Byte offset of a push node's dA entries (unit u) in a plane. fp32 mode (NP = 2): 32 bits hold it, because T*B*16H
+// bytes do (the entry points' limit) and a row has 8H, padded to 16 bytes. bf16 mode: the limit is T*B*8H,
+// and the padding of an odd H (H = 3: 32 bytes a row instead of 24) takes a plane past 4 GiB.
+template <int NP>
+__host__ __device__ inline size_t lev_da_off(int c, int H4s, int u) {
+  if (NP == 2) return 2u * ((uint32_t)c * (uint32_t)H4s + 4u * (uint32_t)u);
+  return 2 * ((size_t)c * (size_t)H4s + 4 * (size_t)u);
+}
+
 // Index arrays written by k_plan.
 struct LevIdx {
   int32_t* order;    // [N0]: step t*B + b of node i (i < P); of the leaves, by group, element and time (P <= i < N0)
