@@ -226,6 +226,12 @@ LevIdx idx_of(char* ws, const Layout& L) {
   x.gslot = (int32_t*)(ws + L.gslot);
   return x;
 }
+// Names the sizes of a schedule (FNV-1a); never 0.
+uint64_t plan_key(const slstm_dims* d, int G) {
+  uint64_t h = 1469598103934665603ull;
+  for (int v : {d->T, d->B, d->I, d->H, d->precision, G}) h = (h ^ (uint32_t)v) * 1099511628211ull;
+  return h | 1;
+}
 int spin_of(const slstm_dims* d) { return d->spin_limit > 0 ? d->spin_limit : kDefaultSpin; }
 // workgroups of a recurrent kernel: every XCD takes the workgroups of its share of the groups
 int lev_grid(const Plan& p) { return 8 * p.NW * ((p.G + 7) / 8); }
@@ -317,6 +323,7 @@ int fwd_impl(const slstm_dims* d, const Plan& p, const Layout& L, bool keep, con
     a.T = T; a.B = B; a.G = p.G; a.cap = L.cap;
     a.ops = ops; a.ptr = ptr; a.top = top; a.ix = ix;
     a.cnt = (int32_t*)(ws + L.cnt); a.elem = (int32_t*)(ws + L.elem); a.walk = (int32_t*)(ws + L.walk); a.ctl = ctl;
+    a.key = keep ? plan_key(d, p.G) : 0;
     if (L.walk_lds) {
       const int waves = (int)std::min<size_t>(16, 147456 / L.walk_lds);
       const size_t shm = waves * L.walk_lds;
@@ -506,6 +513,7 @@ int stacklstm_bwd(const slstm_dims* d, const float* x, const int8_t* ops, const 
   }
 
   const int S = p.S, N0 = T * B;
+  const uint64_t key = plan_key(d, p.G);
   const LevIdx ix = idx_of(ws, L);
   // control words, U^T fragments, interval sums of the upstream gradients
   float* gf = (float*)(ws + L.gf);
@@ -514,9 +522,9 @@ int stacklstm_bwd(const slstm_dims* d, const float* x, const int8_t* ops, const 
     PrepBwdArgs a;
     a.T = T; a.B = B; a.H = H; a.G = p.G; a.NW = p.NW; a.KS = p.KS;
     a.U = U; a.ub = (uint4*)(ws + L.ub); a.uinv = (float*)(ws + L.ubi);
-    a.gslot = ix.gslot; a.keep_errors = keep_errors;
-    auto prep = [&](int n_u, const float* src, float* sums, uint32_t* zero) {
-      a.n_u = n_u; a.d = src; a.sums = sums; a.ctl = zero;
+    a.gslot = ix.gslot; a.ctl = ctl; a.key = key; a.keep_errors = keep_errors;
+    auto prep = [&](int n_u, const float* src, float* sums, int clear) {
+      a.n_u = n_u; a.d = src; a.sums = sums; a.clear = clear;
       const bool vec = H % 4 == 0 && al16(src);
       const size_t parts = (H + (vec ? 255 : 63)) / (vec ? 256 : 64), segs = (T + 31) / 32;
       const dim3 grid(n_u + (B * parts * segs + 3) / 4);
@@ -525,8 +533,8 @@ int stacklstm_bwd(const slstm_dims* d, const float* x, const int8_t* ops, const 
       else if (vec)       hipLaunchKernelGGL((k_prep_bwd<1, 4>), grid, dim3(256), 0, st, a);
       else                hipLaunchKernelGGL((k_prep_bwd<1, 1>), grid, dim3(256), 0, st, a);
     };
-    prep(p.NW * 16, dh_top, gf, ctl);
-    if (gc) prep(0, dc_top, gc, nullptr);
+    prep(p.NW * 16, dh_top, gf, 1);
+    if (gc) prep(0, dc_top, gc, 0);
   }
   uint16_t* dap = (uint16_t*)(ws + L.dap);
   const size_t dplane = (size_t)N0 * L.H4s;
@@ -542,7 +550,7 @@ int stacklstm_bwd(const slstm_dims* d, const float* x, const int8_t* ops, const 
     a.gf = gf; a.gc = gc; a.eg = (float*)(ws + L.eg); a.dcs = (float*)(ws + L.dcs);
     a.dap = dap; a.dplane = dplane; a.sx = (uint16_t*)(ws + L.hu); a.xplane = (size_t)(N0 + B) * L.H4s;
     a.sxs = (float*)(ws + L.sxs); a.ub = (const uint4*)(ws + L.ub); a.uinv = (const float*)(ws + L.ubi);
-    a.db_part = dbp; a.dh0 = dh0; a.dc0 = dc0; a.ctl = ctl;
+    a.db_part = dbp; a.dh0 = dh0; a.dc0 = dc0; a.ctl = ctl; a.key = key;
     if (d->step_clock) a.clk = (long long*)d->step_clock + (size_t)512 * T * 4;
     if ((rc = hip_status(launch_lev_bwd(a, p.NP, p.KS, lev_grid(p), st)))) return rc;
   }
@@ -556,13 +564,13 @@ int stacklstm_bwd(const slstm_dims* d, const float* x, const int8_t* ops, const 
     g.X = (const uint16_t*)(ws + L.xs); g.xplane = (size_t)N0 * L.Ip; g.ldx = L.Ip;
     g.Hp = (const uint16_t*)(ws + (S == 3 ? L.h3 : L.hq)); g.hplane = (size_t)(N0 + B) * L.Hs; g.ldh = L.Hs; g.hrows = N0 + B;
     g.D = dap; g.dplane = dplane; g.ldd = L.H4s;
-    g.opar = ix.opar; g.ctl = ctl; g.part = part; g.split_stride = (size_t)(I + H) * 4 * H;
+    g.opar = ix.opar; g.ctl = ctl; g.key = key; g.part = part; g.split_stride = (size_t)(I + H) * 4 * H;
     if ((rc = hip_status(launch_tn(g, S, st)))) return rc;
     ReduceArgs r;
     r.part = part; r.splits = g.splits; r.stride = g.split_stride; r.db_part = dbp; r.groups = p.G; r.I = I; r.H = H;
     r.dW = dW; r.dU = dU; r.db = db;
     r.T = T; r.B = B; r.n_red = grid1d((size_t)(I + H + 1) * H);
-    r.ops = ops; r.top = top; r.order = ix.order; r.ctl = ctl;
+    r.ops = ops; r.top = top; r.order = ix.order; r.ctl = ctl; r.key = key;
     const int checks = (int)std::min<size_t>(((size_t)N0 + 1023) / 1024, 1024);
     hipLaunchKernelGGL(k_reduce_grads, dim3(r.n_red + checks), dim3(256), 0, st, r);
   }
@@ -575,7 +583,7 @@ int stacklstm_bwd(const slstm_dims* d, const float* x, const int8_t* ops, const 
     g.N = I; g.K = L.H4s; g.N0 = N0; g.lo = 0; g.hi = N0;
     g.A = dap; g.aplane = dplane; g.lda = L.H4s;
     g.B = (const uint16_t*)(ws + L.wp); g.bplane = (size_t)I * L.H4s; g.ldb = L.H4s;
-    g.ctl = ctl; g.C = dx; g.ldc = I; g.order = ix.order; g.H = H;
+    g.ctl = ctl; g.key = key; g.C = dx; g.ldc = I; g.order = ix.order; g.H = H;
     if ((rc = hip_status(launch_nt(g, S, NT_DX, st)))) return rc;
   }
   if ((rc = hip_status(hipGetLastError()))) return rc;

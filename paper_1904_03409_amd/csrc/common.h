@@ -26,6 +26,7 @@ enum {
   CTL_TIMEOUT = 3,       // set when a wait ran out of spins (reported as SLSTM_ETIMEOUT)
   CTL_NPUSHF = 5,        // number of push steps (counted by k_plan in the forward)
   CTL_BADIDX = 6,        // set when a kernel read a producer index outside its valid range
+  CTL_KEY = 8,           // 2 words: the sizes whose schedule the work space holds (k_plan), else 0
   CTL_XCC_SLOT = 16,     // 16 per-XCC slot counters (forward kernel)
   CTL_XCC_SLOT_B = 32,   // 16 per-XCC slot counters (backward kernel)
   CTL_BAR_F = 64,        // forward group barrier counters, one 64-byte line per group
@@ -58,6 +59,13 @@ __device__ __forceinline__ void zero_ctl_bwd(uint32_t* ctl, int keep_errors) {
       ctl[CTL_BADIDX] = 0u;
     }
   }
+}
+
+// Whether the work space holds the schedule of a forward of these sizes. A backward takes its indices
+// from there; in a work space that no such forward wrote they are anything, so its kernels leave
+// without following one, and the call reports SLSTM_EINDEX.
+__device__ __forceinline__ bool has_plan(const uint32_t* ctl, uint64_t key) {
+  return ctl[CTL_KEY] == (uint32_t)key && ctl[CTL_KEY + 1] == (uint32_t)(key >> 32);
 }
 
 // Gate-interleaved ("permuted") column order used inside the library: column 4*u + k

@@ -12,7 +12,7 @@ struct NtArgs {
   int lo, hi, leaves, N0;
   const uint16_t* A; size_t aplane; int lda;
   const uint16_t* B; size_t bplane; int ldb;
-  const uint32_t* ctl;               // CTL_NPUSHF
+  const uint32_t* ctl; uint64_t key; // CTL_NPUSHF; NT_DX: CTL_KEY
   // NT_XW: C[i][N] + bias; NT_DX: C[order[i]][N], and 0 in the rows of the leaves
   float* C; int ldc;
   const float* bias; int H;          // caller's column order
@@ -29,7 +29,7 @@ struct TnArgs {
   const uint16_t* Hp; size_t hplane; int ldh; int hrows;
   const uint16_t* D; size_t dplane; int ldd;
   const int32_t* opar;
-  const uint32_t* ctl;
+  const uint32_t* ctl; uint64_t key;
   float* part; size_t split_stride;  // [splits][I + H][4H]
 };
 
@@ -53,7 +53,7 @@ struct ReduceArgs {
   float* dW; float* dU; float* db;
   int T, B, n_red;                   // n_red: blocks of the sums; the rest check
   const int8_t* ops; const int32_t* top; const int32_t* order;
-  uint32_t* ctl;
+  uint32_t* ctl; uint64_t key;
 };
 
 hipError_t launch_nt(const NtArgs& g, int S, int epi, hipStream_t st);

@@ -279,6 +279,7 @@ __global__ void __launch_bounds__(512, 2) k_nt(NtArgs g) {
   // the barrier, B fragments).
   // With 256 rows alone the dx product of 18 k nodes x 256 inputs ran on 144 CUs (176 us, now 141),
   // that of 2.2 k nodes x 128 inputs on 9 (73 us, now 25).
+  if (EPI == NT_DX && !has_plan(g.ctl, g.key)) return;
   const int P = (int)g.ctl[CTL_NPUSHF];
   const int r_lo = g.leaves ? max(g.lo, P) : g.lo, r_hi = g.leaves ? g.hi : min(g.hi, P);
   const int NTL = (g.N + BN - 1) / BN, R = max(r_hi - r_lo, 0);
@@ -341,7 +342,7 @@ __global__ void __launch_bounds__(512, 2) k_tn(TnArgs g) {
   const int z = lid / per, rem = lid % per, tm = rem % MTL, n0 = (rem / MTL) * BN;
   const bool is_x = tm < g.xt;
   const int m0 = (is_x ? tm : tm - g.xt) * BM, mlim = is_x ? g.I : g.H;   // columns of the operand array
-  const int P = (int)g.ctl[CTL_NPUSHF];
+  const int P = has_plan(g.ctl, g.key) ? (int)g.ctl[CTL_NPUSHF] : 0;
   const int chunk = ((P + g.splits - 1) / g.splits + BK - 1) / BK * BK;
   const int kbeg = min(P, z * chunk), kend = min(P, kbeg + chunk);
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6);
@@ -489,6 +490,7 @@ __global__ void __launch_bounds__(512, 2) k_tn(TnArgs g) {
 __global__ void __launch_bounds__(256) k_reduce_grads(ReduceArgs a) {
   const int H = a.H, H4 = 4 * H, I = a.I;
   if ((int)blockIdx.x >= a.n_red) {
+    if (!has_plan(a.ctl, a.key)) return;
     const size_t P = a.ctl[CTL_NPUSHF], n = (size_t)a.T * a.B, step = (size_t)(gridDim.x - a.n_red) * 256;
     bool bad = false;
     for (size_t i = (size_t)(blockIdx.x - a.n_red) * 256 + threadIdx.x; i < n; i += step) {

@@ -37,6 +37,7 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
   float* red = reinterpret_cast<float*>(lsm + lev_bwd_region(NP, KS));        // [8][16][RLD] partials of the waves
   float* keep = red + 8 * 16 * RLD;                         // [2][2][kLevKeep][32] eg and dcs of a level's first nodes
   __shared__ int s_g, s_w, s_flag, s_ics[kLevPars + 1];
+  if (!has_plan(a.ctl, a.key)) return;
   claim_group_slot(a.ctl + CTL_XCC_SLOT_B, a.G, a.NW, &s_g, &s_w);
   const int g = uni(s_g), w = uni(s_w);
   if (g < 0) return;

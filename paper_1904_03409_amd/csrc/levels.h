@@ -60,6 +60,7 @@ struct PlanArgs {
   int32_t* elem;                // [3][B]: deepest level, pushes, leaf offset of an element
   int32_t* walk;                // [G][2][cap] when the walk arrays do not fit in LDS
   uint32_t* ctl;
+  uint64_t key;                 // of the sizes (CTL_KEY)
 };
 
 struct LevFwdArgs {
@@ -92,7 +93,7 @@ struct LevBwdArgs {
   const uint4* ub; const float* uinv;   // U^T fragments and the inverse scales of their units (k_prep_bwd); kDaExp
   float* db_part;               // [G][4H]
   float* dh0; float* dc0;
-  uint32_t* ctl;
+  uint32_t* ctl; uint64_t key;
   long long* clk;
 };
 

@@ -184,7 +184,11 @@ __global__ void __launch_bounds__(1024) k_plan(PlanArgs a) {
   if (tid == 0) {
     a.ix.gmax[g] = D;
     atomicMax(&a.ctl[CTL_MAXDEPTH], (uint32_t)D);
-    if (g == 0) a.ctl[CTL_NPUSHF] = (uint32_t)P;
+    if (g == 0) {
+      a.ctl[CTL_NPUSHF] = (uint32_t)P;
+      a.ctl[CTL_KEY] = (uint32_t)a.key;
+      a.ctl[CTL_KEY + 1] = (uint32_t)(a.key >> 32);
+    }
   }
 
   // phase 2: first node id of (depth, element), depth-major; leaf offset of each element

@@ -31,5 +31,5 @@ struct PrepBwdArgs {
   const float* U;
   uint4* ub; float* uinv;
   const float* d; const int32_t* gslot; float* sums;   // upstream gradient, its slots, the sums
-  uint32_t* ctl; int keep_errors;  // control words to clear (null: not by this launch)
+  uint32_t* ctl; uint64_t key; int clear, keep_errors;   // clear: this launch clears the control words
 };

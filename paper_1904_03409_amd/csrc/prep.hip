@@ -228,7 +228,12 @@ template <int S, int V>
 __global__ void __launch_bounds__(256) k_prep_bwd(PrepBwdArgs a) {
   constexpr int NP = S == 3 ? 2 : 1;
   const int H = a.H, H4 = 4 * H, tid = threadIdx.x, lane = tid & 63;
-  if (blockIdx.x == 0 && a.ctl) zero_ctl_bwd(a.ctl, a.keep_errors);
+  const bool ok = has_plan(a.ctl, a.key);
+  if (blockIdx.x == 0 && a.clear) {
+    zero_ctl_bwd(a.ctl, a.keep_errors);
+    if (!ok && tid == 0) raise_badidx(a.ctl);
+  }
+  if (!ok) return;
   if (blockIdx.x < (unsigned)a.n_u) {
     const int blk = blockIdx.x, wave = blk & 7, tile = (blk >> 3) & 1, w = blk >> 4, u0 = 32 * w + 16 * tile, KH = a.KS / 2;
     __shared__ float s_sc[16];

@@ -169,3 +169,46 @@ def test_deferred_status():
     rb.dims.defer_status = 0
     assert rb.forward(check=False) == 0                                      # resets: valid ops now
     assert stacklstm_sync_status(rb.workspace) == 0
+
+
+def _bwd_code(r, ws):
+    from paper_1904_03409_amd import stacklstm as s
+    return s.stacklstm_bwd(r.dims, r.x, r.ops, r.W, r.U, r.h0, r.c0, r.h_cell, r.c_cell, r.top, ws, r.dh_top, r.dc_top,
+                           r.dx, r.dW, r.dU, r.db, r.dh0, r.dc0, check=False)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_backward_without_its_forward(precision):
+    """A work space that holds no forward of the backward's sizes (never written, or by a forward of
+    other sizes) gives SLSTM_EINDEX, also deferred; the kernels follow none of its indices. The forward
+    and backward then run as usual."""
+    need_gpu()
+    from paper_1904_03409_amd import stacklstm as s
+    from paper_1904_03409_amd.stacklstm import DeviceRun
+    wl = wk.custom(T=33, B=7, I=12, H=40, seed=1, dc_top=True)
+    r = DeviceRun.from_workload(wl, precision=precision)
+    assert r.forward(check=False) == 0 and r.backward(check=False) == 0
+    torch.cuda.synchronize()
+    want = r.results()
+    for fill in (0, 255):
+        ws = torch.full_like(r.workspace, fill)
+        print(f"[gpu] backward on a work space of {fill}, precision={precision}", flush=True)
+        assert _bwd_code(r, ws) == 8
+        assert s.stacklstm_sync_status(ws) == 8
+    other = DeviceRun.from_workload(wk.custom(T=30, B=8, I=12, H=40, seed=2), precision=precision)
+    ws = torch.zeros(max(r.workspace.numel(), other.workspace.numel()), dtype=torch.uint8, device="cuda")
+    other.workspace = ws
+    assert other.forward(check=False) == 0
+    print(f"[gpu] backward after another forward, precision={precision}", flush=True)
+    assert _bwd_code(r, ws) == 8
+    r.workspace = ws
+    assert r.forward(check=False) == 0
+    other.dims.defer_status = 1
+    assert _bwd_code(other, ws) == 0
+    torch.cuda.synchronize()
+    assert s.stacklstm_sync_status(ws) == 8
+    assert r.forward(check=False) == 0 and r.backward(check=False) == 0
+    torch.cuda.synchronize()
+    got = r.results()
+    for k in want:
+        assert np.array_equal(got[k], want[k]), k
