@@ -36,8 +36,44 @@ __device__ __forceinline__ void tile_step(const bf16x8 (&a)[MI][S], const bf16x8
   }
 }
 
-__device__ __forceinline__ float plane_sum(const uint16_t* p, size_t plane, size_t i) {
-  return bf16_bits_to_f32(p[i]) + bf16_bits_to_f32(p[plane + i]) + bf16_bits_to_f32(p[2 * plane + i]);
+// fp32 mode: an infinite operand has no second and third plane, and products of infinities with planes of
+// both signs or with zero planes give NaN where the fp32 product is infinite. The sum of the first
+// planes' products is infinite or NaN as the fp32 sum is. So a wave with NaN among its results
+// takes those from another pass over K with the first planes, straight from memory: half the
+// time of the tile again at most. (One lane through all of K for each NaN: large training step with a NaN
+// in every gradient 236 ms instead of 2.7.) frag(k, a, b): the fragments of K step k.
+__device__ __forceinline__ bool is_nan(float v) { return v != v; }
+template <int MI, int NJ, typename F>
+__device__ __forceinline__ void redo_nan(f32x4 (&acc)[MI][NJ], int kbeg, int kend, F frag) {
+  bool bad = false;
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) bad |= is_nan(acc[i][j][q]);
+  if (!__ballot(bad)) return;
+  f32x4 v[MI][NJ];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) v[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+  for (int k = kbeg; k < kend; k += 32) {
+    bf16x8 a[MI], b[NJ];
+    frag(k, a, b);
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) v[i][j] = mfma_bf16_16x16x32(b[j], a[i], v[i][j]);
+  }
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (is_nan(acc[i][j][q]) && !__builtin_isfinite(v[i][j][q])) acc[i][j][q] = v[i][j][q];
 }
 
 }  // namespace
@@ -137,34 +173,21 @@ __device__ __forceinline__ void nt_tile(const NtArgs& g, int r_lo, int r_hi, int
 
   float* ws = reinterpret_cast<float*>(sm) + wave * (16 * 68);   // 16 rows x 64 columns (+ 4) of this wave
   if constexpr (S == 3) {
-    // An infinite operand has no second and third plane, and products of infinities with planes of
-    // both signs or with zero planes give NaN where the fp32 product is infinite: NaN results are
-    // computed again from the values themselves.
-    bool bad = false;
+    // (rows and columns past the tile's: the last ones', whose results nobody reads)
+    redo_nan<MI, NJ>(acc, 0, g.K, [&](int k, bf16x8 (&a)[MI], bf16x8 (&b)[NJ]) {
+      const int kl = min(k + 8 * lq, g.K - 8);
+      const bool in = k + 8 * lq < g.K;
 #pragma unroll
-    for (int i = 0; i < MI; ++i)
+      for (int i = 0; i < MI; ++i) a[i] = *(const bf16x8*)(A + (size_t)min(16 * (MI * wm + i) + l16, nr - 1) * g.lda + kl);
 #pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) bad |= acc[i][j][q] != acc[i][j][q];
-    if (__ballot(bad)) {
-#pragma unroll
-      for (int i = 0; i < MI; ++i) {
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) *(f32x4*)&ws[l16 * 68 + j * 16 + 4 * lq] = acc[i][j];
-        for (int e = 0; e < 16; ++e) {
-          float& v = ws[l16 * 68 + (e >> 2) * 16 + 4 * lq + (e & 3)];
-          const int m = 16 * (MI * wm + i) + l16, n = 16 * (NJ * wn + (e >> 2)) + 4 * lq + (e & 3);
-          if (v == v || m >= nr || n >= nc) continue;
-          float t = 0.f;
-          for (int k = 0; k < g.K; ++k)
-            t = fmaf(plane_sum(A, g.aplane, (size_t)m * g.lda + k), plane_sum(Bp, g.bplane, (size_t)n * g.ldb + k), t);
-          v = t;
-        }
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) acc[i][j] = *(const f32x4*)&ws[l16 * 68 + j * 16 + 4 * lq];
+      for (int j = 0; j < NJ; ++j) {
+        b[j] = *(const bf16x8*)(Bp + (size_t)min(16 * (NJ * wn + j) + l16, nc - 1) * g.ldb + kl);
+        if (!in) b[j] = bf16x8{};
       }
-    }
+      if (!in)
+#pragma unroll
+        for (int i = 0; i < MI; ++i) a[i] = bf16x8{};
+    });
   }
 
   float bias[NJ][4];
@@ -445,6 +468,32 @@ __global__ void __launch_bounds__(512, 2) k_tn(TnArgs g) {
     }
     if (more) rows(k0 + 2 * BK);
   }
+  if constexpr (S == 3) {
+    redo_nan<MI, NJ>(acc, kbeg, kend, [&](int k0, bf16x8 (&a)[MI], bf16x8 (&b)[NJ]) {
+      uint16_t va[MI][8], vb[NJ][8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int k = min(k0 + 8 * lq + e, kend - 1);
+        const bool in = k0 + 8 * lq + e < kend;
+        const uint16_t* ar = A + (size_t)(is_x ? k : g.opar[k]) * lda;
+        const uint16_t* dr = g.D + (size_t)k * g.ldd;
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+          const uint16_t v = ar[min(m0 + 16 * (MI * wm + i) + l16, mlim - 1)];
+          va[i][e] = in ? v : (uint16_t)0;
+        }
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          const uint16_t v = dr[min(n0 + 16 * (NJ * wn + j) + l16, g.H4 - 1)];
+          vb[j][e] = in ? v : (uint16_t)0;
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < MI; ++i) __builtin_memcpy(&a[i], va[i], 16);
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) __builtin_memcpy(&b[j], vb[j], 16);
+    });
+  }
   __syncthreads();
   float* ws = reinterpret_cast<float*>(sm) + wave * (16 * 68);
   float* out = g.part + (size_t)z * g.split_stride + (size_t)(is_x ? 0 : g.I) * g.H4;
@@ -453,27 +502,6 @@ __global__ void __launch_bounds__(512, 2) k_tn(TnArgs g) {
 #pragma unroll
     for (int j = 0; j < NJ; ++j) *(f32x4*)&ws[l16 * 68 + j * 16 + 4 * lq] = acc[i][j];
     __builtin_amdgcn_wave_barrier();
-    if constexpr (S == 3) {                             // NaN: as in k_nt
-      bool bad = false;
-#pragma unroll
-      for (int j = 0; j < NJ; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) bad |= acc[i][j][q] != acc[i][j][q];
-      if (__ballot(bad)) {
-        for (int e = 0; e < 16; ++e) {
-          float& v = ws[l16 * 68 + (e >> 2) * 16 + 4 * lq + (e & 3)];
-          const int m = m0 + 16 * (MI * wm + i) + l16, n = n0 + 16 * (NJ * wn + (e >> 2)) + 4 * lq + (e & 3);
-          if (v == v || m >= mlim || n >= g.H4) continue;
-          float t = 0.f;
-          for (int k = kbeg; k < kend; ++k) {
-            const int r = is_x ? k : g.opar[k];
-            t = fmaf(plane_sum(A, aplane, (size_t)r * lda + m), plane_sum(g.D, g.dplane, (size_t)k * g.ldd + n), t);
-          }
-          v = t;
-        }
-        __builtin_amdgcn_wave_barrier();
-      }
-    }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const int r = 4 * e + (lane >> 4), m = m0 + 16 * (MI * wm + i) + r, n = n0 + 64 * wn + 4 * l16;

@@ -103,3 +103,50 @@ def test_infinite_weight_backward(oracle_mod, H):
     wl = wk.custom(T=T, B=B, I=12, H=H, seed=H, ops=_ops(T, B), wscale=0.3, random_state=True)
     wl.U[5, 3 * H + 7] = np.inf
     _backward(oracle_mod, wl, keys=("dx", "dh0", "dc0"))
+
+
+@pytest.mark.parametrize("I,H", [(13, 36), (130, 130)])
+@pytest.mark.parametrize("where", ["x", "W"])
+def test_infinite_inputs_of_the_products(oracle_mod, where, I, H):
+    """Infinities in x or W, forward and backward: x W, dW and dx over them (the gates saturate, so
+    the gate gradients they meet are exactly 0 in places: NaN there too)."""
+    need_gpu()
+    T, B = 45, 3
+    print(f"[gpu] infinite {where}, I={I} H={H}", flush=True)
+    wl = wk.custom(T=T, B=B, I=I, H=H, seed=I + H, wscale=0.3 if H < 100 else 0.1, random_state=True)
+    if where == "x":
+        wl.x[2, 0, 3] = np.inf
+        wl.x[30, 1, I - 1] = -np.inf
+    else:
+        wl.W[2, 2 * H + 5] = np.inf
+        wl.W[I - 1, 3 * H + 7] = -np.inf
+    a1 = oracle_mod.alg1(wl)
+    r = _forward(wl)
+    for k in ("h_cell", "c_cell"):
+        _same(getattr(r, k).cpu().numpy(), a1[k], k)
+    _backward(oracle_mod, wl)
+
+
+def test_diverged_step_takes_about_as_long(oracle_mod):
+    """A training step whose gradients are all NaN: every NaN result is repeated on the matrix units
+    (1.1 times the ordinary step; one lane for each result took 40 times)."""
+    need_gpu()
+    import torch
+    from paper_1904_03409_amd.stacklstm import DeviceRun
+    r = DeviceRun.from_workload(wk.make("parser"), precision=0)
+
+    def step():
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        r.forward()
+        r.backward()
+        b.record()
+        b.synchronize()
+        return a.elapsed_time(b)
+
+    plain = min(step() for _ in range(5))
+    r.dh_top.fill_(float("nan"))
+    nan = min(step() for _ in range(5))
+    print(f"[gpu] step {plain:.3f} ms, all NaN {nan:.3f} ms", flush=True)
+    assert np.isnan(r.results()["dW"]).all()
+    assert nan < 5 * plain
