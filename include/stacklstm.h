@@ -135,12 +135,15 @@ int stacklstm_fwd(const slstm_dims* d, const float* x, const int8_t* ops, const 
 /* Allocation-free variant of stacklstm_fwd, for callers that cannot allocate device memory
  * (serving loops and harnesses that forbid allocation): the same arguments, outputs and
  * status read-back, with no work-space argument. Its work space is a static device array of
- * SLSTM_FWD_STATIC_MAX_BYTES bytes, one per GPU, held until the process ends; the call
- * allocates nothing. Dims whose forward work space (the forward's part of
- * stacklstm_workspace_bytes) exceeds it give SLSTM_EWORKSPACE. Every call on a GPU uses that
+ * SLSTM_FWD_STATIC_BYTES bytes, one per GPU, held until the process ends; the call
+ * allocates nothing. Dims are served if
+ *   8448 + 4 B (T + 1) + 4 B + 16 I H + 16 T B H + 16 T B H [+ 2 (T + 1) B H in SLSTM_BF16_GEMM mode]
+ * bytes, each term rounded up to 256, are at most SLSTM_FWD_STATIC_MAX_BYTES; others give
+ * SLSTM_EWORKSPACE. Every call on a GPU uses that
  * GPU's array: calls that overlap on one GPU (two streams, two host threads) race and must
  * be serialised by the caller. A backward cannot follow it (it keeps nothing for one). */
 #define SLSTM_FWD_STATIC_MAX_BYTES ((size_t)128 << 20)
+#define SLSTM_FWD_STATIC_BYTES ((size_t)256 << 20)
 int stacklstm_fwd_static(const slstm_dims* d, const float* x, const int8_t* ops, const float* W, const float* U,
                          const float* b, const float* h0, const float* c0, float* h_cell, float* c_cell, float* h_top,
                          float* c_top, int32_t* ptr, int32_t* top, void* stream);

@@ -16,7 +16,7 @@ __global__ void k_ctl(uint32_t* ctl, int keep_errors, int bwd);
 template <bool LDS> __global__ void k_plan(PlanArgs a);
 template <int S>
 __global__ void k_split_x(const float* x, const int32_t* order, int lo, int hi, int I, int Ip, int vec, bf16_t* out,
-                          size_t plane);
+                          size_t plane, int part, const uint32_t* ctl);
 template <int S> __global__ void k_prep_fwd(PrepFwdArgs a);
 template <int S, int V> __global__ void k_prep_bwd(PrepBwdArgs a);
 template <int V> __global__ void k_gather_top(GatherArgs a);
@@ -104,7 +104,7 @@ int tn_splits(const slstm_dims* d) {
 
 // Work-space layout. It does not depend on the device (group counts as for 32 CUs per XCD).
 struct Layout {
-  size_t ctl, order, opar, cs, loff, gmax, irow, ics, ioff, cidx, kin, gslot, cnt, elem, walk;
+  size_t ctl, order, opar, cs, loff, gmax, ics, ioff, cidx, kin, gslot, cnt, elem, walk;
   size_t wt, wp, uf, ufi, rin, hu, stash, cpn, hq, h3, cn, xs, fwd_end;
   size_t gf, gc, eg, dcs, dap, sxs, ub, ubi, part, dbp, total;
   int Ip, Hs, H4s, cap, G;
@@ -136,22 +136,24 @@ Layout layout(const slstm_dims* d, bool keep, size_t x_budget) {
   L.cs = put(NN * 4);
   L.loff = put((size_t)L.G * (T + 4) * 4);
   L.gmax = put((size_t)kLevMaxGroups * 4);
-  L.irow = put(NN * 4);
-  L.ics = put(NN * 4);
-  L.ioff = put((size_t)L.G * (T + 4) * 4);
-  L.cidx = put(NN * 4);
-  L.kin = put(N0 * 4);
-  L.gslot = put(N0 * 4);
-  L.cnt = put(B * L.cap * 4);
+  L.ics = put(keep ? NN * 4 : 0);
+  L.ioff = put(keep ? (size_t)L.G * (T + 4) * 4 : 0);
+  L.cidx = put(keep ? NN * 4 : 0);
+  L.kin = put(keep ? N0 * 4 : 0);
+  L.gslot = put(keep ? N0 * 4 : 0);
   L.elem = put(3 * B * 4);
-  L.walk = put(L.walk_lds ? 0 : (size_t)L.G * 2 * L.cap * 4);
   L.wt = put(S * 4 * H * L.Ip * 2);
   L.wp = put(keep ? S * I * L.H4s * 2 : 0);
   L.uf = put((size_t)NW * 8 * KS * 64 * NP * 16);
   L.ufi = put((size_t)NW * kLevUnits * 4);
   L.rin = put(B * 4);
-  // x W and h U of the nodes (forward); the exchange rows of the backward
-  L.hu = put(std::max(NN * 4 * H * 4, keep ? NP * NN * L.H4s * 2 : 0));
+  // k_plan's counts and walk arrays; then x W and h U of the nodes (forward); then the exchange rows of the
+  // backward
+  const size_t walk = align256(B * L.cap * 4);
+  L.hu = put(std::max({NN * 4 * H * 4, keep ? NP * NN * L.H4s * 2 : 0,
+                       walk + (L.walk_lds ? 0 : (size_t)L.G * 2 * L.cap * 4)}));
+  L.cnt = L.hu;
+  L.walk = L.hu + walk;
   L.stash = put(keep ? N0 * 4 * H * 4 : 0);
   L.cpn = put(keep ? N0 * H * 4 : 0);
   L.hq = put(NP * NN * L.Hs * 2);
@@ -218,7 +220,6 @@ LevIdx idx_of(char* ws, const Layout& L) {
   x.cs = (int32_t*)(ws + L.cs);
   x.loff = (int32_t*)(ws + L.loff);
   x.gmax = (int32_t*)(ws + L.gmax);
-  x.irow = (int32_t*)(ws + L.irow);
   x.ics = (int32_t*)(ws + L.ics);
   x.ioff = (int32_t*)(ws + L.ioff);
   x.cidx = (int32_t*)(ws + L.cidx);
@@ -346,7 +347,8 @@ int fwd_impl(const slstm_dims* d, const Plan& p, const Layout& L, bool keep, con
   g.B = (uint16_t*)(ws + L.wt); g.bplane = (size_t)4 * H * L.Ip; g.ldb = L.Ip;
   g.ctl = ctl; g.C = hu; g.ldc = 4 * H; g.bias = b; g.H = H; g.order = ix.order;
   g.opar = ix.opar; g.hu = hu; g.cn = cn; g.hcell = h_cell; g.ccell = c_cell;
-  // (all rows of x at once, or in pieces of the step list where the planes of x have less room)
+  // (all rows of x at once, or in pieces of the step list where the planes of x have less room: then
+  // each of the two passes over them makes the planes of its own rows)
   const bool once = L.x_rows >= N0;
   auto x_pass = [&](int epi, bool split) -> int {
     for (int lo = 0; lo < N0; lo += L.x_rows) {
@@ -354,11 +356,11 @@ int fwd_impl(const slstm_dims* d, const Plan& p, const Layout& L, bool keep, con
       g.lo = lo; g.hi = hi; g.leaves = epi == NT_LEAF; g.aplane = (size_t)(hi - lo) * L.Ip;
       if (split) {
         const int vec = I % 4 == 0 && al16(x);
-        const int grid = grid1d((size_t)(hi - lo) * (L.Ip / 8));
+        const int grid = grid1d((size_t)(hi - lo) * (L.Ip / 8)), part = once ? 0 : epi == NT_XW ? 1 : 2;
         if (S == 3)
-          hipLaunchKernelGGL(k_split_x<3>, dim3(grid), dim3(256), 0, st, x, ix.order, lo, hi, I, L.Ip, vec, xs, g.aplane);
+          hipLaunchKernelGGL(k_split_x<3>, dim3(grid), dim3(256), 0, st, x, ix.order, lo, hi, I, L.Ip, vec, xs, g.aplane, part, ctl);
         else
-          hipLaunchKernelGGL(k_split_x<1>, dim3(grid), dim3(256), 0, st, x, ix.order, lo, hi, I, L.Ip, vec, xs, g.aplane);
+          hipLaunchKernelGGL(k_split_x<1>, dim3(grid), dim3(256), 0, st, x, ix.order, lo, hi, I, L.Ip, vec, xs, g.aplane, part, ctl);
       }
       const int r = hip_status(launch_nt(g, S, epi, st));
       if (r) return r;
@@ -409,9 +411,10 @@ bool fwd_args_ok(const slstm_dims* d, const float* x, const int8_t* ops, const f
 
 // Static work space of the allocation-free forward: one copy per GPU, held until the process
 // ends. Host code uses the device address that hipGetSymbolAddress returns for the current
-// device (kept per device), never the array's name. The largest need beside the planes of x among
-// the dims that static_measure admits is 370 MiB (3.7 M steps of one element at H = 1).
-constexpr size_t kScratchBytes = (size_t)448 << 20;
+// device (kept per device), never the array's name. Of the dims that static_measure admits the one with the
+// largest need beside the planes of x takes 242 MiB (3.7 M steps of one element at H = 1 in fp32 mode: state
+// planes padded to 16 bytes).
+constexpr size_t kScratchBytes = SLSTM_FWD_STATIC_BYTES;
 __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 // Bytes that decide whether dims are served from the static work space: the work space of a

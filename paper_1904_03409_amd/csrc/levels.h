@@ -40,9 +40,8 @@ struct LevIdx {
   int32_t* cs;       // [N0 + B]: first push child of a node (its children end where the next node's begin)
   int32_t* loff;     // [G][T + 4]: first node of level d = 1 .. D + 1 of a group (level D + 1 and D + 2: the end)
   int32_t* gmax;     // [G]: deepest level D
-  // internal nodes (with push children), numbered by group, level and node: a group's numbers start
-  // at the count of nodes of the groups before it
-  int32_t* irow;     // [N0 + B]: node of an internal number
+  // For a backward. Internal nodes (with push children) are numbered by group, level and node: a group's
+  // numbers start at the count of nodes of the groups before it.
   int32_t* ics;      // [N0 + B]: its first child (its children end where the next number's begin)
   int32_t* ioff;     // [G][T + 4]: first internal number of level d = 0 .. D + 1
   int32_t* cidx;     // [N0 + B]: internal number of a node; ~(the next internal number) if it has no children
@@ -60,7 +59,7 @@ struct PlanArgs {
   int32_t* elem;                // [3][B]: deepest level, pushes, leaf offset of an element
   int32_t* walk;                // [G][2][cap] when the walk arrays do not fit in LDS
   uint32_t* ctl;
-  uint64_t key;                 // of the sizes (CTL_KEY)
+  uint64_t key;                 // of the sizes (CTL_KEY); 0: no backward follows, nothing is written for one
 };
 
 struct LevFwdArgs {

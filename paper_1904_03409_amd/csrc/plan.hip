@@ -8,7 +8,8 @@
 //    them from the element's stack of producers.
 // Walking 64 steps together costs about as much as walking two one after the other.
 // Phases: (1) trace and pushes per depth, (2) a scan over (depth, element) for the first node id of
-// each, (3) the walk again, now writing node ids, (4) the numbers of the nodes with children.
+// each, (3) the walk again, now writing node ids, (4) for a backward, the numbers of the nodes with
+// children.
 #include "common.h"
 #include "levels.h"
 
@@ -268,16 +269,18 @@ __global__ void __launch_bounds__(1024) k_plan(PlanArgs a) {
         a.ix.order[pos] = r;
         a.ix.opar[pos] = par;
       }
-      if (c.valid) a.ix.gslot[r] = sl;
+      if (c.valid && a.key) a.ix.gslot[r] = sl;
       leaf += __popcll(m_leaf);
       p0 = __builtin_amdgcn_readlane(c.pa, 63);
       cur = __builtin_amdgcn_readlane(topid, 63);
       slot = __builtin_amdgcn_readlane(sl, 63);
     }
+    if (!a.key) continue;
     // nodes still on the stack were never popped (marked here, resolved in phase 4)
     __threadfence_block();
     for (int d = 1 + lane; d <= p0; d += 64) a.ix.opar[stk[d]] = ~stk[d - 1];
   }
+  if (!a.key) return;
   __threadfence_block();
   __syncthreads();
 
@@ -297,10 +300,7 @@ __global__ void __launch_bounds__(1024) k_plan(PlanArgs a) {
     int total;
     const int idx = run + block_excl(flag, s_w, &total);
     if (q < n) a.ix.cidx[node(q)] = flag ? idx : ~idx;
-    if (flag) {
-      a.ix.irow[idx] = node(q);
-      a.ix.ics[idx] = c0;
-    }
+    if (flag) a.ix.ics[idx] = c0;
     run += total;
   }
   if (tid == 0) a.ix.ics[run] = end;
