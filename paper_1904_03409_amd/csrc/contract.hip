@@ -52,7 +52,7 @@ __device__ __forceinline__ void redo_nan(f32x4 (&acc)[MI][NJ], int kbeg, int ken
     for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int q = 0; q < 4; ++q) bad |= is_nan(acc[i][j][q]);
-  if (!__ballot(bad)) return;
+  if (__builtin_expect(__ballot(bad) == 0, 1)) return;
   f32x4 v[MI][NJ];
 #pragma unroll
   for (int i = 0; i < MI; ++i)

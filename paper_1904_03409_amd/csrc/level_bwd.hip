@@ -20,7 +20,10 @@
 #include "levels.h"
 #include "split.h"
 
-template <int NP, int KS>
+// CLK: with the stamps of dims.step_clock. (A kernel of its own: the scalar registers spill, and every
+// argument kept for later costs reads back on the chain of a level. deep, H = 512: 4266 us with
+// the stamps' branches, 4064 without.)
+template <int NP, int KS, bool CLK>
 __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
   constexpr int S = NP == 2 ? 3 : 1;
   constexpr int KH = KS / 2, SG = KH * 4;                   // K chunks and 16-byte granules of a wave's row slice
@@ -89,9 +92,9 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
       }
     }
   };
-  // optional wall-clock stamps of a level: top, sums stored, all sums there, gradients of the parents done
+  // wall-clock stamps of a level: top, sums stored, all sums there, gradients of the parents done
   auto stamp = [&](int d, int k) {
-    if (a.clk && tid == 0) a.clk[((size_t)blockIdx.x * T + d - 1) * 4 + k] = wall_clock64();
+    if (CLK && tid == 0) a.clk[((size_t)blockIdx.x * T + d - 1) * 4 + k] = wall_clock64();
   };
   // dA of a child: the planes that dW, dU and dx read, and the bias gradient. Nobody waits for these
   // stores. H > 512: a pass that is not the level's last leaves it to the next one, which does it from
@@ -426,9 +429,9 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
   }
 }
 
-template <int NP, int KS>
+template <int NP, int KS, bool CLK>
 static hipError_t launch_t(const LevBwdArgs& a, int grid, hipStream_t st) {
-  auto kern = k_lev_bwd<NP, KS>;
+  auto kern = k_lev_bwd<NP, KS, CLK>;
   constexpr int shm = (int)lev_bwd_lds(NP, KS);
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, shm);
   if (e != hipSuccess) return e;
@@ -438,7 +441,7 @@ static hipError_t launch_t(const LevBwdArgs& a, int grid, hipStream_t st) {
 }
 hipError_t launch_lev_bwd(const LevBwdArgs& a, int NP, int KS, int grid, hipStream_t st) {
 #define CASE(N_, KS_) \
-  if (NP == N_ && KS == KS_) return launch_t<N_, KS_>(a, grid, st);
+  if (NP == N_ && KS == KS_) return a.clk ? launch_t<N_, KS_, true>(a, grid, st) : launch_t<N_, KS_, false>(a, grid, st);
   LEV_CASES(CASE)
 #undef CASE
   return hipErrorInvalidValue;

@@ -11,7 +11,8 @@
 #include "levels.h"
 #include "split.h"
 
-template <int NP, int KS>
+// CLK: with the stamps of dims.step_clock.
+template <int NP, int KS, bool CLK>
 __global__ void __launch_bounds__(kLevThreads, 2) k_lev_fwd(LevFwdArgs a) {
   constexpr int RT = lev_fwd_rt(NP, KS), ROWS = 16 * RT, GRW = KS * 4;  // rows per pass, 16-byte granules per row
   constexpr int KH = KS / 2;
@@ -145,9 +146,9 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_fwd(LevFwdArgs a) {
     }
   };
 
-  // optional wall-clock stamps: level top, first rows landed, products of the last pass done, end
+  // wall-clock stamps: level top, first rows landed, products of the last pass done, end
   auto stamp = [&](int d, int k) {
-    if (a.clk && tid == 0 && d < T) a.clk[((size_t)blockIdx.x * T + d) * 4 + k] = wall_clock64();
+    if (CLK && tid == 0 && d < T) a.clk[((size_t)blockIdx.x * T + d) * 4 + k] = wall_clock64();
   };
   int q0 = n_init, q1 = n_init + Bg;
   int c0 = uni(loff[1]), cend = uni(loff[2]);               // children of the level: nodes [c0, cend)
@@ -266,9 +267,9 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_fwd(LevFwdArgs a) {
   }
 }
 
-template <int NP, int KS>
+template <int NP, int KS, bool CLK>
 static hipError_t launch_t(const LevFwdArgs& a, int grid, hipStream_t st) {
-  auto kern = k_lev_fwd<NP, KS>;
+  auto kern = k_lev_fwd<NP, KS, CLK>;
   constexpr int shm = (int)lev_fwd_lds(NP, KS);
   hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, shm);
   if (e != hipSuccess) return e;
@@ -278,7 +279,7 @@ static hipError_t launch_t(const LevFwdArgs& a, int grid, hipStream_t st) {
 }
 hipError_t launch_lev_fwd(const LevFwdArgs& a, int NP, int KS, int grid, hipStream_t st) {
 #define CASE(N_, KS_) \
-  if (NP == N_ && KS == KS_) return launch_t<N_, KS_>(a, grid, st);
+  if (NP == N_ && KS == KS_) return a.clk ? launch_t<N_, KS_, true>(a, grid, st) : launch_t<N_, KS_, false>(a, grid, st);
   LEV_CASES(CASE)
 #undef CASE
   return hipErrorInvalidValue;

@@ -82,3 +82,35 @@ def test_infinite_input(oracle_mod, precision):
     for k in ("h_cell", "c_cell"):
         got = getattr(r, k).cpu().numpy()
         assert np.all(np.isfinite(a1[k])) and normwise(got, a1[k]) <= TOL[precision], k
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_step_clock(precision):
+    """With dims.step_clock the recurrent kernels of every width run as instantiations with stamps: the
+    same outputs, and four stamps in order for each level."""
+    need_gpu()
+    import ctypes
+    import torch
+    from paper_1904_03409_amd.stacklstm import DeviceRun
+    for H in (24, 60, 130, 300, 500) if precision == 0 else (24, 60, 130, 300, 500, 700, 1000):
+        print(f"[gpu] step clock H={H} prec={precision}", flush=True)
+        wl = wk.custom(T=20, B=5, I=8, H=H, seed=H, ops=_ops("deep", 20, 5), wscale=0.1, random_state=True)
+        r = DeviceRun.from_workload(wl, precision=precision)
+        r.forward()
+        r.backward()
+        want = r.results()
+        clk = torch.zeros(2, 512, wl.T, 4, dtype=torch.int64, device="cuda")
+        r.dims.step_clock = ctypes.c_void_p(clk.data_ptr())
+        r.forward()
+        r.backward()
+        torch.cuda.synchronize()
+        got = r.results()
+        for k in want:
+            assert np.array_equal(got[k], want[k]), (H, k)
+        c = clk.cpu().numpy()
+        for p, levels in ((0, 11), (1, 10)):              # forward: the initial states' level too
+            used = c[p, c[p, :, 0, 0] > 0]
+            assert len(used) == 5 * -(-H // 32)
+            assert np.all(np.diff(used[:, :levels], axis=2) >= 0) and not used[:, levels:].any()
+            step = np.diff(used[:, :levels, 0], axis=1)
+            assert np.all(step > 0 if p == 0 else step < 0)
