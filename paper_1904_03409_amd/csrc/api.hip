@@ -148,9 +148,9 @@ Layout layout(const slstm_dims* d, bool keep, size_t x_budget) {
   L.ufi = put((size_t)NW * kLevUnits * 4);
   L.rin = put(B * 4);
   // k_plan's counts and walk arrays; then x W and h U of the nodes (forward); then the exchange rows of the
-  // backward
-  const size_t walk = align256(B * L.cap * 4);
-  L.hu = put(std::max({NN * 4 * H * 4, keep ? NP * NN * L.H4s * 2 : 0,
+  // backward, in bf16 mode (rows half as long) with the interval sums of dc_top behind them
+  const size_t walk = align256(B * L.cap * 4), sx = align256(NP * NN * L.H4s * 2), sums = 2 * NN * H * 4;
+  L.hu = put(std::max({NN * 4 * H * 4, keep ? sx + (NP == 1 ? sums : 0) : 0,
                        walk + (L.walk_lds ? 0 : (size_t)L.G * 2 * L.cap * 4)}));
   L.cnt = L.hu;
   L.walk = L.hu + walk;
@@ -167,10 +167,11 @@ Layout layout(const slstm_dims* d, bool keep, size_t x_budget) {
     L.total = o;
     return L;
   }
-  L.gf = put(2 * NN * H * 4);
-  L.gc = put(2 * NN * H * 4);
-  L.eg = put(NN * H * 4);
-  L.dcs = put(NN * H * 4);
+  // a backward needs neither c of the nodes (it has the parents') nor, in fp32 mode, the recurrent planes of h
+  L.gf = put(sums);
+  L.gc = NP == 1 ? L.hu + sx : put(sums);
+  L.eg = L.cn;
+  L.dcs = NP == 2 ? L.hq : put(NN * H * 4);
   L.dap = put(S * N0 * L.H4s * 2);
   L.sxs = put(NP == 2 ? NN * NW * 4 : 0);
   L.ub = put((size_t)NW * 8 * KS * 64 * NP * 16);

@@ -46,3 +46,13 @@ def test_host_only_entry_points():
     for code in range(9):
         assert s._status_string(code) not in ("", "?", "unknown status")
     assert s._status_string(99) == "unknown status"
+
+
+def test_workspace_bytes_per_step():
+    """The work space of large sizes, in bytes per element step and hidden unit (I = H or H / 2): what the
+    parts that share space leave."""
+    from paper_1904_03409_amd import stacklstm as s
+    for dims, most in (((240, 256, 256, 512, s.SLSTM_FP32), 95), ((1024, 500, 512, 512, s.SLSTM_FP32), 96.5),
+                       ((240, 256, 256, 512, s.SLSTM_BF16_GEMM), 65.5), ((256, 1024, 512, 1024, s.SLSTM_BF16_GEMM), 63.5)):
+        T, B, H = dims[0], dims[1], dims[3]
+        assert s.stacklstm_workspace_bytes(s.make_dims(*dims)) / (T * B * H) < most, dims
