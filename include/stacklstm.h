@@ -173,26 +173,22 @@ int stacklstm_sync_status(const void* workspace, size_t ws_bytes, void* stream);
 /* Static text for a status code. */
 const char* stacklstm_status_string(int status);
 
-/* Launch configuration the library chooses for `d` (informational; tests use it to reach
+/* Launch configuration of the recurrent kernels for `d` (informational; tests use it to reach
  * every kernel variant). */
 typedef struct {
-  int32_t groups;          /* forward: batch groups (one per XCC slot) */
-  int32_t wg_per_group;    /* forward: workgroups per group */
-  int32_t rows_per_group;  /* forward: batch rows per group (16 * fwd_tiles) */
-  int32_t k_chunks;        /* K chunks of the recurrent contraction in use */
-  int32_t fwd_kernel;      /* 0 plain, 1 pipelined (two LDS tile buffers), 2 wide (bf16, H > 512) */
-  int32_t fwd_tiles;       /* forward: 16-row tiles per group */
-  int32_t k_chunk_cap;     /* K chunks compiled into the kernels (power of two >= k_chunks) */
-  int32_t occupancy;       /* 2: the recurrent kernels are compiled for 256 registers per lane
-                              (two 256-thread workgroups per CU in the forward, one 512-thread
-                              workgroup in the backward), else 1 */
-  int32_t bwd_groups;      /* backward: batch groups */
-  int32_t bwd_tiles;       /* backward: 16-row tiles per group */
-  int32_t bwd_direct;      /* backward: dA rows staged in LDS by DMA (1) or read into registers (0) */
-  int32_t fused_x;         /* 1: the forward kernel contracts x_t W itself (no separate input
-                              projection GEMM; bf16, plain forward, one pass per step) */
-  int32_t bwd_split;       /* 1: the backward contracts dA U^T over each workgroup's own gate
-                              columns and exchanges partial sums instead of dA rows */
+  int32_t groups;          /* batch groups; each runs on one XCC, element b in group b % groups */
+  int32_t wg_per_group;    /* workgroups per group (32 hidden units each) */
+  int32_t rows_per_group;  /* batch elements of the largest group */
+  int32_t k_chunks;        /* K chunks of 32 of h U in use */
+  int32_t fwd_kernel;      /* 0 (one forward kernel) */
+  int32_t fwd_tiles;       /* forward: 16-row tiles of a level's states per pass */
+  int32_t k_chunk_cap;     /* K chunks compiled into the kernels (>= k_chunks) */
+  int32_t occupancy;       /* waves per SIMD: 2, one 512-thread workgroup per CU */
+  int32_t bwd_groups;      /* backward: batch groups (as the forward) */
+  int32_t bwd_tiles;       /* backward: 16-row tiles of parents per product */
+  int32_t bwd_direct;      /* 0 (no such variant), as the next two */
+  int32_t fused_x;
+  int32_t bwd_split;
 } slstm_plan;
 
 /* Fills `out` for `d`; returns a status like the entry points. */

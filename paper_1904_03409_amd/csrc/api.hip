@@ -270,7 +270,7 @@ int stacklstm_plan(const slstm_dims* d, slstm_plan* out) {
   memset(out, 0, sizeof(*out));
   out->groups = p.G;
   out->wg_per_group = p.NW;
-  out->rows_per_group = batch_max(d->H) / groups_max(d->H, 32);
+  out->rows_per_group = (d->B + p.G - 1) / p.G;
   out->k_chunks = p.NW;
   out->fwd_tiles = lev_fwd_rt(p.NP, p.KS);
   out->k_chunk_cap = p.KS;

@@ -1,14 +1,12 @@
-"""Every kernel variant the planner can choose runs against the oracle.
+"""Every variant of the recurrent kernels, and every kind of group, runs against the oracle.
 
-The planner picks, per call, a forward kernel (plain, pipelined or wide), the row tiles per
-group of the forward and the backward, the K-chunk capacity compiled into the kernels, the
-occupancy they are built for and whether the backward stages dA rows by DMA. Those choices
-depend on H (K chunks), B (co-residency of the groups' workgroups) and the precision. The
-test sweeps a grid of (precision, H, B) that crosses every K-chunk bucket, the pipelined and
-wide conditions and every row-tile threshold, collects the distinct variants the planner
-returns, and runs each once (short T) against the oracle: traces of every column, floats of
-sampled columns, and the weight gradients of a second backward whose upstream gradient is
-zero outside the sampled columns."""
+The compiled width (K chunks) and the rows per pass follow from H and the precision; the number of
+groups, the elements of a group and whether the groups are even follow from B as well. The test
+sweeps a grid of (precision, H, B), asks the planner for each, and keeps the first grid point of each
+class: (precision, width compiled and in use, how state rows lie in cache lines; groups of one element,
+of one pass, of several passes at the first level; even or uneven groups). Each runs once (short T)
+against the oracle: traces of every column, floats of sampled columns, and the weight gradients of
+a second backward whose upstream gradient is zero outside the sampled columns."""
 import numpy as np
 import pytest
 
@@ -19,9 +17,9 @@ from tests.torch_ref import normwise
 pytestmark = pytest.mark.gpu
 
 GRID_H = {0: [1, 40, 64, 100, 128, 200, 252, 256, 300, 508, 512],
-          1: [1, 64, 100, 128, 200, 256, 300, 504, 512, 520, 1020, 1024]}
-GRID_B = [1, 17, 64, 100, 128, 129, 200, 256, 257, 300, 384, 400, 512, 513, 600, 700, 768, 769, 900, 1000, 1024]
-KEYS = ("fwd_kernel", "fwd_tiles", "k_chunk_cap", "occupancy", "bwd_tiles", "bwd_direct", "fused_x", "bwd_split")
+          1: [1, 64, 100, 128, 200, 256, 300, 384, 504, 512, 520, 768, 1020, 1024]}
+GRID_B = [1, 17, 64, 100, 128, 129, 200, 256, 257, 300, 384, 400, 512, 513, 600, 700, 768, 769, 900, 1000, 1024, 1500, 3000, 5000, 5120]
+KEYS = ("fwd_tiles", "k_chunk_cap")
 
 
 def reachable_variants():
@@ -35,16 +33,23 @@ def reachable_variants():
                     plan = stacklstm_plan(make_dims(8, B, 8, H, prec, 0))
                 except StackLSTMError:
                     continue
-                key = (prec,) + tuple(plan[k] for k in KEYS) + row_class(prec, H, plan)
+                key = (prec,) + tuple(plan[k] for k in KEYS) + row_class(prec, H, plan) + group_class(B, plan)
                 out.setdefault(key, (prec, H, B))
     return out
 
 
 def row_class(prec, H, plan):
     """How the kernels copy state rows for this H: every K chunk in use, rows of whole 1 KB
-    segments, rows of whole 128-byte lines (no line shared by two rows)."""
-    nbytes = H * (2 if prec else 4)
+    segments, rows of whole 128-byte lines (no line shared by two rows). (A plane has 2 bytes a unit.)"""
+    nbytes = H * 2
     return (int(plan["k_chunks"] == plan["k_chunk_cap"]), int(nbytes % 1024 == 0), int(nbytes % 128 == 0))
+
+
+def group_class(B, plan):
+    """Groups of one element, of one pass of states, of more; whether some group has an element less."""
+    rows = plan["rows_per_group"]
+    assert rows == -(-B // plan["groups"]) and plan["groups"] <= B
+    return (1 if rows == 1 else 2 if rows <= 16 * plan["fwd_tiles"] else 3, int(B % plan["groups"] != 0))
 
 
 # shapes run whatever variant they map to: the largest batches at the largest hidden sizes
@@ -83,8 +88,12 @@ def _sampled_parity(oracle_mod, wl, precision, ncols=3):
 def test_every_planner_variant(oracle_mod):
     need_gpu()
     variants = reachable_variants()
-    print(f"[gpu] {len(variants)} variants: precision, fwd kernel, fwd tiles, K-chunk cap, occupancy, "
-          f"bwd tiles, bwd direct, fused x W, all chunks used, 1 KB rows, 128-byte rows -> first (precision, H, B)", flush=True)
+    print(f"[gpu] {len(variants)} variants: precision, fwd tiles, K-chunk cap, all chunks used, 1 KB rows, "
+          f"128-byte rows, group size class, uneven groups -> first (precision, H, B)", flush=True)
+    for prec, caps in ((0, {2, 4, 8, 16}), (1, {2, 4, 8, 12, 16, 24, 32})):
+        assert {k[2] for k in variants if k[0] == prec} == caps
+        for cap in caps:                                   # every width: one element, one pass and several
+            assert {k[6] for k in variants if k[0] == prec and k[2] == cap} == {1, 2, 3}, (prec, cap)
     failures = {}
     cases = sorted(variants.items()) + [(("extra",), s) for s in EXTRA]
     for key, (prec, H, B) in cases:
