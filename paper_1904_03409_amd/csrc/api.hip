@@ -105,7 +105,7 @@ int tn_splits(const slstm_dims* d) {
 // Work-space layout. It does not depend on the device (group counts as for 32 CUs per XCD).
 struct Layout {
   size_t ctl, order, opar, cs, loff, gmax, ics, ioff, cidx, kin, gslot, cnt, elem, walk;
-  size_t wt, wp, uf, ufi, rin, hu, stash, cpn, hq, h3, cn, xs, fwd_end;
+  size_t wt, wp, uf, ufi, rin, hu, stash, cpn, hq, h3, cn, xs;
   size_t gf, gc, eg, dcs, dap, sxs, ub, ubi, part, dbp, total;
   int Ip, Hs, H4s, cap, G;
   int x_rows;                        // rows of x whose planes fit (all, except in the static work space)
@@ -162,7 +162,6 @@ Layout layout(const slstm_dims* d, bool keep, size_t x_budget) {
   L.x_rows = (int)N0;
   if (x_budget) L.x_rows = (int)std::min<size_t>(N0, std::max<size_t>(x_budget / (S * L.Ip * 2), 1));
   L.xs = put(S * (size_t)L.x_rows * L.Ip * 2);
-  L.fwd_end = o;
   if (!keep) {
     L.total = o;
     return L;

@@ -6,7 +6,6 @@
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef uint16_t bf16_t;  // raw bfloat16 bits in memory
 
 // Status codes shared with the C-ABI (values fixed by include/stacklstm.h).
@@ -21,7 +20,6 @@ constexpr uint32_t kStatusOk = 0x7fffffffu;
 // Work-space word offsets (uint32 units) of the control block at the start of the work space.
 enum {
   CTL_STATUS = 0,        // lowest (element * 8 + code) of a failing element, or 0x7fffffff
-  CTL_MAXDEPTH = 1,
   CTL_ABORT = 2,         // set when a wait ran out of spins: every workgroup leaves its loop
   CTL_TIMEOUT = 3,       // set when a wait ran out of spins (reported as SLSTM_ETIMEOUT)
   CTL_NPUSHF = 5,        // number of push steps (counted by k_plan in the forward)
@@ -76,45 +74,14 @@ __device__ __forceinline__ float bf16_bits_to_f32(bf16_t v) {
   return __uint_as_float(((uint32_t)v) << 16);
 }
 // Round to bfloat16, nearest-even (the hardware conversion on gfx950).
-__device__ __forceinline__ __bf16 f32_to_bf16(float f) { return static_cast<__bf16>(f); }
 __device__ __forceinline__ bf16_t f32_to_bf16_bits(float f) {
   __bf16 h = static_cast<__bf16>(f);
   return __builtin_bit_cast(bf16_t, h);
 }
 
-// Eight floats rounded to bf16 (nearest-even) in pairs, packed as they are converted.
-__device__ __forceinline__ bf16x8 pack_bf16x8(const float (&v)[8]) {
-  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-  typedef float f32x2 __attribute__((ext_vector_type(2)));
-  typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-  u32x4 w;
-#pragma unroll
-  for (int j = 0; j < 4; ++j)
-    w[j] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{v[2 * j], v[2 * j + 1]}, bf16x2));
-  // (an empty asm on the packed words keeps the compiler from sinking the conversions to the
-  // first use, which would keep all the fp32 values live through the set-up)
-  asm volatile("" : "+v"(w));
-  return __builtin_bit_cast(bf16x8, w);
-}
-
-__device__ __forceinline__ f32x4 mfma_f32_16x16x4(float a, float b, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-}
 __device__ __forceinline__ f32x4 mfma_bf16_16x16x32(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
-// Results of an MFMA chain in AGPRs may be read only some wait states after its last
-// instruction (10 for the fp32 16x16x4 form, 8 for the bf16 16x16x32 form: the counts the
-// compiler itself inserts in straight-line code). The compiler's hazard pass misses them on
-// a branch edge that leaves the MFMA's block (measured: 3 wait states on the taken path
-// round a conditional store, and the fourth accumulator read stale). This drain issues 12
-// wait states after the chain, as an asm statement that takes the accumulators as operands
-// and so runs after the chain's last MFMA and before any read of its results; the compiler
-// sees the asm, not an MFMA, as their last writer.
-__device__ __forceinline__ void mfma_drain(f32x4& a, f32x4& b) {
-  asm volatile("s_nop 7\n\ts_nop 3" : "+a"(a), "+a"(b));
-}
-
 // Gate nonlinearities from the hardware base-2 exponential and reciprocal (about one ulp
 // each): sigma(z) = 1 / (1 + 2^(-z log2 e)); tanh(x) = 2 sigma(2x) - 1. Absolute error is
 // a few 1e-7 over the whole range; both saturate correctly (2^(+inf) = inf gives 0, 2^(-inf)
@@ -132,19 +99,16 @@ __device__ __forceinline__ unsigned xcc_id() {
   return v & 0xf;
 }
 
-// Loads of data that another CU wrote earlier in the same kernel. They go through a
-// buffer descriptor (bounds-checked: an offset past `bytes` reads 0 instead of faulting)
-// with the sc1 cache policy, which bypasses this CU's L1 and reads the XCC's L2, so a
-// line that L1 cached before the other CU's write is never returned stale.
+// Buffer descriptor of `bytes` bytes (an offset past them reads 0 instead of faulting; at most 4 GiB).
+// Data that another CU wrote earlier in the same kernel is read with the sc1 cache policy, which
+// bypasses this CU's L1 and reads the XCC's L2: a line that L1 cached before the other CU's write is
+// never returned stale.
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 __device__ __forceinline__ rsrc_t make_rsrc(const void* base, size_t bytes) {
   uint32_t n = bytes > 0xffffffffu ? 0xffffffffu : (uint32_t)bytes;
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)n, 0x00020000);
 }
 constexpr int kSc1 = 16;  // cache-policy bit SC1 of gfx94x/gfx950 memory instructions
-__device__ __forceinline__ uint4 ld_coh_b128(rsrc_t r, uint32_t off) {
-  return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, kSc1));
-}
 __device__ __forceinline__ float canon_nan(float h) { return h == h ? h : __builtin_nanf(""); }
 
 // A producer index s read at step t must lie in [-1, t) (the state read at step t) or
@@ -166,9 +130,8 @@ __device__ __forceinline__ int checked_src(int s, int hi, uint32_t* ctl) {
 // Group barrier for workgroups that all run on one XCC (one shared L2).
 // Each wave waits until its own stores are acknowledged by L2, the workgroup meets at
 // s_barrier, one lane adds to the group counter and polls it with L1-bypassing loads.
-// Data written by other workgroups before the barrier must then be read with the
-// ld_coh_* loads above. Returns true when the spin limit ran out (or another group's
-// did): the caller must then leave its loop so that every wave of the grid exits.
+// Data written by other workgroups before the barrier must then be read past the L1 (sc1). Returns
+// true when the spin limit ran out (or another group's did): the caller must then leave its loop so that every wave of the grid exits.
 // Arrival half: stores acknowledged, workgroup met, the group counter incremented. The lane that
 // polls is one of the last wave, whose threads have the fewest loads of their own in flight when
 // the workgroup prefetches between the halves (loads return in order, a poll behind them).
@@ -264,18 +227,6 @@ __device__ __forceinline__ void wait_vm() {
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
   asm volatile("" ::: "memory");
 }
-// The same for a wave-uniform count n in [0, 16] (n outside it waits for all).
-__device__ __forceinline__ void wait_vm_upto16(int n) {
-  switch (n) {
-#define SLSTM_WAIT_CASE(k) case k: wait_vm<k>(); break;
-    SLSTM_WAIT_CASE(1) SLSTM_WAIT_CASE(2) SLSTM_WAIT_CASE(3) SLSTM_WAIT_CASE(4) SLSTM_WAIT_CASE(5)
-    SLSTM_WAIT_CASE(6) SLSTM_WAIT_CASE(7) SLSTM_WAIT_CASE(8) SLSTM_WAIT_CASE(9) SLSTM_WAIT_CASE(10)
-    SLSTM_WAIT_CASE(11) SLSTM_WAIT_CASE(12) SLSTM_WAIT_CASE(13) SLSTM_WAIT_CASE(14) SLSTM_WAIT_CASE(15)
-    SLSTM_WAIT_CASE(16)
-#undef SLSTM_WAIT_CASE
-    default: wait_vm<0>(); break;
-  }
-}
 // A copy of v the compiler cannot see through: what is computed from it is computed where it is
 // used, instead of being kept in registers through a whole kernel.
 __device__ __forceinline__ int opaque(int v) {
@@ -303,10 +254,3 @@ __device__ __forceinline__ T* at32(T* base, uint32_t off) {
 }
 // Wave-uniform value kept in a scalar register.
 __device__ __forceinline__ int uni(int v) { return __builtin_amdgcn_readfirstlane(v); }
-__device__ __forceinline__ void dma16_global(const void* gp, uint32_t lds, bool sc1) {
-  lds = __builtin_amdgcn_readfirstlane(lds);   // wave-uniform by contract; keeps it in an SGPR
-  if (sc1)
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off sc1" ::"s"(lds), "v"(gp) : "memory", "m0");
-  else
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(gp) : "memory", "m0");
-}

@@ -22,7 +22,7 @@ struct NtArgs {
 };
 
 // dW | dU: C(m, n) = sum over push nodes k of X(k, m) dA(k, n); rows m < I of x (array row k), the
-// others of the state the node read (array row parent(k)). Split over K into gridDim.z partials.
+// others of the state the node read (array row parent(k)). Split over K into `splits` partials.
 struct TnArgs {
   int I, H, H4, splits, xt;          // xt: row tiles that cover x
   const uint16_t* X; size_t xplane; int ldx;

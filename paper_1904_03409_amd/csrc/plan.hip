@@ -184,7 +184,6 @@ __global__ void __launch_bounds__(1024) k_plan(PlanArgs a) {
   const int D = s_max, P = s_total;
   if (tid == 0) {
     a.ix.gmax[g] = D;
-    atomicMax(&a.ctl[CTL_MAXDEPTH], (uint32_t)D);
     if (g == 0) {
       a.ctl[CTL_NPUSHF] = (uint32_t)P;
       a.ctl[CTL_KEY] = (uint32_t)a.key;

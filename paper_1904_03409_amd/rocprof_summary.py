@@ -10,7 +10,7 @@
       run (DIR2). Both counters are read in KiB per dispatch and scaled by what they read
       for the plain copy kernel of N bytes in the same run (the elementwise b = a * 1 kernel
       that bench.py --copy-probe launches). With --json, the persistent kernels' entries are
-      merged into OUT keyed CONFIG/dtype/phase (dtype from the kernel's precision argument),
+      merged into OUT keyed CONFIG/dtype/phase (dtype from the planes of the recurrent products),
       together with the hash of the kernel sources they were taken from (bench.py reports
       them only while that hash still matches). The totals of one whole fwd+bwd step per
       precision (every kernel, K steps per run) are stored as CONFIG/dtype/step.
@@ -73,12 +73,12 @@ def _per_dispatch(d, counter):
 
 def _step_bytes(d, counter, scale, steps_per_run):
     """Scaled bytes of one fwd+bwd step for the fp32 run and for the bf16 run that bench.py
-    starts after it (the bf16 run begins at its first bf16 kernel); the copy probe's kernels
-    are left out."""
+    starts after it (the bf16 run begins at its first preparation of bf16 operands); the copy
+    probe's kernels are left out."""
     seg = {"f32": 0.0, "bf16": 0.0}
     cur = "f32"
     for _, name, v in _dispatches(d, counter):
-        if "<1," in name:
+        if "k_prep_fwd<1>" in name:
             cur = "bf16"
         if "MulFunctor" in name or "FillFunctor" in name:
             continue
@@ -86,7 +86,7 @@ def _step_bytes(d, counter, scale, steps_per_run):
     return {k: v / steps_per_run for k, v in seg.items()}
 
 
-PHASE_OF = (("void k_fwd", "rec_fwd"), ("void k_bwd", "rec_bwd"))
+PHASE_OF = (("void k_lev_fwd", "rec_fwd"), ("void k_lev_bwd", "rec_bwd"))
 
 
 def traffic(fetch_dir, write_dir, copy_bytes, key, json_out, steps_per_run):
@@ -111,7 +111,7 @@ def traffic(fetch_dir, write_dir, copy_bytes, key, json_out, steps_per_run):
         lines.append(f"| `{name}` | {fb:.0f} | {wb:.0f} | {hbm:.4g} |")
         for prefix, phase in PHASE_OF:
             if k.startswith(prefix):
-                dtype = "f32" if k.split("<", 1)[1].startswith("0") else "bf16"
+                dtype = "f32" if k.split("<", 1)[1].startswith("2") else "bf16"     # (planes: two fp16, one bf16)
                 entries[f"{key}/{dtype}/{phase}"] = {"kernel": k, "fetch_kib": fb, "write_kib": wb,
                                                      "hbm_bytes_per_launch": hbm}
     fs = _step_bytes(fetch_dir, "FETCH_SIZE", f_scale, steps_per_run)

@@ -2,36 +2,30 @@
 from paper_1904_03409_amd import build
 
 
-def test_counted_wait_kernels():
-    # the wide forward always counts its waits
-    assert build.counted_waits("_Z10k_fwd_wideILi8ELi32EEv7RecArgs")
-    # backward variants with direct dA staging: whole 1 KB segments, one workgroup per CU, <= 4 tiles
-    assert build.counted_waits("_Z5k_bwdILi0ELi2ELi32ELi1ELb0EEv7RecArgs")       # fp32 H 512: 2 KB rows
-    assert build.counted_waits("_Z5k_bwdILi1ELi4ELi16ELi1ELb0EEv7RecArgs")       # bf16 H 512: 1 KB rows
-    assert not build.counted_waits("_Z5k_bwdILi0ELi2ELi32ELi1ELb1EEv7RecArgs")   # gate-split: no dA staging
-    assert not build.counted_waits("_Z5k_bwdILi0ELi8ELi32ELi1ELb0EEv7RecArgs")   # eight tiles: built without it
-    assert not build.counted_waits("_Z5k_bwdILi1ELi8ELi32ELi2ELb0EEv7RecArgs")   # two workgroups per CU
-    assert not build.counted_waits("_Z5k_bwdILi0ELi1ELi8ELi1ELb0EEv7RecArgs")    # 512-byte rows
-    assert not build.counted_waits("_Z5k_fwdILi0ELi1ELi1ELi32ELi1EEv7RecArgs")
+def test_scratch_rule():
+    assert build.may_spill("_Z4k_tnILi3ELb1EEv6TnArgs")
+    for name in ("_Z4k_tnILi3ELb0EEv6TnArgs", "_Z4k_tnILi1ELb1EEv6TnArgs", "_Z9k_lev_bwdILi2ELi16ELb0EEv10LevBwdArgs",
+                 "_Z9k_lev_fwdILi1ELi32ELb1EEv10LevFwdArgs", "_Z4k_ntILi3ELi1EEv6NtArgs", "_Z6k_planILb1EEv8PlanArgs"):
+        assert not build.may_spill(name)
 
 
 def test_resource_report_parse():
     text = "\n".join([
-        "a.hip:1:1: remark: Function Name: _Z5k_bwdILi0ELi2ELi32ELi1ELb0EEv7RecArgs [-Rpass-analysis=kernel-resource-usage]",
+        "a.hip:1:1: remark: Function Name: _Z9k_lev_bwdILi2ELi16ELb0EEv10LevBwdArgs [-Rpass-analysis=kernel-resource-usage]",
         "a.hip:1:1: remark:     VGPRs: 256 [-Rpass-analysis=kernel-resource-usage]",
         "a.hip:1:1: remark:     ScratchSize [bytes/lane]: 0 [-Rpass-analysis=kernel-resource-usage]",
-        "a.hip:9:1: remark: Function Name: _Z5k_bwdILi0ELi8ELi32ELi1ELb0EEv7RecArgs [-Rpass-analysis=kernel-resource-usage]",
+        "a.hip:9:1: remark: Function Name: _Z4k_tnILi3ELb1EEv6TnArgs [-Rpass-analysis=kernel-resource-usage]",
         "a.hip:9:1: remark:     ScratchSize [bytes/lane]: 880 [-Rpass-analysis=kernel-resource-usage]",
     ])
     rep = build.resource_report(text)
-    assert rep == {"_Z5k_bwdILi0ELi2ELi32ELi1ELb0EEv7RecArgs": 0, "_Z5k_bwdILi0ELi8ELi32ELi1ELb0EEv7RecArgs": 880}
+    assert rep == {"_Z9k_lev_bwdILi2ELi16ELb0EEv10LevBwdArgs": 0, "_Z4k_tnILi3ELb1EEv6TnArgs": 880}
 
 
 def _asm(nop_taken: str) -> str:
     return "\n".join([
         "_Z5k_xxxv:",
-        "\tv_mfma_f32_16x16x4_f32 a[0:3], v1, v2, a[0:3]",
-        "\tv_mfma_f32_16x16x4_f32 a[4:7], v3, v4, a[4:7]",
+        "\tv_mfma_f32_16x16x32_f16 a[0:3], v[10:13], v[14:17], a[0:3]",
+        "\tv_mfma_f32_16x16x32_f16 a[4:7], v[18:21], v[22:25], a[4:7]",
         *nop_taken.splitlines(),
         "\ts_cbranch_vccnz .LBB0_5",
         "; %bb.4:",
@@ -49,11 +43,12 @@ def _asm(nop_taken: str) -> str:
 def test_mfma_branch_hazard_scan():
     # the pattern that returned a stale accumulator: 1 (branch) + 2 (s_nop 1) wait states on the taken path
     hz = build.mfma_branch_hazards(_asm(""))
-    assert len(hz) == 1 and "after 3 wait states (needs 10)" in hz[0] and hz[0].startswith("_Z5k_xxxv")
-    # the explicit drain (12 wait states) before the branch clears it
-    assert build.mfma_branch_hazards(_asm("\ts_nop 7\n\ts_nop 3")) == []
-    # bf16 16x16x32 needs 8: 1 + 2 + 5 covers it
-    bf = _asm("\ts_nop 4").replace("v_mfma_f32_16x16x4_f32 a[4:7], v3, v4", "v_mfma_f32_16x16x32_bf16 a[4:7], v[2:5], v[6:9]")
-    assert build.mfma_branch_hazards(bf.replace("v_mfma_f32_16x16x4_f32 a[0:3]", "v_mfma_f32_16x16x32_bf16 a[0:3]")) == []
+    assert len(hz) == 1 and "after 3 wait states (needs 8)" in hz[0] and hz[0].startswith("_Z5k_xxxv")
+    # enough wait states before the branch clear it: 1 + 2 + 5 is 8, one less is not
+    assert build.mfma_branch_hazards(_asm("\ts_nop 4")) == []
+    assert len(build.mfma_branch_hazards(_asm("\ts_nop 3"))) == 1
+    assert build.mfma_branch_hazards(_asm("\ts_nop 4").replace("_f16 ", "_bf16 ")) == []
+    # an MFMA the table does not name needs the longest wait
+    assert "needs 19" in build.mfma_branch_hazards(_asm("\ts_nop 4").replace("16x16x32_f16 a[4:7]", "32x32x16_f16 a[4:7]"))[0]
     # a read of registers the MFMA did not write is no hazard
-    assert build.mfma_branch_hazards(_asm("").replace("a7", "a9").replace("a3", "a11")) == []
+    assert build.mfma_branch_hazards(_asm("").replace("v0, a7", "v0, a9")) == []
