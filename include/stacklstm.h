@@ -31,13 +31,19 @@
  *    index stays in range).
  *  - No exception crosses the ABI. The only global state is the cached device
  *    properties (multiprocessor count per device), the kernels' launch attributes, and
- *    for stacklstm_fwd_static its static work space per GPU (with its device address).
+ *    for stacklstm_fwd_static its static work space per GPU (with its device address;
+ *    SLSTM_FWD_STATIC_BYTES of device memory, held by every process that loads the library).
  *    Calls on different work spaces may overlap, on any streams and from any host
  *    threads; calls that share a work space must not overlap. Results do not depend on
  *    what runs beside them.
  *  - Supported sizes: T >= 0, B >= 1, I >= 1, 1 <= H <= 512 (SLSTM_FP32) or
- *    H <= 1024 (SLSTM_BF16_GEMM); B up to 8 groups of 128 rows per XCC pass
- *    (SLSTM_ENORESIDENT beyond what one launch can hold).
+ *    H <= 1024 (SLSTM_BF16_GEMM); T*B*16H bytes (SLSTM_FP32) or T*B*8H bytes under 4 GiB and
+ *    T*B <= 2^28 (SLSTM_EINVAL beyond); B up to 128 times the smaller of 64 and
+ *    8 floor(32 / ceil(H / 16)), for H > 512 up to 1024 (SLSTM_ENORESIDENT beyond).
+ *  - How it runs: the op streams give every push a node whose parent is the state it reads; all
+ *    nodes of one stack depth, over every step and element, are computed together, level by level
+ *    (the pop and hold steps, whose states nobody reads, all at once at the end). The serial chain
+ *    is the depth of the stack, not T.
  */
 #ifndef STACKLSTM_H
 #define STACKLSTM_H
@@ -59,16 +65,24 @@ typedef enum {
   SLSTM_EDEVICE = 6,       /* a HIP runtime error */
   SLSTM_ETIMEOUT = 7,      /* a wait for another workgroup's data exceeded its spin limit
                               (dims->spin_limit failed polls, or the default limit) */
-  SLSTM_EINDEX = 8         /* a kernel read a producer index or reached a stack depth outside
-                              its valid range: the top or ops passed to stacklstm_bwd are not
-                              the forward's (or a read returned stale data) */
+  SLSTM_EINDEX = 8         /* the top or ops passed to stacklstm_bwd are not the forward's (a
+                              producer index outside its valid range, a push where the forward had
+                              none or the reverse), or the work space holds no forward of these sizes */
 } slstm_status;
 
 typedef enum {
-  SLSTM_FP32 = 0,          /* fp32 operands, fp32 accumulation */
+  SLSTM_FP32 = 0,          /* fp32 in, out and accumulated. Products run on the 16-bit matrix units,
+                              on operands split into planes whose sum is the operand: x W, dW, dU and
+                              dx on three bf16 planes (all 24 bits; of the nine plane products the six
+                              that matter in fp32), h U and dA U^T on two fp16 planes of the operand
+                              times a power of two (22 to 24 bits of the largest of a unit's weights,
+                              of 128 columns of dA, of an initial state; of a state, of 1: what is
+                              2^-17 of that or less keeps 2^-40 of it). Errors against 64 bits are
+                              those of fp32 products or smaller, over fp32's range of exponents
+                              (gradients below 1e-35 lose bits in dx, dW and dU) */
   SLSTM_BF16_GEMM = 1      /* operands of every matrix product rounded to bf16 (nearest
-                              even): x, W, U, h_prev, dA; fp32 accumulation, fp32 h/c,
-                              fp32 nonlinearities */
+                              even): x, W, U, h_prev, dA (in dA U^T: the sum of dA over the steps that
+                              read one state); fp32 accumulation, fp32 h/c, fp32 nonlinearities */
 } slstm_precision;
 
 typedef struct {
@@ -81,20 +95,22 @@ typedef struct {
                               SLSTM_ETIMEOUT: 0 = the default (4M), > 0 = this limit */
   void* phase_events;      /* NULL, or an array of SLSTM_PHASE_EVENTS hipEvent_t created by the
                               caller; the calls record them on `stream` between their phases:
-                              fwd [0] start, [1] after the op scan and trace,
-                              [2] after the input projection and the preparation of the exchange
-                              buffers, [3] after the persistent forward kernel, [4] after the
-                              h_top/c_top gathers; bwd [5] after the backward's preparation
-                              (control words, exchange buffer), right before the persistent
-                              backward kernel, [6] after it, [7] after dW and db, [8] after dU,
-                              [9] after dx. [2]-[3] and [5]-[6] time the persistent kernels
-                              alone. For profiling only. */
+                              fwd [0] start, [1] after the planes of W and U, the op scan, the trace
+                              and the schedule, [2] after the planes of x and x W of the push steps,
+                              [3] after the persistent forward kernel, [4] after the other steps'
+                              cells and the h_top/c_top gathers; bwd [5] after the backward's
+                              preparation (control words, U^T, sums of the upstream gradients),
+                              right before the persistent backward kernel, [6] after it, [7] and
+                              [8] both after dW, dU and db (one launch), [9] after dx. [2]-[3] and
+                              [5]-[6] time the persistent kernels alone. For profiling only. */
   void* step_clock;        /* NULL, or a device int64 buffer of 2 * 512 * T * 4 entries: the
                               persistent kernels store 100 MHz wall-clock stamps per workgroup
-                              and step, [pass (0 fwd, 1 bwd)][workgroup][t][4], at four points of
-                              each step (forward: loop top, h_prev staged, MFMA done, epilogue
-                              done; backward: loop top, epilogue done, row list ready, dh
-                              scattered). For profiling only. */
+                              and level, [pass (0 fwd, 1 bwd)][workgroup][level][4] (forward: stack
+                              depth of the states read, from 0; backward: of the nodes, less one;
+                              entries of levels that do not occur are not written), at four
+                              points of a level (forward: top, first rows staged, last products done,
+                              cells done; backward: top, sums stored, all sums there, gradients of
+                              the parents done). For profiling only. */
   int32_t defer_status;    /* 0: each call ends with a read-back of its control words (one host
                               synchronisation) and returns the call's own status. 1: the call
                               returns SLSTM_OK once its kernels are queued (host-side argument
@@ -112,10 +128,10 @@ typedef struct {
  * stack depths to the backward; pass the same buffer, untouched, to both calls. */
 size_t stacklstm_workspace_bytes(const slstm_dims* d);
 
-/* Forward over T steps (Algorithm 1 for every element and step). Op scan and producer
- * trace (section 3's p <- p + op on an integer stack), the input projection x_t W + b of
- * all steps as one MFMA GEMM, the persistent recurrent kernel and the gathers of the
- * returned states all run in the library's kernels.
+/* Forward over T steps (Algorithm 1 for every element and step). Op scan, producer trace
+ * (section 3's p <- p + op on an integer stack) and level schedule, x_t W + b of the push steps,
+ * the persistent recurrent kernel over the levels, the cells of the other steps and the
+ * gathers of the returned states all run in the library's kernels.
  *  x      [T, B, I]   inputs x_t                                 (read)
  *  ops    [T, B]      int8 ops, +1 push / -1 pop / 0 hold         (read)
  *  W [I, 4H], U [H, 4H], b [4H], h0 [B, H], c0 [B, H]             (read)
@@ -149,13 +165,16 @@ int stacklstm_fwd_static(const slstm_dims* d, const float* x, const int8_t* ops,
                          float* c_top, int32_t* ptr, int32_t* top, void* stream);
 
 /* Backward of L given dL/dh_top and dL/dc_top (section 5), after stacklstm_fwd on the
- * same inputs and work space. The reverse loop scatters each step's gradient into the step
- * that produced the state it read (the producer table `top`); dW, dU, db, dx are contracted
- * over the push steps only (on the other steps the gate gradient is exactly 0) on the
- * library's MFMA GEMM. A `top` or `ops` that is not the forward's gives SLSTM_EINDEX when
- * a kernel meets an index or stack depth outside its range.
- *  x, ops, W, U, h0, c0       as given to stacklstm_fwd          (read)
- *  h_cell, c_cell, top        as written by stacklstm_fwd        (read)
+ * same inputs and work space (which holds the schedule, the gate activations and the operands
+ * of the products; a backward may be repeated on it). From the deepest level up each node's
+ * gradient goes to its parent; dW, dU, db, dx are contracted over the push steps only (on the
+ * other steps the gate gradient is exactly 0). A `top` or `ops` that is not the forward's gives
+ * SLSTM_EINDEX where it can be told (see there), as does a work space without a forward of these
+ * sizes; no address is taken from either.
+ *  U, ops                     as given to stacklstm_fwd          (read)
+ *  top                        as written by stacklstm_fwd        (read: checked)
+ *  x, W, h0, c0, h_cell, c_cell   as given to and written by stacklstm_fwd (not read; all but W must
+ *                             not be NULL when T > 0)
  *  dh_top [T, B, H]           gradient w.r.t. h_top              (read)
  *  dc_top [T, B, H] or NULL   gradient w.r.t. c_top (NULL = 0)   (read)
  *  dx [T, B, I], dW [I, 4H], dU [H, 4H], db [4H], dh0 [B, H], dc0 [B, H]  (written)
