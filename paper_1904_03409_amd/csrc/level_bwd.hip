@@ -48,6 +48,7 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = uni(tid >> 6), l16 = lane & 15, lq = lane >> 4;
   const int uu = tid & 31, u = 32 * w + uu, kk = tid >> 5;
   const bool u_ok = u < H;
+  const bool solo = KS == 2 && NW == 1;                     // the group is this workgroup: no exchange with others
   uint32_t* bar = a.ctl + CTL_BAR_B + 16 * g;
   const int n_init = N0 + lev_goff(B, a.G, g), Bg = lev_bg(B, a.G, g);
   const int32_t* ioff = a.ix.ioff + (size_t)g * (T + 4);
@@ -276,9 +277,9 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
       }
     }
     stamp(d, 1);
-    group_arrive(bar);
+    group_arrive(bar, solo);
     int c0_next = 0, n0_next = 0;
-    const uint32_t seen = group_peek(bar);
+    const uint32_t seen = solo ? 0u : group_peek(bar);
     {
       if (d > 1) {
         const int n0 = uni(i0_next);
@@ -288,7 +289,7 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
         n0_next = n0;
         if constexpr (!kLate) prefetch(c0_next, c0);
       }
-      if (group_wait(bar, (uint32_t)(NW * (D - d + 1)), seen, a.ctl, a.spin_limit, &s_flag)) {
+      if (!solo && group_wait(bar, (uint32_t)(NW * (D - d + 1)), seen, a.ctl, a.spin_limit, &s_flag)) {
         stop = true;
         break;
       }

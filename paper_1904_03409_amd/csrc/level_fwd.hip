@@ -31,6 +31,7 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_fwd(LevFwdArgs a) {
   const int n_init = N0 + lev_goff(B, a.G, g), Bg = lev_bg(B, a.G, g);
   const int32_t* loff = a.ix.loff + (size_t)g * (T + 4);
   const int D = uni(a.ix.gmax[g]);
+  const bool solo = KS == 2 && a.NW == 1;                   // the group is this workgroup: no exchange with others
 
   uint4 uf[2][KH][NP];
   {
@@ -256,14 +257,14 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_fwd(LevFwdArgs a) {
     }
     stamp(d, 3);
     if (d >= D) break;
-    group_arrive(bar);
-    const uint32_t seen = group_peek(bar);
+    group_arrive(bar, solo);
+    const uint32_t seen = solo ? 0u : group_peek(bar);
     q0 = c0;
     q1 = c0 = cend;                                         // (levels follow each other)
     cend = uni(next_end);
     prefetch(pre, q0, q1, c0, cend);
     prefetch_c(pre, q0, q1);
-    if (group_wait(bar, (uint32_t)(a.NW * (d + 1)), seen, a.ctl, a.spin_limit, &s_flag)) break;
+    if (!solo && group_wait(bar, (uint32_t)(a.NW * (d + 1)), seen, a.ctl, a.spin_limit, &s_flag)) break;
   }
 }
 
