@@ -195,24 +195,7 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
                                 dct * ga[0] * (1.f - ga[2] * ga[2]), dh * tc * ga[3] * (1.f - ga[3])};
               ch_a[k * 32 + uu] = da;
               ch_c[k * 32 + uu] = float2{dct * ga[1] + ic, ih};
-              if constexpr (kDefer) {
-                if (!defer) put_da(c, u, da);
-                continue;
-              }
-              // (written out: through put_da the fp32 kernel of H = 512 spills four more registers)
-              bf16_t p[4][S];
-#pragma unroll
-              for (int q = 0; q < 4; ++q) {
-                db_add(q, da[q]);
-                split_bf16<S>(da[q], p[q]);
-              }
-#pragma unroll
-              for (int s = 0; s < S; ++s) {
-                bf16_t* dst = (bf16_t*)((char*)(a.dap + s * a.dplane) + lev_da_off<NP>(c, H4s, u));
-                *(uint2*)dst =
-                    uint2{(uint32_t)p[0][s] | ((uint32_t)p[1][s] << 16), (uint32_t)p[2][s] | ((uint32_t)p[3][s] << 16)};
-                if (u == H - 1 && (H & 1)) *(uint2*)(dst + 4) = uint2{0u, 0u};   // row padding
-              }
+              if (!kDefer || !defer) put_da(c, u, da);
             }
             if (NP == 2 && KS > 8) __builtin_amdgcn_sched_barrier(0);   // (one node at a time: registers)
           }

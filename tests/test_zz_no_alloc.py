@@ -48,3 +48,36 @@ def test_static_forward_rejects_large_dims():
     run = s.DeviceRun.from_workload(wl, want_top=True)
     rc, _ = _static_forward(run)
     assert rc == 4
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("I", [2048, 2046])
+def test_static_forward_in_pieces(precision, I):
+    """Inputs whose operand planes have no room in the static array beside the rest are taken in pieces
+    of the step list, the push steps' and the others' apart: the same outputs."""
+    need_gpu()
+    from paper_1904_03409_amd import stacklstm as s
+    T, B, H = (100, 300, 16) if precision == 0 else (100, 800, 16)
+    print(f"[gpu] static forward in pieces I={I} prec={precision}", flush=True)
+    wl = wk.custom(T=T, B=B, I=4, H=H, seed=I)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(I)
+    x = torch.randn(T, B, I, generator=g, device="cuda")
+    W = torch.randn(I, 4 * H, generator=g, device="cuda") * 0.02
+    up = lambda a: torch.from_numpy(a).to("cuda")
+    args = (x, up(wl.ops), W, up(wl.U), up(wl.b), up(wl.h0), up(wl.c0))
+    dims = s.make_dims(T, B, I, H, precision)
+    ws = torch.empty(s.stacklstm_workspace_bytes(dims), dtype=torch.uint8, device="cuda")
+    outs = []
+    for static in (False, True):
+        out = [torch.full((T, B, H), float("nan"), device="cuda") for _ in range(4)]
+        out += [torch.full((n, B), -7, dtype=torch.int32, device="cuda") for n in (T + 1, T)]
+        rc = s.stacklstm_fwd_static(dims, *args, *out, check=False) if static else \
+            s.stacklstm_fwd(dims, *args, *out, ws, check=False)
+        assert rc == 0
+        torch.cuda.synchronize()
+        outs.append(out)
+    planes = (3 if precision == 0 else 1) * T * B * I * 2
+    assert planes > (256 << 20)
+    for k, a, b in zip(OUTS, *outs):
+        assert torch.equal(a, b), k
