@@ -116,9 +116,10 @@ def traffic(fetch_dir, write_dir, copy_bytes, key, json_out, steps_per_run):
                                                      "hbm_bytes_per_launch": hbm}
     fs = _step_bytes(fetch_dir, "FETCH_SIZE", f_scale, steps_per_run)
     ws = _step_bytes(write_dir, "WRITE_SIZE", w_scale, steps_per_run)
-    lines += ["", f"Whole fwd+bwd step (every kernel, {steps_per_run} steps per run): fp32 "
-              f"{(fs['f32'] + ws['f32']) / 1e9:.3f} GB, bf16-GEMM {(fs['bf16'] + ws['bf16']) / 1e9:.3f} GB."]
-    for dt in ("f32", "bf16"):
+    ran = sorted({k.split("/")[1] for k in entries}, reverse=True)
+    lines += ["", f"Whole fwd+bwd step (every kernel, {steps_per_run} steps per run): " +
+              ", ".join(f"{dt} {(fs[dt] + ws[dt]) / 1e9:.3f} GB" for dt in ran) + "."]
+    for dt in ran:
         entries[f"{key}/{dt}/step"] = {"kernel": "all kernels of one fwd+bwd step",
                                        "hbm_bytes_per_launch": fs[dt] + ws[dt]}
     if json_out:
