@@ -15,8 +15,8 @@
 __global__ void k_ctl(uint32_t* ctl, int keep_errors, int bwd);
 template <bool LDS> __global__ void k_plan(PlanArgs a);
 template <int S>
-__global__ void k_split_x(const float* x, const int32_t* order, int lo, int hi, int I, int Ip, int vec, bf16_t* out,
-                          size_t plane, int part, const uint32_t* ctl);
+__global__ void k_split_x(const float* x, const int32_t* order, int lo, int hi, int I, int k0, int Kc, int vec, bf16_t* out,
+                          size_t plane);
 template <int S> __global__ void k_prep_fwd(PrepFwdArgs a);
 template <int S, int V> __global__ void k_prep_bwd(PrepBwdArgs a);
 template <int V> __global__ void k_gather_top(GatherArgs a);
@@ -108,7 +108,7 @@ struct Layout {
   size_t wt, wp, uf, ufi, rin, hu, stash, cpn, hq, h3, cn, xs;
   size_t gf, gc, eg, dcs, dap, sxs, ub, ubi, part, dbp, total;
   int Ip, Hs, H4s, cap, G;
-  int x_rows;                        // rows of x whose planes fit (all, except in the static work space)
+  int x_rows, x_cols;                // rows and columns of x whose planes fit (all, except in the static work space)
   size_t walk_lds;                   // bytes of a wave's walk arrays when they live in LDS, else 0
 };
 
@@ -160,8 +160,15 @@ Layout layout(const slstm_dims* d, bool keep, size_t x_budget) {
   L.h3 = put(keep && S == 3 ? S * NN * L.Hs * 2 : 0);       // (bf16 mode: hq)
   L.cn = put(NN * H * 4);
   L.x_rows = (int)N0;
-  if (x_budget) L.x_rows = (int)std::min<size_t>(N0, std::max<size_t>(x_budget / (S * L.Ip * 2), 1));
-  L.xs = put(S * (size_t)L.x_rows * L.Ip * 2);
+  L.x_cols = L.Ip;
+  if (x_budget) {
+    // all rows if 64 columns of them fit, and as many columns (64 at a time, two K steps) as do
+    const size_t least = std::min(L.Ip, 64), a_col = S * 2;
+    L.x_rows = (int)std::min<size_t>(N0, std::max<size_t>(x_budget / (least * a_col), 1));
+    const size_t cols = x_budget / std::max<size_t>(L.x_rows * a_col, 1) / 64 * 64;
+    if (cols < (size_t)L.Ip) L.x_cols = (int)std::max(cols, least);
+  }
+  L.xs = put(S * (size_t)L.x_rows * L.x_cols * 2);
   if (!keep) {
     L.total = o;
     return L;
@@ -342,32 +349,33 @@ int fwd_impl(const slstm_dims* d, const Plan& p, const Layout& L, bool keep, con
   // planes of x, x W + b of the push nodes
   NtArgs g;
   memset(&g, 0, sizeof(g));
-  g.N = 4 * H; g.K = L.Ip; g.N0 = N0;
-  g.A = xs; g.lda = L.Ip;
-  g.B = (uint16_t*)(ws + L.wt); g.bplane = (size_t)4 * H * L.Ip; g.ldb = L.Ip;
-  g.ctl = ctl; g.C = hu; g.ldc = 4 * H; g.bias = b; g.H = H; g.order = ix.order;
+  g.N = 4 * H; g.N0 = N0;
+  g.bplane = (size_t)4 * H * L.Ip; g.ldb = L.Ip;
+  g.ctl = ctl; g.C = hu; g.ldc = 4 * H; g.H = H; g.order = ix.order;
   g.opar = ix.opar; g.hu = hu; g.cn = cn; g.hcell = h_cell; g.ccell = c_cell;
-  // (all rows of x at once, or in pieces of the step list where the planes of x have less room: then
-  // each of the two passes over them makes the planes of its own rows)
-  const bool once = L.x_rows >= N0;
-  auto x_pass = [&](int epi, bool split) -> int {
-    for (int lo = 0; lo < N0; lo += L.x_rows) {
-      const int hi = std::min(N0, lo + L.x_rows);
-      g.lo = lo; g.hi = hi; g.leaves = epi == NT_LEAF; g.aplane = (size_t)(hi - lo) * L.Ip;
-      if (split) {
-        const int vec = I % 4 == 0 && al16(x);
-        const int grid = grid1d((size_t)(hi - lo) * (L.Ip / 8)), part = once ? 0 : epi == NT_XW ? 1 : 2;
-        if (S == 3)
-          hipLaunchKernelGGL(k_split_x<3>, dim3(grid), dim3(256), 0, st, x, ix.order, lo, hi, I, L.Ip, vec, xs, g.aplane, part, ctl);
-        else
-          hipLaunchKernelGGL(k_split_x<1>, dim3(grid), dim3(256), 0, st, x, ix.order, lo, hi, I, L.Ip, vec, xs, g.aplane, part, ctl);
-      }
-      const int r = hip_status(launch_nt(g, S, epi, st));
-      if (r) return r;
-    }
-    return SLSTM_OK;
+  // one contraction over columns k0 .. k0 + K - 1 of the rows lo .. hi - 1 whose planes are in xs
+  auto x_w = [&](int epi, bool leaves, int lo, int hi, int k0, int K, const float* bias) {
+    g.lo = lo; g.hi = hi; g.leaves = leaves; g.pre = k0 > 0; g.K = K; g.bias = bias;
+    g.A = xs; g.lda = K; g.aplane = (size_t)(hi - lo) * K;
+    g.B = (uint16_t*)(ws + L.wt) + k0;
+    return hip_status(launch_nt(g, S, epi, st));
   };
-  if ((rc = x_pass(NT_XW, true))) return rc;
+  // (planes of all of x at once, or, where they have less room, of a range of its columns and if need be
+  // rows at a time: the sums of both kinds of steps go on in hu, whose rows P .. N0 - 1 no node has, and the
+  // leaves' cells start from theirs)
+  const bool once = L.x_rows >= N0 && L.x_cols >= L.Ip;
+  for (int lo = 0; lo < N0; lo += L.x_rows) {
+    const int hi = std::min(N0, lo + L.x_rows);
+    for (int k0 = 0; k0 < L.Ip; k0 += L.x_cols) {
+      const int K = std::min(L.x_cols, L.Ip - k0), vec = I % 4 == 0 && al16(x);
+      const int grid = grid1d((size_t)(hi - lo) * (K / 8));
+      const size_t plane = (size_t)(hi - lo) * K;
+      if (S == 3) hipLaunchKernelGGL(k_split_x<3>, dim3(grid), dim3(256), 0, st, x, ix.order, lo, hi, I, k0, K, vec, xs, plane);
+      else        hipLaunchKernelGGL(k_split_x<1>, dim3(grid), dim3(256), 0, st, x, ix.order, lo, hi, I, k0, K, vec, xs, plane);
+      if ((rc = x_w(NT_XW, false, lo, hi, k0, K, k0 + K >= L.Ip ? b : nullptr))) return rc;
+      if (!once && (rc = x_w(NT_XW, true, lo, hi, k0, K, nullptr))) return rc;
+    }
+  }
   mark(d, 2, st);
 
   // the recurrence over the levels
@@ -386,7 +394,7 @@ int fwd_impl(const slstm_dims* d, const Plan& p, const Layout& L, bool keep, con
   mark(d, 3, st);
 
   // the leaves (pop and hold steps), then Algorithm 1's return values
-  if ((rc = x_pass(NT_LEAF, !once))) return rc;
+  if ((rc = x_w(NT_LEAF, true, 0, N0, once ? 0 : L.Ip, once ? L.Ip : 0, b))) return rc;
   if (h_top || c_top) {
     GatherArgs a;
     a.top = top; a.ctl = ctl; a.hcell = h_cell; a.h0 = h0; a.ccell = c_cell; a.c0 = c0;

@@ -8,7 +8,8 @@
 // nodes [0, P) or the leaves [P, N0), cut to [lo, hi); A row i is array row i - lo.
 enum { NT_XW = 0, NT_LEAF = 1, NT_DX = 2 };
 struct NtArgs {
-  int N, K;                          // K: columns of A and B (a multiple of 8)
+  int N, K;                          // K: columns of A and B (a multiple of 8; NT_LEAF with pre: 0)
+  int pre;                           // NT_XW, NT_LEAF: the sums go on from C[i][N] (K taken in parts)
   int lo, hi, leaves, N0;
   const uint16_t* A; size_t aplane; int lda;
   const uint16_t* B; size_t bplane; int ldb;

@@ -41,10 +41,11 @@ __device__ __forceinline__ void tile_step(const bf16x8 (&a)[MI][S], const bf16x8
 // planes' products is infinite or NaN as the fp32 sum is. So a wave with NaN among its results
 // takes those from another pass over K with the first planes, straight from memory: half the
 // time of the tile again at most. (One lane through all of K for each NaN: large training step with a NaN
-// in every gradient 236 ms instead of 2.7.) frag(k, a, b): the fragments of K step k.
+// in every gradient 236 ms instead of 2.7.) init(i, j): where the sums started; frag(k, a, b): the
+// fragments of K step k.
 __device__ __forceinline__ bool is_nan(float v) { return v != v; }
-template <int MI, int NJ, typename F>
-__device__ __forceinline__ void redo_nan(f32x4 (&acc)[MI][NJ], int kbeg, int kend, F frag) {
+template <int MI, int NJ, typename I, typename F>
+__device__ __forceinline__ void redo_nan(f32x4 (&acc)[MI][NJ], int kbeg, int kend, I init, F frag) {
   bool bad = false;
 #pragma unroll
   for (int i = 0; i < MI; ++i)
@@ -57,7 +58,7 @@ __device__ __forceinline__ void redo_nan(f32x4 (&acc)[MI][NJ], int kbeg, int ken
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) v[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int j = 0; j < NJ; ++j) v[i][j] = init(i, j);
 #pragma unroll 1
   for (int k = kbeg; k < kend; k += 32) {
     bf16x8 a[MI], b[NJ];
@@ -78,8 +79,8 @@ __device__ __forceinline__ void redo_nan(f32x4 (&acc)[MI][NJ], int kbeg, int ken
 
 }  // namespace
 
-// One block tile of k_nt: 16 MI x (8 / WN) rows, K steps of BK.
-template <int S, int EPI, int MI>
+// One block tile of k_nt: 16 MI x (8 / WN) rows, K steps of BK. PRE: the sums go on from C.
+template <int S, int EPI, int MI, bool PRE>
 __device__ __forceinline__ void nt_tile(const NtArgs& g, int r_lo, int r_hi, int lid, unsigned char* sm, int* s_row,
                                         int* s_par) {
   constexpr int BM = nt_bm(S, MI), BN = nt_bn(S), BK = nt_bk(S, MI), GR = BK / 8;
@@ -136,12 +137,21 @@ __device__ __forceinline__ void nt_tile(const NtArgs& g, int r_lo, int r_hi, int
     }
   };
 
+  // what the sums start from
+  auto init = [&](int i, int j) {
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (PRE) {
+      const int m = 16 * (MI * wm + i) + l16, n = n0 + 16 * (NJ * wn + j) + 4 * lq;
+      if (m < nr && n < g.N) v = *(const f32x4*)(g.C + (size_t)(m0 + m) * g.ldc + n);
+    }
+    return v;
+  };
   f32x4 acc[MI][NJ];
 #pragma unroll
   for (int i = 0; i < MI; ++i)
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  issue(0, 0, 0, 1);
+    for (int j = 0; j < NJ; ++j) acc[i][j] = init(i, j);
+  if (!PRE || g.K > 0) issue(0, 0, 0, 1);
   int buf = 0;
   for (int k0 = 0; k0 < g.K; k0 += BK, buf ^= 1) {
     wait_vm<0>();
@@ -174,7 +184,7 @@ __device__ __forceinline__ void nt_tile(const NtArgs& g, int r_lo, int r_hi, int
   float* ws = reinterpret_cast<float*>(sm) + wave * (16 * 68);   // 16 rows x 64 columns (+ 4) of this wave
   if constexpr (S == 3) {
     // (rows and columns past the tile's: the last ones', whose results nobody reads)
-    redo_nan<MI, NJ>(acc, 0, g.K, [&](int k, bf16x8 (&a)[MI], bf16x8 (&b)[NJ]) {
+    redo_nan<MI, NJ>(acc, 0, g.K, init, [&](int k, bf16x8 (&a)[MI], bf16x8 (&b)[NJ]) {
       const int kl = min(k + 8 * lq, g.K - 8);
       const bool in = k + 8 * lq < g.K;
 #pragma unroll
@@ -196,7 +206,7 @@ __device__ __forceinline__ void nt_tile(const NtArgs& g, int r_lo, int r_hi, int
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int n = n0 + 16 * (NJ * wn + j) + 4 * lq + q;
-      bias[j][q] = (EPI != NT_DX && n < g.N) ? g.bias[perm_to_orig(n, g.H)] : 0.f;
+      bias[j][q] = (EPI != NT_DX && g.bias && n < g.N) ? g.bias[perm_to_orig(n, g.H)] : 0.f;
     }
 
   if constexpr (EPI == NT_LEAF) {
@@ -291,7 +301,7 @@ __device__ __forceinline__ void nt_tile(const NtArgs& g, int r_lo, int r_hi, int
   }
 }
 
-template <int S, int EPI>
+template <int S, int EPI, bool PRE>
 __global__ void __launch_bounds__(512, 2) k_nt(NtArgs g) {
   extern __shared__ __align__(16) unsigned char sm[];
   __shared__ int s_row[256], s_par[256];
@@ -334,10 +344,10 @@ __global__ void __launch_bounds__(512, 2) k_nt(NtArgs g) {
     return;
   }
   switch (sel) {
-    case 1: nt_tile<S, EPI, Q>(g, r_lo, r_hi, lid, sm, s_row, s_par); break;
-    case 2: nt_tile<S, EPI, 2 * Q>(g, r_lo, r_hi, lid, sm, s_row, s_par); break;
-    case 3: nt_tile<S, EPI, 3 * Q>(g, r_lo, r_hi, lid, sm, s_row, s_par); break;
-    default: nt_tile<S, EPI, 4 * Q>(g, r_lo, r_hi, lid, sm, s_row, s_par); break;
+    case 1: nt_tile<S, EPI, Q, PRE>(g, r_lo, r_hi, lid, sm, s_row, s_par); break;
+    case 2: nt_tile<S, EPI, 2 * Q, PRE>(g, r_lo, r_hi, lid, sm, s_row, s_par); break;
+    case 3: nt_tile<S, EPI, 3 * Q, PRE>(g, r_lo, r_hi, lid, sm, s_row, s_par); break;
+    default: nt_tile<S, EPI, 4 * Q, PRE>(g, r_lo, r_hi, lid, sm, s_row, s_par); break;
   }
 }
 
@@ -469,7 +479,7 @@ __global__ void __launch_bounds__(512, 2) k_tn(TnArgs g) {
     if (more) rows(k0 + 2 * BK);
   }
   if constexpr (S == 3) {
-    redo_nan<MI, NJ>(acc, kbeg, kend, [&](int k0, bf16x8 (&a)[MI], bf16x8 (&b)[NJ]) {
+    redo_nan<MI, NJ>(acc, kbeg, kend, [](int, int) { return f32x4{0.f, 0.f, 0.f, 0.f}; }, [&](int k0, bf16x8 (&a)[MI], bf16x8 (&b)[NJ]) {
       uint16_t va[MI][8], vb[NJ][8];
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -545,9 +555,9 @@ __global__ void __launch_bounds__(256) k_reduce_grads(ReduceArgs a) {
   }
 }
 
-template <int S, int EPI>
+template <int S, int EPI, bool PRE>
 static hipError_t launch_nt_t(const NtArgs& g, hipStream_t st) {
-  auto kern = k_nt<S, EPI>;
+  auto kern = k_nt<S, EPI, PRE>;
   constexpr size_t stages = nt_lds(S, nt_mi(S)), leaf = EPI == NT_LEAF ? nt_leaf_lds(S, nt_mi(S)) : 0;
   constexpr int shm = (int)(leaf > stages ? leaf : stages);
   const hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, shm);
@@ -562,9 +572,10 @@ static hipError_t launch_nt_t(const NtArgs& g, hipStream_t st) {
 }
 hipError_t launch_nt(const NtArgs& g, int S, int epi, hipStream_t st) {
   if (g.hi <= g.lo) return hipSuccess;
-#define CASE(S_, E_) \
-  if (S == S_ && epi == E_) return launch_nt_t<S_, E_>(g, st);
-  CASE(1, NT_XW) CASE(1, NT_LEAF) CASE(1, NT_DX) CASE(3, NT_XW) CASE(3, NT_LEAF) CASE(3, NT_DX)
+#define CASE(S_, E_, P_) \
+  if (S == S_ && epi == E_ && (g.pre != 0) == P_) return launch_nt_t<S_, E_, P_>(g, st);
+  CASE(1, NT_XW, false) CASE(1, NT_LEAF, false) CASE(1, NT_DX, false) CASE(1, NT_XW, true) CASE(1, NT_LEAF, true)
+  CASE(3, NT_XW, false) CASE(3, NT_LEAF, false) CASE(3, NT_DX, false) CASE(3, NT_XW, true) CASE(3, NT_LEAF, true)
 #undef CASE
   return hipErrorInvalidValue;
 }

@@ -8,18 +8,17 @@
 // Largest finite magnitude so far and |v| (an infinity is one at any scale)
 __device__ __forceinline__ float max_finite(float m, float v) { return __builtin_isfinite(v) ? fmaxf(m, fabsf(v)) : m; }
 
-// Rows lo .. hi-1 of the step list (push nodes, then leaves) of x as planes [S][hi - lo][Ip],
-// zero past I. part: of those rows all (0), the push nodes' (1) or the leaves' (2).
+// Columns k0 .. k0 + Kc - 1 (multiples of 8) of rows lo .. hi-1 of the step list (push nodes, then leaves) of
+// x as planes [S][hi - lo][Kc], zero past I.
 template <int S>
 __global__ void __launch_bounds__(256) k_split_x(const float* __restrict__ x, const int32_t* __restrict__ order, int lo,
-                                                 int hi, int I, int Ip, int vec, bf16_t* __restrict__ out, size_t plane,
-                                                 int part, const uint32_t* __restrict__ ctl) {
-  const int gr = Ip / 8, P = part ? (int)ctl[CTL_NPUSHF] : 0;
-  const size_t first = part == 2 ? (size_t)max(P - lo, 0) * gr : 0;
-  const size_t n = (size_t)max((part == 1 ? min(hi, P) : hi) - lo, 0) * gr;
-  for (size_t i = first + (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+                                                 int hi, int I, int k0, int Kc, int vec, bf16_t* __restrict__ out,
+                                                 size_t plane) {
+  const int gr = Kc / 8;
+  const size_t n = (size_t)(hi - lo) * gr;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
     const size_t row = i / gr;
-    const int k = (int)(i - row * gr) * 8;
+    const int kc = (int)(i - row * gr) * 8, k = k0 + kc;
     const float* src = x + (size_t)order[lo + row] * I + k;
     float v[8];
     if (vec && k + 8 <= I) {
@@ -32,11 +31,11 @@ __global__ void __launch_bounds__(256) k_split_x(const float* __restrict__ x, co
     uint4 g[S];
     split_granule<S>(v, g);
 #pragma unroll
-    for (int s = 0; s < S; ++s) *(uint4*)(out + s * plane + row * Ip + k) = g[s];
+    for (int s = 0; s < S; ++s) *(uint4*)(out + s * plane + row * Kc + kc) = g[s];
   }
 }
-template __global__ void k_split_x<1>(const float*, const int32_t*, int, int, int, int, int, bf16_t*, size_t, int, const uint32_t*);
-template __global__ void k_split_x<3>(const float*, const int32_t*, int, int, int, int, int, bf16_t*, size_t, int, const uint32_t*);
+template __global__ void k_split_x<1>(const float*, const int32_t*, int, int, int, int, int, int, bf16_t*, size_t);
+template __global__ void k_split_x<3>(const float*, const int32_t*, int, int, int, int, int, int, bf16_t*, size_t);
 
 // Forward operands, by block range:
 //  * W tiles of 32 inputs x 32 units: wt [S][4H][Ip] (rows n = 4u + gate) and wp [S][I][H4s]

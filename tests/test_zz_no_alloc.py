@@ -50,20 +50,30 @@ def test_static_forward_rejects_large_dims():
     assert rc == 4
 
 
-@pytest.mark.parametrize("precision", [0, 1])
-@pytest.mark.parametrize("I", [2048, 2046])
-def test_static_forward_in_pieces(precision, I):
-    """Inputs whose operand planes have no room in the static array beside the rest are taken in pieces
-    of the step list, the push steps' and the others' apart: the same outputs."""
+PIECES = [
+    # (T, B, I, H, precision): planes of x that take several ranges of columns (the last one short; rows of x
+    # without 16-byte alignment), and of which not even 64 columns of all rows fit
+    (100, 300, 2048, 16, 0), (100, 300, 2046, 16, 0), (100, 800, 2048, 16, 1), (100, 800, 2046, 16, 1),
+    (700, 1000, 72, 4, 0),
+]
+
+
+@pytest.mark.parametrize("shape", PIECES)
+def test_static_forward_in_pieces(shape):
+    """Inputs whose operand planes have no room in the static array beside the rest: the projection goes on
+    over ranges of their columns (and rows): the same outputs."""
     need_gpu()
     from paper_1904_03409_amd import stacklstm as s
-    T, B, H = (100, 300, 16) if precision == 0 else (100, 800, 16)
-    print(f"[gpu] static forward in pieces I={I} prec={precision}", flush=True)
+    T, B, I, H, precision = shape
+    print(f"[gpu] static forward in pieces {shape}", flush=True)
     wl = wk.custom(T=T, B=B, I=4, H=H, seed=I)
     g = torch.Generator(device="cuda")
     g.manual_seed(I)
     x = torch.randn(T, B, I, generator=g, device="cuda")
     W = torch.randn(I, 4 * H, generator=g, device="cuda") * 0.02
+    x[3, 5, 10], x[3, 5, I - 1] = float("inf"), -float("inf")   # infinities of one step in two pieces: NaN or not
+    x[9, 6, 7] = x[9, 6, I - 2] = float("inf")
+    x[20, 7, I - 1] = float("inf")
     up = lambda a: torch.from_numpy(a).to("cuda")
     args = (x, up(wl.ops), W, up(wl.U), up(wl.b), up(wl.h0), up(wl.c0))
     dims = s.make_dims(T, B, I, H, precision)
@@ -80,4 +90,4 @@ def test_static_forward_in_pieces(precision, I):
     planes = (3 if precision == 0 else 1) * T * B * I * 2
     assert planes > (256 << 20)
     for k, a, b in zip(OUTS, *outs):
-        assert torch.equal(a, b), k
+        assert torch.equal(torch.isnan(a), torch.isnan(b)) and torch.equal(torch.nan_to_num(a), torch.nan_to_num(b)), k
