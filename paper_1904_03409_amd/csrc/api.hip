@@ -165,8 +165,8 @@ Layout layout(const slstm_dims* d, bool keep, size_t x_budget) {
     // all rows if 64 columns of them fit, and as many columns (64 at a time, two K steps) as do
     const size_t least = std::min(L.Ip, 64), a_col = S * 2;
     L.x_rows = (int)std::min<size_t>(N0, std::max<size_t>(x_budget / (least * a_col), 1));
-    const size_t cols = x_budget / std::max<size_t>(L.x_rows * a_col, 1) / 64 * 64;
-    if (cols < (size_t)L.Ip) L.x_cols = (int)std::max(cols, least);
+    const size_t cols = x_budget / std::max<size_t>(L.x_rows * a_col, 1);
+    if (cols < (size_t)L.Ip) L.x_cols = (int)std::max(cols / 64 * 64, least);
   }
   L.xs = put(S * (size_t)L.x_rows * L.x_cols * 2);
   if (!keep) {
@@ -434,7 +434,7 @@ size_t static_measure(const slstm_dims* d) {
          (d->precision == SLSTM_BF16_GEMM ? align256((T + 1) * B * H * 2) : 0);
 }
 // The forward's layout in the static work space: what is left beside the other parts holds the
-// planes of x, in pieces if need be.
+// planes of x, a range of their columns (and rows) at a time if need be.
 Layout static_layout(const slstm_dims* d) {
   const Layout L = layout(d, false, 1);
   return L.total >= kScratchBytes ? L : layout(d, false, std::max<size_t>(kScratchBytes - L.total, 1));

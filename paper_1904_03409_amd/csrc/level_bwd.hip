@@ -100,7 +100,7 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
   // dA of a child: the planes that dW, dU and dx read, and the bias gradient. Nobody waits for these
   // stores. H > 512: a pass that is not the level's last leaves it to the next one, which does it from
   // LDS while its own operands are on their way (H = 1024, levels of 170 nodes: 50.0 -> 46.7 us a
-  // level). The last pass does it in place (from LDS it costs 0.2 us a level, and after the barrier's
+  // level by the step clock). The last pass does it in place (from LDS it costs 0.2 us a level, and after the barrier's
   // arrival 0.4: the next rows queue behind the stores); so do the others, whose levels gained 1% at
   // most from it (H = 512) or lost up to 4% (H = 300).
   auto put_da = [&](int c, int ou, const f32x4& da) {

@@ -1,5 +1,6 @@
 // Operand preparation: bf16 planes (split.h) of x, W, U and the initial states in the layouts the
-// contractions read, and the interval sums of the upstream gradient. All bandwidth bound.
+// contractions read, and the interval sums of the upstream gradient. Bandwidth bound at large sizes
+// (256 x 240 steps, H = 512: planes of x 4.1 to 5.5 TB/s, interval sums 4.0 to 4.3, where a copy reaches 5.1).
 #include "common.h"
 #include "levels.h"
 #include "prep.h"
