@@ -229,6 +229,14 @@ __device__ __forceinline__ void wait_vm() {
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
   asm volatile("" ::: "memory");
 }
+// A sum with what its additions round off summed beside it, apart from the sum: where that is infinite the
+// rest is NaN and is left out.
+__device__ __forceinline__ void comp_add(float& s, float& e, float v) {
+  const float z = s + v, w = z - s;
+  e += (s - (z - w)) + (v - w);
+  s = z;
+}
+__device__ __forceinline__ float comp_sum(float s, float e) { return __builtin_isfinite(e) ? s + e : s; }
 // A copy of v the compiler cannot see through: what is computed from it is computed where it is
 // used, instead of being kept in registers through a whole kernel.
 __device__ __forceinline__ int opaque(int v) {

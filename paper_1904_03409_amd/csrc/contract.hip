@@ -548,7 +548,23 @@ __global__ void __launch_bounds__(256) k_reduce_grads(ReduceArgs a) {
     const size_t st = bias ? (size_t)H4 : a.stride;
     const int cnt = bias ? a.groups : a.splits;
     f32x4 s = {0.f, 0.f, 0.f, 0.f};
-    for (int z = 0; z < cnt; ++z) s += *(const f32x4*)(src + (size_t)z * st + 4 * u);
+    if (bias) {                                        // (up to 128 groups: compensated)
+      f32x4 e = {0.f, 0.f, 0.f, 0.f};
+      for (int z = 0; z < cnt; ++z) {
+        const f32x4 v = *(const f32x4*)(src + (size_t)z * st + 4 * u);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          float t = s[k], r = e[k];
+          comp_add(t, r, v[k]);
+          s[k] = t;
+          e[k] = r;
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) s[k] = comp_sum(s[k], e[k]);
+    } else {
+      for (int z = 0; z < cnt; ++z) s += *(const f32x4*)(src + (size_t)z * st + 4 * u);
+    }
     float* dst = bias ? a.db : (row < (size_t)I ? a.dW + row * H4 : a.dU + (row - I) * H4);
 #pragma unroll
     for (int k = 0; k < 4; ++k) dst[(size_t)k * H + u] = s[k];

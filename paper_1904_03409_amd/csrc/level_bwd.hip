@@ -66,14 +66,8 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
   }
   const float ui = NP == 2 ? a.uinv[u] : 1.f;               // inverse scale of this thread's unit
 
-  // sums over this thread's nodes for the bias gradient, and of what their additions rounded off (apart
-  // from the sum: where it is infinite they are NaN and are left out)
+  // sums over this thread's nodes for the bias gradient (comp_add)
   float db[4] = {0.f, 0.f, 0.f, 0.f}, dbe[4] = {0.f, 0.f, 0.f, 0.f};
-  auto db_add = [&](int q, float v) {
-    const float z = db[q] + v, w = z - db[q];
-    dbe[q] += (db[q] - (z - w)) + (v - w);
-    db[q] = z;
-  };
   // operands of a pass of children that do not depend on other levels
   struct Pre { f32x4 ga; float cp, gf, ih; int kin; };
   Pre it[NI];
@@ -107,7 +101,7 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
     bf16_t p[4][S];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      db_add(q, da[q]);
+      comp_add(db[q], dbe[q], da[q]);
       split_bf16<S>(da[q], p[q]);
     }
 #pragma unroll
@@ -385,13 +379,17 @@ __global__ void __launch_bounds__(kLevThreads, 2) k_lev_bwd(LevBwdArgs a) {
   // bias gradient of the group: the 16 threads of a unit in order
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < 4; ++q)
-    if (__builtin_isfinite(dbe[q])) db[q] += dbe[q];
+  for (int q = 0; q < 4; ++q) db[q] = comp_sum(db[q], dbe[q]);
   ch_a[kk * 32 + uu] = f32x4{db[0], db[1], db[2], db[3]};
   __syncthreads();
   if (kk == 0 && u_ok) {
-    f32x4 s = ch_a[uu];
-    for (int k = 1; k < 16; ++k) s += ch_a[k * 32 + uu];
+    f32x4 s;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      float t = ch_a[uu][q], e = 0.f;
+      for (int k = 1; k < 16; ++k) comp_add(t, e, ch_a[k * 32 + uu][q]);
+      s[q] = comp_sum(t, e);
+    }
     *(f32x4*)(a.db_part + (size_t)g * H4 + 4 * u) = s;
   }
   // initial states (their gradients from children: the parity that level 1 wrote)

@@ -114,3 +114,26 @@ def test_step_clock(precision):
             assert np.all(np.diff(used[:, :levels], axis=2) >= 0) and not used[:, levels:].any()
             step = np.diff(used[:, :levels, 0], axis=1)
             assert np.all(step > 0 if p == 0 else step < 0)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("B,H", [(301, 33), (1000, 8), (130, 200)])
+def test_bias_gradient_of_many_groups(precision, B, H):
+    """db of equal gate gradients (no weights, one depth) is their number times one of them: the sums over a
+    thread's nodes, a workgroup's threads and up to 128 groups lose one rounding, not one per addition."""
+    need_gpu()
+    from paper_1904_03409_amd.stacklstm import DeviceRun
+    T = 58
+    print(f"[gpu] db of equal gradients B={B} H={H} prec={precision}", flush=True)
+    wl = wk.custom(T=T, B=B, I=4, H=H, seed=1, ops=_ops("alternate", T, B))
+    for a in (wl.x, wl.W, wl.U, wl.b, wl.h0, wl.c0):
+        a[...] = 0
+    v = np.linspace(0.1, 0.7, H).astype(np.float32)
+    wl.dh_top[...] = v
+    r = DeviceRun.from_workload(wl, precision=precision)
+    r.forward()
+    r.backward()
+    db = r.db.cpu().numpy().astype(np.float64)
+    want = 0.25 * v.astype(np.float64) * (B * T // 2)      # o i of a gate at 0, g alone: 0.5 0.5
+    assert np.all(np.abs(db[2 * H:3 * H] / want - 1) <= 2.0 ** -23)
+    assert not db[:2 * H].any() and not db[3 * H:].any()
